@@ -797,6 +797,181 @@ size_t conv_tiled_lds(int nt, int wv = 4, int nw = 1, bool pool1 = false) {
            sizeof(uint4);
 }
 
+// The convolution on grids that the 16 x 4 x 4 tiles above do not divide:
+// conv3d_kernel's products in conv3d_kernel's order (taps outer, 16-channel
+// slices inner, the same MFMA), so every output is bitwise the same, from an
+// LDS halo and LDS weights instead of gathers from memory. A block takes a
+// tile of TX x (16 MT / TX) x 4 points (TX = 2^ltx: 4, 8 or 16), wavefront w
+// its plane z0 + w as MT runs of 16 points, and NT 16-channel output tiles;
+// points beyond the grid are computed on zeros and not stored. Since the taps
+// are the outer loop, the halo holds all input channels. Its rows, and the
+// weights' rows, are cin + 8 elements, an odd multiple of 16 bytes, so that
+// the 8-byte fragment reads of 16 consecutive rows touch every LDS bank once.
+// The weights are staged G taps at a time (all 27 where they fit beside the
+// halo), the next stage's loads held in registers meanwhile. They are the
+// MFMA's first operand (lane (r, q) then holds channels 4q .. 4q + 3 of point
+// r: 8-byte stores). NC = cin / 16 is a constant, so that the fragment reads
+// of a tap row are a base and immediates. Bound by one block's chain (staging
+// latency, then 27 NC steps) on the small grids and by the LDS reads and the
+// exposed staging on the large ones. Against conv3d_kernel (27 gathers of 8
+// bytes per lane and step; two blocks on an 8^3 grid): 8^3 64 -> 64 105 -> 8.7
+// us, 40 x 24 x 56 80 -> 32 85 -> 25 us, 104 x 88 x 120 48 -> 16 336 -> 141 us.
+constexpr int kAnyPW = 6;  // 16-byte weight pieces a thread holds for the next stage
+template <int NC, int MT, int NT>
+__global__ void __launch_bounds__(256) conv3d_any_kernel(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
+    const float *__restrict__ bias, int cout, int nx, int ny, int nz, int ltx, int ntx, int nty,
+    int G, int flip, int relu, const uint16_t *__restrict__ mask, uint16_t *__restrict__ yb,
+    float *__restrict__ yf) {
+    extern __shared__ uint4 lds[];
+    constexpr int cin = 16 * NC, C8 = 2 * NC, RS = C8 + 1;  // 16-byte pieces of a row, its LDS stride
+    constexpr int RE = 8 * RS;                              // the stride in elements
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    const int hx = (1 << ltx) + 2, hy = (16 * MT >> ltx) + 2, hp = hx * hy * 6;
+    // h / hx = h mx >> 16 for halo points h < 65536 / hx (hp <= 648, hx, hy <= 18)
+    const int mx = (65535 + hx) / hx, my = (65535 + hy) / hy;
+    const int cob = blockIdx.y * 16 * NT;
+    const int tz = blockIdx.x / (ntx * nty), rest = blockIdx.x - tz * ntx * nty;
+    const int ty = rest / ntx, tx = rest - ty * ntx;
+    const int x0 = tx << ltx, y0 = ty * (16 * MT >> ltx), z0 = tz * 4;
+    uint4 *wlds = lds + hp * RS;
+
+    // piece c of the stage from tap t0: row (tap, output channel) c / C8 of
+    // NT 16 rows per tap
+    auto wsrc = [&](int t0, int c) __attribute__((always_inline)) {
+        const int row = (int)((uint32_t)c / C8), part = c - row * C8;
+        const int t = t0 + row / (16 * NT), o = row % (16 * NT);
+        return *(const u4v *)(w + (uint32_t)(t * cout + cob + o) * cin + 8 * part);
+    };
+    auto wdst = [&](int c) __attribute__((always_inline)) {
+        const int row = (int)((uint32_t)c / C8);
+        return (u4v *)&wlds[row * RS + (c - row * C8)];
+    };
+    // first stage's weights and the halo: 16-byte pieces, eight loads of a
+    // thread in flight; halo points that no output needs are zeros
+    constexpr int U = 8;
+    const int np = G * 16 * NT * C8;  // pieces of a stage
+    for (int c0 = threadIdx.x; c0 < np; c0 += 256 * U) {
+        u4v v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = wsrc(0, min(c0 + 256 * u, np - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c0 + 256 * u < np) *wdst(c0 + 256 * u) = v[u];
+    }
+    for (int c0 = threadIdx.x; c0 < hp * C8; c0 += 256 * U) {
+        uint4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + 256 * u;
+            const int h = (int)((uint32_t)c / C8), part = c - h * C8;
+            const int hr = h * mx >> 16, hz = hr * my >> 16;
+            const int gx = x0 - 1 + h - hr * hx, gy = y0 - 1 + hr - hz * hy, gz = z0 - 1 + hz;
+            v[u] = uint4{0u, 0u, 0u, 0u};
+            if (hz < 6 && gx <= nx && gy <= ny && gz <= nz) {
+                const int gp = wrap(gx, nx) + nx * (wrap(gy, ny) + ny * wrap(gz, nz));
+                v[u] = *(const uint4 *)(x + (uint32_t)gp * cin + 8 * part);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + 256 * u, h = (int)((uint32_t)c / C8);
+            if (c < hp * C8) lds[h * RS + (c - h * C8)] = v[u];
+        }
+    }
+    // element offsets in LDS of the lane's points at offset (0, 0, 0), slice 0
+    const uint16_t *tile = (const uint16_t *)lds;
+    const uint16_t *wt = (const uint16_t *)wlds + r * RE + 4 * q;
+    int pa[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int i = 16 * mt + r;
+        pa[mt] = (((wave + 1) * hy + (i >> ltx) + 1) * hx + (i & ((1 << ltx) - 1)) + 1) * RE + 4 * q;
+    }
+    f4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
+
+    const int sg = flip ? -RE : RE;
+    u4v pw[kAnyPW];
+    for (int t0 = 0; t0 < 27; t0 += G) {
+        const bool more = t0 + G < 27;
+        __syncthreads();
+        if (more) {
+            unroll<0, kAnyPW>([&](auto J) __attribute__((always_inline)) {
+                // past the last piece: the last again, not stored
+                pw[decltype(J)::value] = wsrc(t0 + G, min((int)threadIdx.x + 256 * decltype(J)::value, np - 1));
+            });
+        }
+        // a row of three taps (dy, dz) at a time: 3 NC steps, every read a
+        // base and an immediate
+        for (int tl = 0; tl < G; tl += 3) {
+            const int row = (t0 + tl) / 3, dy = row % 3 - 1, dz = row / 3 - 1;
+            const int off = sg * (dz * hy + dy) * hx;
+            const uint16_t *wr = wt + tl * 16 * NT * RE;
+            unroll<0, 3>([&](auto X) __attribute__((always_inline)) {
+                constexpr int dx = decltype(X)::value - 1;
+                const uint16_t *at[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) at[mt] = tile + pa[mt] + off + dx * sg;
+#pragma unroll
+                for (int cc = 0; cc < NC; ++cc) {
+                    s4 a[MT], b[NT];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        b[nt] = *(const s4 *)(wr + ((dx + 1) * 16 * NT + nt * 16) * RE + cc * 16);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) a[mt] = *(const s4 *)(at[mt] + cc * 16);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b[nt], a[mt],
+                                                                                     acc[mt][nt], 0, 0, 0);
+                }
+            });
+        }
+        if (more) {
+            __syncthreads();  // this stage's weights are read
+            unroll<0, kAnyPW>([&](auto J) __attribute__((always_inline)) {
+                const int c = threadIdx.x + 256 * decltype(J)::value;
+                if (c < np) *wdst(c) = pw[decltype(J)::value];
+            });
+        }
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int i = 16 * mt + r;
+        const int px = x0 + (i & ((1 << ltx) - 1)), py = y0 + (i >> ltx), pz = z0 + wave;
+        if (px >= nx || py >= ny || pz >= nz) continue;
+        const long p = px + (long)nx * (py + (long)ny * pz);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int co = cob + nt * 16 + 4 * q;
+            float v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[j] = acc[mt][nt][j] + (bias ? bias[co + j] : 0.f);
+                if (relu) v[j] = fmaxf(v[j], 0.f);
+            }
+            if (mask) {
+                const uint2 m = *(const uint2 *)(mask + p * cout + co);
+                const uint32_t mw[2] = {m.x, m.y};
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (!(bf2f((uint16_t)(mw[j >> 1] >> (16 * (j & 1)))) > 0.f)) v[j] = 0.f;
+            }
+            if (yb)
+                *(uint2 *)(yb + p * cout + co) = uint2{uint32_t(f2bf(v[0])) | (uint32_t(f2bf(v[1])) << 16),
+                                                       uint32_t(f2bf(v[2])) | (uint32_t(f2bf(v[3])) << 16)};
+            if (yf) *(f4 *)(yf + p * cout + co) = f4{v[0], v[1], v[2], v[3]};
+        }
+    }
+}
+
 // Weight gradient of one tap over one chunk of points:
 // dW[t][o][i] = sum_p dY[p][o] X[p + d_t][i], an M = cout, N = cin, K = points
 // product. Lane l feeds A[m = l % 16][k = 4 (l / 16) + j] = dY[p_j][o] and
@@ -955,7 +1130,10 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
     }
 }
 
-// Weight gradient on the 16 x 4 x 4 point tiles of the forward kernel:
+// Weight gradient on the 16 x 4 x 4 point tiles of the forward kernel (partial
+// tiles at the ends of an axis included; against the per-tap product that
+// grids with such tiles took: 8^3 64 -> 64 35 -> 14 us, 40 x 24 x 56 80 -> 32
+// 223 -> 30 us, 104 x 88 x 120 48 -> 16 902 -> 97 us, with its reduction):
 // dW[t][o][i] = sum_p dY[p][o] X[p + d_t][i] as M = o, N = i, K = points
 // products on the 16x16x32 BF16 MFMA. A persistent block takes work items
 // blockIdx.x, + gridDim.x, ... (tiles in the forward's XCD slabs where the
@@ -977,8 +1155,8 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
 // partial dW goes to part[block][t][o][i] and the partials are summed in
 // fixed order. One M tile keeps four wavefronts per SIMD (the LDS allows
 // four blocks per CU).
-template <int MT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : 1, 8)))
+template <int MT, bool RAG, bool FLUSH = false>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 1 && !FLUSH ? 4 : 1, 8)))
 wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
                    const uint16_t *__restrict__ dy, int cout,
                    int nx, int ny, int nz,
@@ -996,13 +1174,27 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, q = lane >> 4;
     const int cc = blockIdx.y * 16;
-    const int ntx = nx / kTX, nty = ny / kTY;
-    const int ntile = ntx * nty * (nz / kTZ);
+    // RAG (sizes that the tiles do not divide): the last tiles of an axis
+    // reach beyond the grid, where the output gradient is staged as zeros, and
+    // so is the halo that no point of the grid reads
+    const int ntx = RAG ? (nx + kTX - 1) / kTX : nx / kTX, nty = RAG ? (ny + kTY - 1) / kTY : ny / kTY;
+    const int ntile = ntx * nty * (RAG ? (nz + kTZ - 1) / kTZ : nz / kTZ);
     f4 acc[kNTap][MT];
 #pragma unroll
     for (int u = 0; u < kNTap; ++u)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[u][mt] = f4{0.f, 0.f, 0.f, 0.f};
+    // FLUSH: each tile's products are summed apart and added to the total
+    // (short chains of FP32 additions), for the output channels from
+    // 16 blockIdx.z
+    f4 tot[FLUSH ? kNTap : 1][MT];
+    const int co0 = FLUSH ? 16 * (int)blockIdx.z : 0;
+    if constexpr (FLUSH) {
+#pragma unroll
+        for (int u = 0; u < kNTap; ++u)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) tot[u][mt] = f4{0.f, 0.f, 0.f, 0.f};
+    }
     // bias gradient (blocks of the first input chunk): wavefront 3, which has
     // two tap rows to wavefront 0's three, adds dY times ones on the MFMA
     const bool do_bias = bpart != nullptr && blockIdx.y == 0;
@@ -1058,10 +1250,15 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
             int h, e0;
             if (xpiece(c, h, e0)) {
                 const int hx = h % kHX, hy = (h / kHX) % kHY, hz = h / (kHX * kHY);
+                if constexpr (RAG) {
+                    xv[it][0] = xv[it][1] = uint4{0u, 0u, 0u, 0u};
+                    if (y0 - 1 + hy > ny || z0 - 1 + hz > nz || x0 - 1 + hx > nx) continue;
+                }
                 const int gy = wrap(y0 - 1 + hy, ny), gz = wrap(z0 - 1 + hz, nz);
                 const int g0 = wrap(x0 - 1 + hx, nx) + nx * (gy + ny * gz);
-                const int g1 = wrap(x0 + hx, nx) + nx * (gy + ny * gz);
                 xv[it][0] = *(const uint4 *)(x + g0 * cin + cc + e0);
+                if (RAG && x0 + hx > nx) continue;
+                const int g1 = wrap(x0 + hx, nx) + nx * (gy + ny * gz);
                 xv[it][1] = *(const uint4 *)(x + g1 * cin + cc + e0);
             }
         }
@@ -1070,9 +1267,15 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
             const int c = threadIdx.x + 256 * it;
             int pl, oc;
             dpiece(c, pl, oc);
-            const int gp = (x0 + (pl & 15)) + nx * ((y0 + ((pl >> 4) & 3)) + ny * (z0 + (pl >> 6)));
-            dv[it][0] = *(const uint4 *)(dy + gp * cout + 8 * oc);
-            dv[it][1] = *(const uint4 *)(dy + (gp + 1) * cout + 8 * oc);
+            const int gx = x0 + (pl & 15), gy = y0 + ((pl >> 4) & 3), gz = z0 + (pl >> 6);
+            const int gp = gx + nx * (gy + ny * gz);
+            if constexpr (RAG) {
+                dv[it][0] = dv[it][1] = uint4{0u, 0u, 0u, 0u};
+                if (gx >= nx || gy >= ny || gz >= nz) continue;
+            }
+            dv[it][0] = *(const uint4 *)(dy + gp * cout + co0 + 8 * oc);
+            if (RAG && gx + 1 >= nx) continue;
+            dv[it][1] = *(const uint4 *)(dy + (gp + 1) * cout + co0 + 8 * oc);
         }
     };
     if ((int)blockIdx.x < ntile) fetch(blockIdx.x);
@@ -1113,6 +1316,21 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
         else if (wave < 3 || !do_bias) wgrad_steps<MT, 2, false>(dyt, xht, arow, xlane, wave, acc);
         else wgrad_steps<MT, 2, true>(dyt, xht, arow, xlane, 3, acc);
         __builtin_amdgcn_s_setprio(0);
+        if constexpr (FLUSH) {
+#pragma unroll
+            for (int u = 0; u < kNTap; ++u)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    tot[u][mt] += acc[u][mt];
+                    acc[u][mt] = f4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    }
+    if constexpr (FLUSH) {
+#pragma unroll
+        for (int u = 0; u < kNTap; ++u)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[u][mt] = tot[u][mt];
     }
     // D[m = 4 q + j][n = r] of tap t, M tile mt: dW[t][mt 16 + 4 q + j][cc + r];
     // accumulator u = 3 rr + d holds tap t = d + 3 (dy + 1) + 9 (dz + 1) of row
@@ -1126,13 +1344,13 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                part[(((long)blockIdx.x * 27 + t) * cout + mt * 16 + 4 * q + j) * cin + cc + r] = acc[u][mt][j];
+                part[(((long)blockIdx.x * 27 + t) * cout + co0 + mt * 16 + 4 * q + j) * cin + cc + r] = acc[u][mt][j];
     }
     if (do_bias && wave == 3 && r == 0) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bpart[(long)blockIdx.x * cout + mt * 16 + 4 * q + j] = acc[6][mt][j];
+            for (int j = 0; j < 4; ++j) bpart[(long)blockIdx.x * cout + co0 + mt * 16 + 4 * q + j] = acc[6][mt][j];
     }
 }
 
@@ -2030,12 +2248,18 @@ int conv_blocks(int nt, int nchunk, int cus, int wv) {
     return (nt == 1 ? (nchunk == 1 ? 8 : 4) : 3) * cus;
 }
 
-// The tiled weight gradient: lattice sizes multiples of the 16 x 4 x 4 tile,
-// 32-bit element indices, aligned operands, at most 64 output channels.
+// 16 x 4 x 4 point tiles that cover a grid.
+long rag_tiles(int nx, int ny, int nz) {
+    return (long)((nx + kTX - 1) / kTX) * ((ny + kTY - 1) / kTY) * ((nz + kTZ - 1) / kTZ);
+}
+
+// The tiled weight gradient: 32-bit element indices, aligned operands, at
+// most 64 output channels, and more than one tile's worth of points (below,
+// one launch of the per-tap product is as fast: 4^3 64 -> 64, 15 us both).
 bool wgrad_tiled_ok(const void *x, int cin, const void *dy, int cout, int nx, int ny, int nz) {
     const long P = (long)nx * ny * nz;
-    return nx % kTX == 0 && ny % kTY == 0 && nz % kTZ == 0 && cout <= 64 && elems_ok(P, cin) &&
-           elems_ok(P, cout) && ((uintptr_t)x & 15) == 0 && ((uintptr_t)dy & 15) == 0;
+    return cout <= 64 && P >= kTX * kTY * kTZ && elems_ok(P, cin) && elems_ok(P, cout) &&
+           aligned16(x) && aligned16(dy);
 }
 
 // Persistent blocks of the tiled weight gradient per 16-channel input chunk:
@@ -2236,6 +2460,101 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
 #undef SUR_CONV_LAUNCH
 }
 
+constexpr size_t kMaxLds = 160 * 1024;  // of a block, and of a CU
+
+// Points of the tiles 2^ltx x (16 mt / 2^ltx) x 4 that cover a grid.
+long any_padded(int mt, int ltx, int nx, int ny, int nz) {
+    const long tx = 1 << ltx, ty = 16 * mt >> ltx;
+    return (nx + tx - 1) / tx * tx * ((ny + ty - 1) / ty * ty) * ((nz + 3) / 4 * 4);
+}
+
+// Tile width of conv3d_any_kernel: the one that covers the grid with the
+// fewest points, the widest of equals.
+int any_ltx(int mt, int nx, int ny, int nz) {
+    int best = 4;
+    for (int l = 3; l >= 2; --l)
+        if (any_padded(mt, l, nx, ny, nz) < any_padded(mt, best, nx, ny, nz)) best = l;
+    return best;
+}
+
+// Launches conv3d_any_kernel where it applies: 32-bit element indices, the
+// alignments of its accesses, up to 128 input channels. False: nothing launched.
+bool conv_any_launch(const void *x, int cin, const void *w, const float *bias, int cout, int nx,
+                     int ny, int nz, int flip, int relu, const void *mask, void *y_bf16,
+                     float *y_f32, hipStream_t st) {
+    const long P = (long)nx * ny * nz;
+    if (cin > 128 || !elems_ok(P, cin) || !elems_ok(P, cout) || !aligned16(x) || !aligned16(y_f32) ||
+        !aligned16(w) || ((uintptr_t)mask & 7) || ((uintptr_t)y_bf16 & 7))
+        return false;
+    // the widest block tile (most products per fragment read, least halo)
+    // that still gives one and a half blocks per CU; below that the time is
+    // one block's chain, shortest with one run and one output tile
+    const int no = cout / 16;
+    const long cus = device_cus() > 0 ? device_cus() : 256;
+    const int cand[6][2] = {{4, 3}, {4, 2}, {2, 2}, {4, 1}, {2, 1}, {1, 1}};
+    int mt = 0, nt = 0, ltx = 0, tx = 0, ty = 0;
+    long ntile = 0;
+    size_t halo = 0, tap = 0;
+    for (const auto &c : cand) {
+        if (no % c[1]) continue;
+        const int l = any_ltx(c[0], nx, ny, nz);
+        const size_t h = (size_t)((1 << l) + 2) * ((16 * c[0] >> l) + 2) * 6 * (2 * cin + 16);
+        const size_t t = (size_t)16 * c[1] * (2 * cin + 16);
+        if (h + 3 * t > kMaxLds) continue;
+        const long n = any_padded(c[0], l, nx, ny, nz) / (64 * c[0]);
+        mt = c[0];
+        nt = c[1];
+        ltx = l;
+        tx = 1 << l;
+        ty = 16 * mt >> l;
+        ntile = n;
+        halo = h;
+        tap = t;
+        if (2 * n * (no / nt) >= 3 * cus) break;
+    }
+    if (mt == 0) return false;
+    // taps per weight stage: the most that cost no block per CU (a block
+    // alone on its CU leaves it idle while it stages: 48 -> 16 channels on
+    // 104 x 88 x 120, 141 us with 3 taps and two blocks, 214 with all 27 and
+    // one) and that a thread's registers hold
+    const long need = (ntile * (no / nt) + cus - 1) / cus;
+    auto per_cu = [&](int g) { return std::min(need, (long)(kMaxLds / (halo + g * tap))); };
+    int G = 27;
+    while (G > 3 && (per_cu(G) < per_cu(3) || (G < 27 && G * 2 * nt * cin > 256 * kAnyPW))) G /= 3;
+    const size_t lds = halo + G * tap;
+    const int ntx = (nx + tx - 1) / tx, nty = (ny + ty - 1) / ty;
+    const dim3 grid((unsigned)ntile, (unsigned)(no / nt));
+#define SUR_ANY_LAUNCH(C, M, N)                                                                  \
+    hipLaunchKernelGGL((conv3d_any_kernel<C, M, N>), grid, dim3(256), lds, st, (const uint16_t *)x, \
+                       (const uint16_t *)w, bias, cout, nx, ny, nz, ltx, ntx, nty, G, flip, relu,  \
+                       (const uint16_t *)mask, (uint16_t *)y_bf16, y_f32)
+#define SUR_ANY_N(C)                             \
+    case C:                                      \
+        switch (10 * mt + nt) {                  \
+            case 43: SUR_ANY_LAUNCH(C, 4, 3); break; \
+            case 42: SUR_ANY_LAUNCH(C, 4, 2); break; \
+            case 22: SUR_ANY_LAUNCH(C, 2, 2); break; \
+            case 41: SUR_ANY_LAUNCH(C, 4, 1); break; \
+            case 21: SUR_ANY_LAUNCH(C, 2, 1); break; \
+            default: SUR_ANY_LAUNCH(C, 1, 1); break; \
+        }                                        \
+        break;
+    switch (cin / 16) {
+        SUR_ANY_N(1)
+        SUR_ANY_N(2)
+        SUR_ANY_N(3)
+        SUR_ANY_N(4)
+        SUR_ANY_N(5)
+        SUR_ANY_N(6)
+        SUR_ANY_N(7)
+        SUR_ANY_N(8)
+        default: return false;
+    }
+#undef SUR_ANY_N
+#undef SUR_ANY_LAUNCH
+    return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2253,6 +2572,8 @@ int sur_conv3d(const void *x, int32_t cin, const void *w, const float *bias, int
                           y_bf16, y_f32, nullptr, (hipStream_t)stream);
         return launched();
     }
+    if (conv_any_launch(x, cin, w, bias, cout, nx, ny, nz, flip, relu, mask, y_bf16, y_f32, (hipStream_t)stream))
+        return launched();
     const dim3 grid((unsigned)((P + 255) / 256), (unsigned)((cout + 63) / 64));
     hipLaunchKernelGGL(conv3d_kernel, grid, dim3(256), 0, (hipStream_t)stream, (const uint16_t *)x,
                        cin, (const uint16_t *)w, bias, cout, nx, ny, nz, flip, relu,
@@ -2324,12 +2645,30 @@ int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, i
         const dim3 grid((unsigned)nch, (unsigned)(cin / 16));
         // the bias partials follow the weight partials: one per block
         float *bp = dbias ? scratch + nch * n : nullptr;
+        const bool rag = nx % kTX || ny % kTY || nz % kTZ;
+        // long chains of additions (48 -> 16 on 104 x 88 x 120, 25 tiles a
+        // block: 5.3e-7 relative error of dW against 2.9e-7 of the per-tap
+        // product) and the smallest grids (8^3 64 -> 64: 9.0e-8 against
+        // 7.2e-8; and 32 blocks instead of 8) take the flushed form (1.6e-7
+        // and 7.1e-8); in between the plain form is as exact and faster
+        const long tiles = rag_tiles(nx, ny, nz);
+        if (rag && (tiles > 8 * nch || P < 4096)) {
+            const dim3 gz(grid.x, grid.y, (unsigned)(cout / 16));
+            hipLaunchKernelGGL((wgrad_tiled_kernel<1, true, true>), gz, dim3(256), 0, s, xb, cin, db,
+                               cout, nx, ny, nz, scratch, bp);
+        } else
+#define SUR_WG_LAUNCH(M)                                                                             \
+    if (rag) hipLaunchKernelGGL((wgrad_tiled_kernel<M, true>), grid, dim3(256), 0, s, xb, cin, db,   \
+                                cout, nx, ny, nz, scratch, bp);                                      \
+    else hipLaunchKernelGGL((wgrad_tiled_kernel<M, false>), grid, dim3(256), 0, s, xb, cin, db, cout, \
+                            nx, ny, nz, scratch, bp)
         switch (cout / 16) {
-            case 1: hipLaunchKernelGGL(wgrad_tiled_kernel<1>, grid, dim3(256), 0, s, xb, cin, db, cout, nx, ny, nz, scratch, bp); break;
-            case 2: hipLaunchKernelGGL(wgrad_tiled_kernel<2>, grid, dim3(256), 0, s, xb, cin, db, cout, nx, ny, nz, scratch, bp); break;
-            case 3: hipLaunchKernelGGL(wgrad_tiled_kernel<3>, grid, dim3(256), 0, s, xb, cin, db, cout, nx, ny, nz, scratch, bp); break;
-            default: hipLaunchKernelGGL(wgrad_tiled_kernel<4>, grid, dim3(256), 0, s, xb, cin, db, cout, nx, ny, nz, scratch, bp); break;
+            case 1: SUR_WG_LAUNCH(1); break;
+            case 2: SUR_WG_LAUNCH(2); break;
+            case 3: SUR_WG_LAUNCH(3); break;
+            default: SUR_WG_LAUNCH(4); break;
         }
+#undef SUR_WG_LAUNCH
         tiled_bp = bp;
         bias_done = true;
     } else {
