@@ -80,11 +80,6 @@ __device__ __forceinline__ float ls_psi_f(float f, float W) {
     f = fminf(fmaxf(f, (float)LS_EPS), 1.f - (float)LS_EPS);
     return 0.25f * W * logf(f / (1.f - f));
 }
-__device__ __forceinline__ double ls_psi(double f, double W) {
-    f = fmin(fmax(f, LS_EPS), 1.0 - LS_EPS);
-    return 0.25 * W * log(f / (1.0 - f));
-}
-__device__ __forceinline__ double ls_phi(double s, double W) { return 0.5 * (1.0 + tanh(2.0 * s / W)); }
 __device__ __forceinline__ float ls_phi_f(float s, float W) { return 0.5f * (1.f + tanhf(2.f * s / W)); }
 
 // ------------------------------------------------------------ convolution
@@ -1895,6 +1890,7 @@ __global__ void __launch_bounds__(1024) final_sum_kernel(const double *__restric
                                                          double scale, double *__restrict__ out) {
     __shared__ double red[16];
     double s = 0.0;
+#pragma unroll 8
     for (long k = threadIdx.x; k < n; k += 1024) s += part[k];
     s = wsum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -1944,6 +1940,58 @@ __global__ void coarsen_kernel(const float *__restrict__ phi, const float *__res
         const float v = ch < 5 ? 0.125f * s[ch] / scale[ch] : 0.f;
         if (cf) cf[qq * 16 + ch] = v;
         if (cb) cb[qq * 16 + ch] = f2bf(v);
+    }
+}
+
+// The same with 8-byte reads of the x pairs and 16-byte stores: a thread
+// averages one cell, the block's 256 cells pass through LDS, and four lanes
+// write one cell's row (a row written by one thread puts a wavefront's stores
+// 64 bytes apart). Rows of phi, u and p 8-byte aligned, cf 16, cb 8. Bound by
+// HBM: 256^3 197 -> 105 us (470 MB).
+__global__ void __launch_bounds__(256) coarsen_rows_kernel(const float *__restrict__ phi,
+                                                           const float *__restrict__ u,
+                                                           const float *__restrict__ p, int nx, int ny,
+                                                           int nz, const float *__restrict__ scale,
+                                                           float *__restrict__ cf,
+                                                           uint16_t *__restrict__ cb) {
+    __shared__ float val[256][5];
+    const int cx = nx / 2, cy = ny / 2, cz = nz / 2;
+    const long Pc = (long)cx * cy * cz, q0 = (long)blockIdx.x * 256, qq = q0 + threadIdx.x;
+    const long N = (long)nx * ny * nz;
+    if (qq < Pc) {
+        int X, Y, Z;
+        coords(qq, cx, cy, X, Y, Z);
+        float s[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+        const float *src[5] = {phi, u, u + N, u + 2 * N, p};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const long f = 2 * X + (long)nx * ((2 * Y + (k & 1)) + (long)ny * (2 * Z + (k >> 1)));
+#pragma unroll
+            for (int ch = 0; ch < 5; ++ch) {
+                const float2 v = *(const float2 *)(src[ch] + f);
+                s[ch] += v.x;
+                s[ch] += v.y;
+            }
+        }
+#pragma unroll
+        for (int ch = 0; ch < 5; ++ch) val[threadIdx.x][ch] = 0.125f * s[ch] / scale[ch];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const int e = threadIdx.x + 256 * it, c = e >> 2, j = e & 3;
+        if (q0 + c >= Pc) continue;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        if (j == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = val[c][k];
+        } else if (j == 1) {
+            v[0] = val[c][4];
+        }
+        if (cf) *(float4 *)(cf + (q0 + c) * 16 + 4 * j) = float4{v[0], v[1], v[2], v[3]};
+        if (cb)
+            *(uint2 *)(cb + (q0 + c) * 16 + 4 * j) = uint2{uint32_t(f2bf(v[0])) | (uint32_t(f2bf(v[1])) << 16),
+                                                           uint32_t(f2bf(v[2])) | (uint32_t(f2bf(v[3])) << 16)};
     }
 }
 
@@ -2113,80 +2161,114 @@ __global__ void features_kernel(float *__restrict__ s, int nx, int ny, int nz) {
 }
 
 // Fine update from two coarse states s0 -> s1: u and p get the trilinear
-// prolongation of the change; phi moves its level set: the coarse change of
-// psi is prolonged and phi <- phi + Phi(Psi(phi) + dpsi) - Phi(Psi(phi))
-// (no change where dpsi = 0).
-__global__ void prolong_update_kernel(const float *__restrict__ s0, const float *__restrict__ s1,
-                                      int cx, int cy, int cz, const float *__restrict__ scale,
-                                      float width, double *__restrict__ phi,
-                                      double *__restrict__ u, double *__restrict__ p) {
+// prolongation of the change; phi moves its level set: the coarse change d of
+// psi is prolonged and phi <- phi + Phi(Psi(phi) + d) - Phi(Psi(phi)). With
+// Psi(f) = (W/4) ln(f/(1 - f)) and Phi its inverse, that difference is
+// f (1 - f) m / (1 + f m), m = exp(4 d/W) - 1: one expm1 and one division
+// instead of a logarithm and two hyperbolic tangents, without their
+// cancellation (no change where d = 0).
+// A block takes tiles of 2^ltx x 4 x (512 >> ltx) fine nodes, eight a thread.
+// The coarse cells around a tile (at most 34 x 4 x 6) are differenced once
+// into LDS, their psi included; per node that took sixteen logarithms and 40
+// reads of 64-byte rows. The sums of phi and of max(phi (1 - phi), 0) before
+// and after the update, which the mass restoration needs, come from the same
+// pass: four FP64 values per block. Bound by HBM: 256^3 1080 -> 350 us with
+// the two separate passes of sums (1.6 GB).
+constexpr int kPuCells = 34 * 4 * 6;
+
+__global__ void __launch_bounds__(256) prolong_update_kernel(
+    const float *__restrict__ s0, const float *__restrict__ s1, int cx, int cy, int cz,
+    const float *__restrict__ scale, float width, int ltx, int ntx, int nty, long ntiles,
+    double *__restrict__ phi, double *__restrict__ u, double *__restrict__ p,
+    double *__restrict__ part) {
+    __shared__ float cell[5][kPuCells];
+    __shared__ double red[4][4];
     const int nx = 2 * cx, ny = 2 * cy, nz = 2 * cz;
     const long N = (long)nx * ny * nz;
-    const long f = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= N) return;
-    int X, Y, Z;
-    coords(f, nx, ny, X, Y, Z);
-    auto lo = [](int X) { return (X - 1) >> 1; };
-    const int x0 = lo(X), y0 = lo(Y), z0 = lo(Z);
-    const float wx = (X & 1) ? 0.25f : 0.75f, wy = (Y & 1) ? 0.25f : 0.75f, wz = (Z & 1) ? 0.25f : 0.75f;
-    float acc[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < 8; ++k) {
-        const int ix = wrap(x0 + (k & 1), cx), iy = wrap(y0 + ((k >> 1) & 1), cy), iz = wrap(z0 + (k >> 2), cz);
-        const float w = ((k & 1) ? wx : 1.f - wx) * (((k >> 1) & 1) ? wy : 1.f - wy) * ((k >> 2) ? wz : 1.f - wz);
-        const long qq = (ix + (long)cx * (iy + (long)cy * iz)) * 16;
-        acc[0] += w * (ls_psi_f(scale[0] * s1[qq], width) - ls_psi_f(scale[0] * s0[qq], width));
-        for (int ch = 1; ch < 5; ++ch) acc[ch] += w * (s1[qq + ch] - s0[qq + ch]);
+    const int tz = 512 >> ltx;
+    const int hx = (1 << (ltx - 1)) + 2, hz = tz / 2 + 2;  // cells of a tile: hx x 4 x hz
+    const float sc0 = scale[0], sc1 = scale[1], sc2 = scale[2], sc3 = scale[3], sc4 = scale[4];
+    const double w4 = 4.0 / (double)width;
+    double a0 = 0.0, b0 = 0.0, a1 = 0.0, b1 = 0.0;
+    for (long t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int bz = (int)(t / ((long)ntx * nty)), rest = (int)(t - (long)bz * ntx * nty);
+        const int by = rest / ntx, bx = rest - by * ntx;
+        const int x0 = bx << ltx, y0 = by * 4, z0 = bz * tz;
+        __syncthreads();  // the previous tile's cells are read
+        for (int c = threadIdx.x; c < hx * 4 * hz; c += 256) {
+            const int r = c / hx;
+            const int ix = x0 / 2 - 1 + c - r * hx, iy = y0 / 2 - 1 + (r & 3), iz = z0 / 2 - 1 + (r >> 2);
+            if (ix > cx || iy > cy || iz > cz) continue;  // no node of the grid reads it
+            const long qq = (wrap(ix, cx) + (long)cx * (wrap(iy, cy) + (long)cy * wrap(iz, cz))) * 16;
+            cell[0][c] = ls_psi_f(sc0 * s1[qq], width) - ls_psi_f(sc0 * s0[qq], width);
+#pragma unroll
+            for (int ch = 1; ch < 5; ++ch) cell[ch][c] = s1[qq + ch] - s0[qq + ch];
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (int k8 = 0; k8 < 8; ++k8) {
+            const int e = threadIdx.x + 256 * k8;
+            const int lx = e & ((1 << ltx) - 1), ly = (e >> ltx) & 3, lz = e >> (ltx + 2);
+            const int X = x0 + lx, Y = y0 + ly, Z = z0 + lz;
+            if (X >= nx || Y >= ny || Z >= nz) continue;
+            // fine node X sits between the cells floor((X - 1)/2) and the next
+            const int c0 = ((lx + 1) >> 1) + hx * (((ly + 1) >> 1) + 4 * ((lz + 1) >> 1));
+            const float wx = (X & 1) ? 0.25f : 0.75f, wy = (Y & 1) ? 0.25f : 0.75f, wz = (Z & 1) ? 0.25f : 0.75f;
+            float acc[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float w = ((k & 1) ? wx : 1.f - wx) * (((k >> 1) & 1) ? wy : 1.f - wy) * ((k >> 2) ? wz : 1.f - wz);
+                const int c = c0 + (k & 1) + hx * (((k >> 1) & 1) + 4 * (k >> 2));
+#pragma unroll
+                for (int ch = 0; ch < 5; ++ch) acc[ch] += w * cell[ch][c];
+            }
+            const long f = X + (long)nx * (Y + (long)ny * Z);
+            const double f0 = phi[f];
+            const double fc = fmin(fmax(f0, LS_EPS), 1.0 - LS_EPS);
+            const double m = expm1(w4 * (double)acc[0]);
+            const double f1 = f0 + fc * (1.0 - fc) * m / fma(fc, m, 1.0);
+            phi[f] = f1;
+            u[f] += (double)(sc1 * acc[1]);
+            u[N + f] += (double)(sc2 * acc[2]);
+            u[2 * N + f] += (double)(sc3 * acc[3]);
+            p[f] += (double)(sc4 * acc[4]);
+            a0 += f0;
+            b0 += fmax(f0 * (1.0 - f0), 0.0);
+            a1 += f1;
+            b1 += fmax(f1 * (1.0 - f1), 0.0);
+        }
     }
-    const double f0 = phi[f];
-    const double so = ls_psi(f0, width);
-    phi[f] = f0 + (ls_phi(so + (double)acc[0], width) - ls_phi(so, width));
-    u[f] += (double)(scale[1] * acc[1]);
-    u[N + f] += (double)(scale[2] * acc[2]);
-    u[2 * N + f] += (double)(scale[3] * acc[3]);
-    p[f] += (double)(scale[4] * acc[4]);
-}
-
-// Per-block FP64 sums {sum phi, sum max(phi (1 - phi), 0)} of a fine field.
-__global__ void __launch_bounds__(256) field_sums_kernel(const double *__restrict__ phi, long N,
-                                                         double *__restrict__ part) {
-    __shared__ double red[2][4];
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    double a = 0.0, b = 0.0;
-    if (i < N) {
-        a = phi[i];
-        b = fmax(a * (1.0 - a), 0.0);
-    }
-    a = wsum(a);
-    b = wsum(b);
+    double v[4] = {wsum(a0), wsum(b0), wsum(a1), wsum(b1)};
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (lane == 0) {
-        red[0][wv] = a;
-        red[1][wv] = b;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) red[k][wv] = v[k];
     }
     __syncthreads();
-    if (threadIdx.x < 2) {
+    if (threadIdx.x < 4) {
         const int k = threadIdx.x;
-        part[(long)blockIdx.x * 2 + k] = ((red[k][0] + red[k][1]) + red[k][2]) + red[k][3];
+        part[(long)blockIdx.x * 4 + k] = ((red[k][0] + red[k][1]) + red[k][2]) + red[k][3];
     }
 }
 
-__global__ void __launch_bounds__(1024) sums2_final_kernel(const double *__restrict__ part, long nb,
+// Sums of the rows of part (four FP64 values each), in a fixed order.
+__global__ void __launch_bounds__(1024) sums4_final_kernel(const double *__restrict__ part, long nb,
                                                            double *__restrict__ out) {
-    __shared__ double red[2][16];
-    double a = 0.0, b = 0.0;
+    __shared__ double red[4][16];
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
     for (long k = threadIdx.x; k < nb; k += 1024) {
-        a += part[2 * k];
-        b += part[2 * k + 1];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] += part[4 * k + j];
     }
-    a = wsum(a);
-    b = wsum(b);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) {
-        red[0][wv] = a;
-        red[1][wv] = b;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const double r = wsum(v[j]);
+        if (lane == 0) red[j][wv] = r;
     }
     __syncthreads();
-    if (threadIdx.x < 2) {
+    if (threadIdx.x < 4) {
         double r = 0.0;
         for (int w = 0; w < 16; ++w) r += red[threadIdx.x][w];
         out[threadIdx.x] = r;
@@ -2960,8 +3042,12 @@ int sur_coarsen(const float *phi, const float *u, const float *p, int32_t nx, in
         nx % 2 || ny % 2 || nz % 2)
         return SUR_EINVAL;
     const long Pc = (long)(nx / 2) * (ny / 2) * (nz / 2);
-    hipLaunchKernelGGL(coarsen_kernel, grid1(Pc), dim3(256), 0, (hipStream_t)stream, phi, u, p, nx,
-                       ny, nz, scale, coarse_f32, (uint16_t *)coarse_bf16);
+    if ((((uintptr_t)phi | (uintptr_t)u | (uintptr_t)p | (uintptr_t)coarse_bf16) & 7) == 0 && aligned16(coarse_f32))
+        hipLaunchKernelGGL(coarsen_rows_kernel, grid1(Pc), dim3(256), 0, (hipStream_t)stream, phi, u, p,
+                           nx, ny, nz, scale, coarse_f32, (uint16_t *)coarse_bf16);
+    else
+        hipLaunchKernelGGL(coarsen_kernel, grid1(Pc), dim3(256), 0, (hipStream_t)stream, phi, u, p, nx,
+                           ny, nz, scale, coarse_f32, (uint16_t *)coarse_bf16);
     return launched();
 }
 
@@ -3027,12 +3113,17 @@ int sur_prolong_update(const float *s0, const float *s1, int32_t cnx, int32_t cn
     hipStream_t st = (hipStream_t)stream;
     const long N = 8L * cnx * cny * cnz;
     const long nb = grid1(N).x;
-    hipLaunchKernelGGL(field_sums_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const double *)phi, N, scratch);
-    hipLaunchKernelGGL(sums2_final_kernel, dim3(1), dim3(1024), 0, st, (const double *)scratch, nb, sums);
-    hipLaunchKernelGGL(prolong_update_kernel, dim3((unsigned)nb), dim3(256), 0, st, s0, s1, cnx, cny, cnz,
-                       scale, (float)width, phi, u, p);
-    hipLaunchKernelGGL(field_sums_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const double *)phi, N, scratch);
-    hipLaunchKernelGGL(sums2_final_kernel, dim3(1), dim3(1024), 0, st, (const double *)scratch, nb, sums + 2);
+    // tile width: the x size, 16 to 64 nodes; the blocks' sums fill at most
+    // the scratch of 2 doubles per 256 nodes (one block writes sums itself)
+    const int ltx = 2 * cnx > 32 ? 6 : (2 * cnx > 16 ? 5 : 4), tz = 512 >> ltx;
+    const int ntx = (2 * cnx + (1 << ltx) - 1) >> ltx, nty = (2 * cny + 3) / 4;
+    const long ntiles = (long)ntx * nty * ((2 * cnz + tz - 1) / tz);
+    const long nblk = std::max(1L, std::min(ntiles, nb / 2));
+    double *part = nblk > 1 ? scratch : sums;
+    hipLaunchKernelGGL(prolong_update_kernel, dim3((unsigned)nblk), dim3(256), 0, st, s0, s1, cnx, cny, cnz,
+                       scale, (float)width, ltx, ntx, nty, ntiles, phi, u, p, part);
+    if (nblk > 1)
+        hipLaunchKernelGGL(sums4_final_kernel, dim3(1), dim3(1024), 0, st, (const double *)scratch, nblk, sums);
     hipLaunchKernelGGL(fix_mass_field_kernel, dim3((unsigned)nb), dim3(256), 0, st, phi, N,
                        (const double *)(sums + 2), (const double *)sums);
     return launched();
