@@ -8,6 +8,7 @@
 // by reading it in place, since it then holds the post-propagation PDFs at t).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -115,8 +116,11 @@ struct Layout {
 Layout layout_of(const lbm_params *P) {
     Layout L;
     const size_t N = (size_t)P->nx * P->ny * P->nz;
-    // the reduction partials are sized for the largest tile count any launch
-    // shape can give (tile width 1)
+    // rows of the reduction partials: the tile count at tile width 1. Some
+    // sizes have more tiles at the width in use (133 x 154: 154 against 133 a
+    // plane); the diagnostics then take their tile rows in parts (reduce_diag).
+    // The phase-mass partials are 2 values a block, not NSUM: they fit at up
+    // to 8.5 times this count, and no size has more than twice it.
     TileCfg narrow{0, 0, 1};
     const size_t nblocks = num_tiles(P, narrow);
     L.pdf_bytes = align_up((size_t)num_pop(P) * plane_pitch(P));
@@ -483,10 +487,16 @@ void step_any(lbm_ctx *c, Mode m, int src, int dst, int mf_mode = 0) {
 
 Mode prop_mode(const lbm_ctx *c) { return c->P.courant == 1.0 ? SHIFT : LW; }
 
+// Tile rows ty0 .. ty0 + nty - 1 of the moments (all planes).
+struct Rows {
+    int ty0, nty;
+};
+
 template <class St, Mode M, bool W>
-void launch_moments(lbm_ctx *c, const FieldOut &o) {
+void launch_moments(lbm_ctx *c, const FieldOut &o, const Rows &b) {
     using R = typename St::R;
-    const DevParams<R> P = launch_params<R>(c);
+    DevParams<R> P = launch_params<R>(c);
+    if (b.nty < P.nty) P = with_box(P, b.ty0, b.nty, 0, P.nz, c->tc.band);
     if constexpr (St::Q == 19) {
         if (c->P.normal_fd) {
             launch_phi<St, M>(c, c->cur ^ 1, MassFix{0, nullptr, nullptr, 0});
@@ -500,51 +510,66 @@ void launch_moments(lbm_ctx *c, const FieldOut &o) {
 }
 
 template <class St, Mode M>
-void moments_w(lbm_ctx *c, const FieldOut &o) {
+void moments_w(lbm_ctx *c, const FieldOut &o, const Rows &b) {
     const bool walls = c->P.wall[0] || c->P.wall[1] || c->P.wall[2];
-    if (walls) launch_moments<St, M, true>(c, o);
-    else launch_moments<St, M, false>(c, o);
+    if (walls) launch_moments<St, M, true>(c, o, b);
+    else launch_moments<St, M, false>(c, o, b);
 }
 
 template <class St>
-void moments_dispatch(lbm_ctx *c, const FieldOut &o) {
-    if (c->prev_local) moments_w<St, LOCAL>(c, o);
-    else if (prop_mode(c) == SHIFT) moments_w<St, SHIFT>(c, o);
-    else moments_w<St, LW>(c, o);
+void moments_dispatch(lbm_ctx *c, const FieldOut &o, const Rows &b) {
+    if (c->prev_local) moments_w<St, LOCAL>(c, o, b);
+    else if (prop_mode(c) == SHIFT) moments_w<St, SHIFT>(c, o, b);
+    else moments_w<St, LW>(c, o, b);
 }
 
 struct MomentsOp {
     template <class St>
-    static void run(lbm_ctx *c, const FieldOut &o) {
-        moments_dispatch<St>(c, o);
+    static void run(lbm_ctx *c, const FieldOut &o, const Rows &b) {
+        moments_dispatch<St>(c, o, b);
     }
 };
 
-void moments_any(lbm_ctx *c, const FieldOut &o) { with_storage<MomentsOp>(c, c, o); }
+int tile_rows(const lbm_ctx *c) { return (c->P.ny + (BLOCK >> c->tc.tx_log2) - 1) / (BLOCK >> c->tc.tx_log2); }
 
+void moments_any(lbm_ctx *c, const FieldOut &o, const Rows &b) { with_storage<MomentsOp>(c, c, o, b); }
+void moments_any(lbm_ctx *c, const FieldOut &o) { moments_any(c, o, Rows{0, tile_rows(c)}); }
+
+// The state at the current time from fields: post-propagation populations
+// into dst and their collision into post, in one launch (the
+// finite-difference variant collides in its own two passes).
 template <class St>
-void launch_init(lbm_ctx *c, const double *phi0, const double *u0, const double *p0, int dst) {
+void launch_init(lbm_ctx *c, const double *phi0, const double *u0, const double *p0, int dst, int post) {
     using R = typename St::R;
     const DevParams<double> PD = make_params<double>(&c->P, c->tc);
     const DevParams<R> PR = make_params<R>(&c->P, c->tc);
     const bool walls = c->P.wall[0] || c->P.wall[1] || c->P.wall[2];
-    if (walls)
-        hipLaunchKernelGGL((init_kernel<St, true>), tile_grid(PR), dim3(BLOCK), 0, c->stream,
-                           phi0, u0, p0, PD, PR, buf_of<St>(c, dst), c->flag, c->partials);
-    else
-        hipLaunchKernelGGL((init_kernel<St, false>), tile_grid(PR), dim3(BLOCK), 0, c->stream,
-                           phi0, u0, p0, PD, PR, buf_of<St>(c, dst), c->flag, c->partials);
+    auto launch = [&](auto W, auto S) {
+        hipLaunchKernelGGL((init_kernel<St, decltype(W)::value, decltype(S)::value>), tile_grid(PR),
+                           dim3(BLOCK), 0, c->stream, phi0, u0, p0, PD, PR, buf_of<St>(c, dst),
+                           c->flag, c->partials, buf_of<St>(c, post), make_wet<R>(&c->P));
+    };
+    if constexpr (St::Q == 19) {
+        if (c->P.normal_fd) {
+            if (walls) launch(std::true_type{}, std::false_type{});
+            else launch(std::false_type{}, std::false_type{});
+            launch_step_fd<St, LOCAL>(c, dst, post, MassFix{0, c->partials, c->mf + 1, 0});
+            return;
+        }
+    }
+    if (walls) launch(std::true_type{}, std::true_type{});
+    else launch(std::false_type{}, std::true_type{});
 }
 
 struct InitOp {
     template <class St>
-    static void run(lbm_ctx *c, const double *phi0, const double *u0, const double *p0, int dst) {
-        launch_init<St>(c, phi0, u0, p0, dst);
+    static void run(lbm_ctx *c, const double *phi0, const double *u0, const double *p0, int dst, int post) {
+        launch_init<St>(c, phi0, u0, p0, dst, post);
     }
 };
 
-void init_any(lbm_ctx *c, const double *phi0, const double *u0, const double *p0, int dst) {
-    with_storage<InitOp>(c, c, phi0, u0, p0, dst);
+void init_any(lbm_ctx *c, const double *phi0, const double *u0, const double *p0, int dst, int post) {
+    with_storage<InitOp>(c, c, phi0, u0, p0, dst, post);
 }
 
 template <class St>
@@ -566,14 +591,42 @@ void load_any(lbm_ctx *c, const double *f, const double *g, int dst) {
     with_storage<LoadOp>(c, c, f, g, dst);
 }
 
+// Folds the first `rows` partial rows, in order, into c->result (or into row 0).
+void fold_partials(lbm_ctx *c, int rows, bool last) {
+    int stride = 1;
+    if (rows > 4 * RRUN) {  // runs of rows by many blocks first
+        const int nb = (rows + RRUN - 1) / RRUN;
+        hipLaunchKernelGGL(reduce_partials_kernel, dim3(nb), dim3(256), 0, c->stream, c->partials,
+                           rows, 1, RRUN, (double *)nullptr);
+        rows = nb;
+        stride = RRUN;
+    }
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3(1), dim3(256), 0, c->stream, c->partials, rows,
+                       stride, rows, last ? c->result : (double *)nullptr);
+}
+
 // Runs the diagnostics reduction of the state at t into c->result (device).
+// Where the tiles outnumber the rows of the partials, their rows go in parts:
+// row 0 keeps the parts before, the others take the next tile rows.
 int reduce_diag(lbm_ctx *c, const double *phi_ref) {
     FieldOut o{};
     o.phi_ref = phi_ref;
     o.partials = c->partials;
-    moments_any(c, o);
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3(1), dim3(RBLOCK), 0, c->stream,
-                       (const double *)c->partials, c->nblocks, c->result);
+    const int nty = tile_rows(c), per = c->nblocks / nty;  // blocks of a tile row
+    const int cap = (int)(c->L.partial_bytes / (NSUM * sizeof(double)));
+    if (c->nblocks <= cap) {
+        moments_any(c, o);
+        fold_partials(c, c->nblocks, true);
+        return check_launch(c);
+    }
+    for (int ty = 0; ty < nty;) {
+        o.row0 = ty > 0 ? 1 : 0;
+        const int n = std::min(nty - ty, (cap - 1) / per);
+        if (n < 1) return LBM_EDEVICE;
+        moments_any(c, o, Rows{ty, n});
+        ty += n;
+        fold_partials(c, o.row0 + n * per, ty == nty);
+    }
     return check_launch(c);
 }
 
@@ -582,10 +635,9 @@ int reduce_diag(lbm_ctx *c, const double *phi_ref) {
 // collision into buffer 0; checks the inputs (synchronises the stream).
 int build_state(lbm_ctx *c, const double *d_phi, const double *d_u, const double *d_p) {
     hipLaunchKernelGGL(clear_int_kernel, dim3(1), dim3(1), 0, c->stream, c->flag);
-    init_any(c, d_phi, d_u, d_p, 1);
+    init_any(c, d_phi, d_u, d_p, 1, 0);
     hipLaunchKernelGGL(massfix_kernel, dim3(1), dim3(RBLOCK), 0, c->stream,
                        (const double *)c->partials, c->nblocks, c->mf, c->mf + 1, 1);
-    step_any(c, LOCAL, 1, 0);
     c->cur = 0;
     c->prev_local = true;
     c->mf_pending = false;

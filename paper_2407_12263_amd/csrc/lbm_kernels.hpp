@@ -825,11 +825,12 @@ __device__ __forceinline__ Dst<St> make_dst(const Buf<St> &b, const DevParams<ty
     return d;
 }
 
-template <class St>
+// READBACK: fs and gs become the values that a read of the stored node gives.
+template <class St, bool READBACK = false>
 __device__ __forceinline__ void store(const Dst<St> &dst, uint32_t n,
                                       const DevParams<typename St::R> &P,
-                                      const typename St::R (&fs)[St::Q],
-                                      const typename St::R (&gs)[St::Q]) {
+                                      std::conditional_t<READBACK, typename St::R, const typename St::R> (&fs)[St::Q],
+                                      std::conditional_t<READBACK, typename St::R, const typename St::R> (&gs)[St::Q]) {
     using R = typename St::R;
     using T = typename St::T;
     using L = LatQ<St::Q>;
@@ -856,10 +857,21 @@ __device__ __forceinline__ void store(const Dst<St> &dst, uint32_t n,
             const uint32_t w = uint32_t(__builtin_bit_cast(uint16_t, hf)) |
                                (uint32_t(__builtin_bit_cast(uint16_t, hg)) << 16);
             bstore<uint32_t>(w, dst.f, voff, (uint32_t)i * dst.plane);
+            if constexpr (READBACK) {
+                fs[i] = fma(P.iscale_f, R(decode<St>(hf)), t * P.rho0);
+                gs[i] = decode<St>(hg);
+            }
         });
         // sum_i (t_i phi_s + 2^-k h_i) = sum_i g*_i: the storage rounding of g
         // is absorbed by phi_s, so the node keeps its phase mass
-        bstore<float>(phi_a + resid, dst.phis, n * 4u, 0u);
+        const float phis = phi_a + resid;
+        bstore<float>(phis, dst.phis, n * 4u, 0u);
+        if constexpr (READBACK) {
+            unroll<0, NQ>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                gs[i] = fma(P.iscale_g, gs[i], wgt<R, NQ>(L::cls(i)) * phis);
+            });
+        }
     }
 }
 
@@ -869,14 +881,27 @@ __device__ __forceinline__ double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+// The same over a wavefront with data-parallel moves between registers; the
+// result is lane 63's. A shuffle of a double is two LDS permutes: the 17
+// values of the diagnostics took 204 a wavefront, which bounded the kernel
+// (128^3 FP32: 114 us, 83 with these; its read of the state takes 63).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double keep, double v) {
+    const uint64_t k = __builtin_bit_cast(uint64_t, keep), x = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)k, (int)(uint32_t)x, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(k >> 32), (int)(x >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-__device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+// OP 0: sum (lanes without a source add 0), 1: max, 2: min (they keep theirs)
+template <int OP>
+__device__ __forceinline__ double wave_last(double v) {
+    auto step = [&](double o) { v = OP == 0 ? v + o : (OP == 1 ? fmax(v, o) : fmin(v, o)); };
+    step(dpp<0x111, 0xf>(OP == 0 ? 0.0 : v, v));  // row_shr:1, 2, 4, 8
+    step(dpp<0x112, 0xf>(OP == 0 ? 0.0 : v, v));
+    step(dpp<0x114, 0xf>(OP == 0 ? 0.0 : v, v));
+    step(dpp<0x118, 0xf>(OP == 0 ? 0.0 : v, v));
+    step(dpp<0x142, 0xa>(OP == 0 ? 0.0 : v, v));  // row_bcast:15 into rows 1 and 3
+    step(dpp<0x143, 0xc>(OP == 0 ? 0.0 : v, v));  // row_bcast:31 into rows 2 and 3
     return v;
 }
 
@@ -1061,9 +1086,13 @@ __global__ void __launch_bounds__(RBLOCK) massfix_kernel(const double *partials,
     __shared__ double red[RBLOCK / 64][2];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double a = 0.0, b = 0.0;
+    // eight rows of a thread in flight, added in order (65,536 rows, one
+    // block: bound by the loads' latency, 27 -> 9 us)
+#pragma unroll 8
     for (int k = threadIdx.x; k < nblocks; k += RBLOCK) {
-        a += partials[2 * (size_t)k];
-        b += partials[2 * (size_t)k + 1];
+        const double2 v = ((const double2 *)partials)[k];
+        a += v.x;
+        b += v.y;
     }
     a = wave_sum(a);
     b = wave_sum(b);
@@ -1097,7 +1126,8 @@ struct FieldOut {
     int dtype;                 // 0 double, 1 float
     double *pdf_f, *pdf_g;     // FP64 post-propagation PDFs (or NULL)
     const double *phi_ref;     // for the L2 entries (or NULL)
-    double *partials;          // NSUM per block (or NULL)
+    double *partials;          // NSUM per block (or NULL), from row row0 on
+    int row0;
 };
 
 // Moments of the state at t (propagation mode M from the previous buffer):
@@ -1168,15 +1198,14 @@ __global__ void __launch_bounds__(BLOCK) moments_kernel(CBuf<St> src, DevParams<
         }
     }
     if (out.partials) {
-        // deterministic block reduction: wave shuffles, then waves in order
+        // deterministic block reduction: wavefronts, then waves in order
         __shared__ double red[BLOCK / 64][NSUM];
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-        for (int k = 0; k < NSUM; ++k) {
-            double v = acc[k];
-            v = (k == 6 || k == 8) ? wave_max(v) : (k == 7 ? wave_min(v) : wave_sum(v));
-            if (lane == 0) red[wv][k] = v;
-        }
+        unroll<0, NSUM>([&](auto K) {
+            constexpr int k = decltype(K)::value;
+            const double v = wave_last<(k == 6 || k == 8) ? 1 : (k == 7 ? 2 : 0)>(acc[k]);
+            if (lane == 63) red[wv][k] = v;
+        });
         __syncthreads();
         if (threadIdx.x < NSUM) {
             const int k = threadIdx.x;
@@ -1185,43 +1214,44 @@ __global__ void __launch_bounds__(BLOCK) moments_kernel(CBuf<St> src, DevParams<
                 const double x = red[w][k];
                 v = (k == 6 || k == 8) ? fmax(v, x) : (k == 7 ? fmin(v, x) : v + x);
             }
-            out.partials[(size_t)linear_block() * NSUM + k] = v;
+            out.partials[((size_t)out.row0 + linear_block()) * NSUM + k] = v;
         }
     }
 }
 
-// Final reduction of the per-block partials (one block of RBLOCK threads:
-// each thread folds a strided run of blocks for all NSUM entries, then the
-// waves are combined in order, so the result does not depend on timing).
-__global__ void __launch_bounds__(RBLOCK) reduce_partials_kernel(const double *partials, int nblocks,
-                                                                 double *result) {
-    __shared__ double red[RBLOCK / 64][NSUM];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    double acc[NSUM];
-#pragma unroll
-    for (int k = 0; k < NSUM; ++k) acc[k] = (k == 6 || k == 8) ? -1e300 : (k == 7 ? 1e300 : 0.0);
-    for (int b = threadIdx.x; b < nblocks; b += RBLOCK) {
-#pragma unroll
-        for (int k = 0; k < NSUM; ++k) {
-            const double x = partials[(size_t)b * NSUM + k];
-            acc[k] = (k == 6 || k == 8) ? fmax(acc[k], x) : (k == 7 ? fmin(acc[k], x) : acc[k] + x);
+// Reduction of the diagnostics' partial rows: block b folds rows b run ..
+// b run + run - 1 (of nrows), `stride` rows apart in memory, into out, or into
+// its own first row if out is NULL. Thread (group, column) takes every 15th
+// row of one column, so a block's reads are contiguous; the groups are
+// combined in order, so the result does not depend on timing. One block over
+// 8192 rows was a chain of 136-byte strided reads (41 us; two passes of this
+// kernel, 64 blocks and then one, 8 us).
+constexpr int RGRP = 15;
+constexpr int RRUN = 128;
+
+__global__ void __launch_bounds__(256) reduce_partials_kernel(double *partials, int nrows, int stride,
+                                                              int run, double *out) {
+    __shared__ double red[RGRP][NSUM];
+    const int k = threadIdx.x % NSUM, g = threadIdx.x / NSUM;
+    const bool mx = (k == 6 || k == 8), mn = (k == 7);
+    const int r0 = (int)blockIdx.x * run, r1 = r0 + run < nrows ? r0 + run : nrows;
+    double v = mx ? -1e300 : (mn ? 1e300 : 0.0);
+    if (g < RGRP) {
+#pragma unroll 4
+        for (int r = r0 + g; r < r1; r += RGRP) {
+            const double x = partials[(size_t)r * stride * NSUM + k];
+            v = mx ? fmax(v, x) : (mn ? fmin(v, x) : v + x);
         }
-    }
-#pragma unroll
-    for (int k = 0; k < NSUM; ++k) {
-        const double v = (k == 6 || k == 8) ? wave_max(acc[k]) : (k == 7 ? wave_min(acc[k]) : wave_sum(acc[k]));
-        if (lane == 0) red[wv][k] = v;
+        red[g][k] = v;
     }
     __syncthreads();
     if (threadIdx.x < NSUM) {
-        const int k = threadIdx.x;
-        const bool mx = (k == 6 || k == 8), mn = (k == 7);
-        double v = red[0][k];
-        for (int w = 1; w < RBLOCK / 64; ++w) {
+        v = red[0][k];
+        for (int w = 1; w < RGRP; ++w) {
             const double x = red[w][k];
             v = mx ? fmax(v, x) : (mn ? fmin(v, x) : v + x);
         }
-        result[k] = v;
+        (out ? out : partials + (size_t)r0 * stride * NSUM)[k] = v;
     }
 }
 
@@ -1234,31 +1264,30 @@ __global__ void __launch_bounds__(RBLOCK) reduce_partials_kernel(const double *p
 template <class St, bool WALLS>
 __device__ __forceinline__ void init_node(const double *phi0, const double *u0, const double *p0,
                                           const DevParams<double> &P,
-                                          const DevParams<typename St::R> &PR, const Buf<St> &dst,
-                                          int *bad, const Site<St::Q> &s) {
+                                          int *bad, const Site<St::Q> &s,
+                                          typename St::R (&fo)[St::Q], typename St::R (&go)[St::Q]) {
     using R = typename St::R;
     using L = LatQ<St::Q>;
     constexpr int NQ = St::Q;
     const size_t N = (size_t)P.N, n = s.n;
     const double ph0 = phi0[n];
+    // opposite directions give the same difference: one term per pair
     double g[3] = {0.0, 0.0, 0.0};
-    unroll<1, NQ>([&](auto I) {
-        constexpr int i = decltype(I)::value;
+    unroll<0, (NQ - 1) / 2>([&](auto K) {
+        constexpr int i = 2 * decltype(K)::value + 1;
         constexpr int ex = L::EX[i], ey = L::EY[i], ez = L::EZ[i];
-        constexpr double t = wgt<double, NQ>(L::cls(i));
+        constexpr double t3 = 3.0 * wgt<double, NQ>(L::cls(i));
         double vp = phi0[s.nb[i]];
         double vm = phi0[s.nb[L::OPP[i]]];
         if constexpr (WALLS) {
             if (beyond_wall<i, -1>(s)) vp = ph0;
             if (beyond_wall<i, 1>(s)) vm = ph0;
         }
-        const double d = 0.5 * (vp - vm) * t;
-        g[0] += ex * d;
-        g[1] += ey * d;
-        g[2] += ez * d;
+        const double d = (vp - vm) * t3;
+        if constexpr (ex != 0) g[0] += ex * d;
+        if constexpr (ey != 0) g[1] += ey * d;
+        if constexpr (ez != 0) g[2] += ez * d;
     });
-#pragma unroll
-    for (int a = 0; a < 3; ++a) g[a] *= 3.0;
 
     Macro<double> m;
     m.phi = ph0;
@@ -1270,9 +1299,10 @@ __device__ __forceinline__ void init_node(const double *phi0, const double *u0, 
     const double gn = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
     const double s4 = P.four_over_delta * ph0 * (1.0 - ph0);
     const double wg = floor_weight(P, gn);
+    const double rg = wg > 0.0 ? wg / gn : 0.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        m.n[a] = wg > 0.0 ? wg * g[a] / gn : 0.0;
+        m.n[a] = rg * g[a];
         m.S[a] = s4 * m.n[a];
         m.gradrho[a] = P.drho * g[a];
     }
@@ -1282,43 +1312,63 @@ __device__ __forceinline__ void init_node(const double *phi0, const double *u0, 
         atomicOr(bad, 1);
 
     const NodeCoef<double> q = node_coef(P, m);
-    R fo[NQ], go[NQ];
-    unroll<0, NQ>([&](auto I) {
+    // f = t (A - B/2), g = t (Gq - (tau_phi + 1/2) c e^.grad(phi)); the even and
+    // odd parts of a pair evaluated once, as in collide()
+    const double rog = (1.0 / P.omega_g) * P.c;
+    auto put = [&](auto I, double A, double B, double Gq, double eg0) {
+        // the products are the stored values: never fused into the sums that
+        // a collision in the same kernel takes of them
+#pragma clang fp contract(off)
         constexpr int i = decltype(I)::value;
-        constexpr int cl = L::cls(i);
-        constexpr double t = wgt<double, NQ>(cl);
-        double poly, A, B, Gq, eg0;
-        if constexpr (i == 0) {
-            poly = -q.a3;
-            A = fma(m.rho, poly, q.A0[0]);
-            B = -poly * q.ug - q.uG * P.inv_cs2;
-            Gq = fma(m.phi, poly, m.phi);
-            eg0 = 0.0;
-        } else {
-            const double eu = edot<i, NQ>(q.cu);
-            const double en = edot<i, NQ>(m.n);
-            const double eg = edot<i, NQ>(q.cgr);
-            const double eG = edot<i, NQ>(q.crG);
-            const double es = edot<i, NQ>(q.tS);
-            poly = fma(eu, fma(eu, P.half_inv_cs4, P.inv_cs2), -q.a3);
-            A = fma(m.rho, poly, fma(q.kpsi * en, en, q.A0[cl]));
-            B = fma(poly, eg - q.ug, fma(eG - q.uG, P.inv_cs2, 2.0 * P.half_inv_cs4 * eu * eG));
-            Gq = fma(m.phi, poly, m.phi + es);
-            eg0 = P.c * edot<i, NQ>(g);
-        }
-        fo[i] = R(t * (A - 0.5 * B));
-        go[i] = R(t * (Gq - (1.0 / P.omega_g) * eg0));
+        constexpr double t = wgt<double, NQ>(L::cls(i));
+        fo[i] = R(t * fma(-0.5, B, A));
+        go[i] = R(t * fma(-rog, eg0, Gq));
+    };
+    {
+        const double poly = -q.a3;
+        put(std::integral_constant<int, 0>{}, fma(m.rho, poly, q.A0[0]),
+            -poly * q.ug - q.uG * P.inv_cs2, fma(m.phi, poly, m.phi), 0.0);
+    }
+    const double uGs = q.uG * P.inv_cs2;
+    unroll<0, (NQ - 1) / 2>([&](auto K) {
+        constexpr int i = 2 * decltype(K)::value + 1;
+        const double eu = edot<i, NQ>(q.cu), en = edot<i, NQ>(m.n), eg = edot<i, NQ>(q.cgr);
+        const double eG = edot<i, NQ>(q.crG), es = edot<i, NQ>(q.tS), eg0 = edot<i, NQ>(g);
+        const double E = fma(eu * eu, P.half_inv_cs4, -q.a3), O = eu * P.inv_cs2;
+        const double pp = E + O, pm = E - O;
+        const double kn = fma(q.kpsi * en, en, q.A0[L::cls(i)]);
+        const double t1 = fma(2.0 * P.half_inv_cs4 * eu, eG, -uGs), eGs = eG * P.inv_cs2;
+        put(std::integral_constant<int, i>{}, fma(m.rho, pp, kn), fma(pp, eg - q.ug, t1 + eGs),
+            fma(m.phi, pp, m.phi + es), eg0);
+        put(std::integral_constant<int, i + 1>{}, fma(m.rho, pm, kn), fma(pm, -eg - q.ug, t1 - eGs),
+            fma(m.phi, pm, m.phi - es), -eg0);
     });
-    store<St>(make_dst(dst, PR), s.n, PR, fo, go);
 }
 
-template <class St, bool WALLS>
+// STEP: the first collision too, from the stored (rounded) populations, into
+// post: what a LOCAL step of the stored state gives, without reading it back
+// (256^3 FP16: 588 + 504 us as two passes, 810 in one; bound by the FP64
+// arithmetic of the equilibria).
+template <class St, bool WALLS, bool STEP>
 __global__ void __launch_bounds__(BLOCK) init_kernel(const double *phi0, const double *u0,
                                                      const double *p0, DevParams<double> P,
                                                      DevParams<typename St::R> PR, Buf<St> dst,
-                                                     int *bad, double *partials) {
+                                                     int *bad, double *partials, Buf<St> post,
+                                                     Wet<typename St::R> wp) {
+    using R = typename St::R;
     const Site<St::Q> s = make_site<St::Q>(P);
-    if (s.valid) init_node<St, WALLS>(phi0, u0, p0, P, PR, dst, bad, s);
+    if (s.valid) {
+        R f[St::Q], g[St::Q];
+        init_node<St, WALLS>(phi0, u0, p0, P, bad, s, f, g);
+        store<St, STEP>(make_dst(dst, PR), s.n, PR, f, g);
+        if constexpr (STEP) {
+            const R none[3] = {R(0), R(0), R(0)};
+            const Macro<R> m = site_moments<WALLS, false>(PR, s, f, g, none, wp);
+            const NodeCoef<R> q = node_coef(PR, m);
+            collide(PR, m, q, f, g);
+            store<St>(make_dst(post, PR), s.n, PR, f, g);
+        }
+    }
     block_sum2(s.valid ? phi0[s.n] : 0.0, 0.0, partials + 2 * (size_t)linear_block());
 }
 
