@@ -882,9 +882,9 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 // The same over a wavefront with data-parallel moves between registers; the
-// result is lane 63's. A shuffle of a double is two LDS permutes: the 17
-// values of the diagnostics took 204 a wavefront, which bounded the kernel
-// (128^3 FP32: 114 us, 83 with these; its read of the state takes 63).
+// result is lane 63's. A shuffle of a double is two LDS permutes, 204 a
+// wavefront for the 17 values of the diagnostics (128^3 FP32: 114 -> 109 us;
+// the same pass without them, lbm_fields, takes 91).
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp(double keep, double v) {
     const uint64_t k = __builtin_bit_cast(uint64_t, keep), x = __builtin_bit_cast(uint64_t, v);
@@ -1087,7 +1087,7 @@ __global__ void __launch_bounds__(RBLOCK) massfix_kernel(const double *partials,
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double a = 0.0, b = 0.0;
     // eight rows of a thread in flight, added in order (65,536 rows, one
-    // block: bound by the loads' latency, 27 -> 9 us)
+    // block: bound by the loads' latency, 27 -> 17 us)
 #pragma unroll 8
     for (int k = threadIdx.x; k < nblocks; k += RBLOCK) {
         const double2 v = ((const double2 *)partials)[k];
@@ -1224,8 +1224,8 @@ __global__ void __launch_bounds__(BLOCK) moments_kernel(CBuf<St> src, DevParams<
 // its own first row if out is NULL. Thread (group, column) takes every 15th
 // row of one column, so a block's reads are contiguous; the groups are
 // combined in order, so the result does not depend on timing. One block over
-// 8192 rows was a chain of 136-byte strided reads (41 us; two passes of this
-// kernel, 64 blocks and then one, 8 us).
+// 8192 rows was a chain of 136-byte strided reads (43 us; two passes of this
+// kernel, 64 blocks and then one, 15 us).
 constexpr int RGRP = 15;
 constexpr int RRUN = 128;
 
@@ -1347,8 +1347,8 @@ __device__ __forceinline__ void init_node(const double *phi0, const double *u0, 
 
 // STEP: the first collision too, from the stored (rounded) populations, into
 // post: what a LOCAL step of the stored state gives, without reading it back
-// (256^3 FP16: 588 + 504 us as two passes, 810 in one; bound by the FP64
-// arithmetic of the equilibria).
+// (256^3 FP16: 588 + 504 us as two passes, 930 in one; 3.4 GB and 1570 vector
+// instructions a wavefront, a third of them FP64, take 670 us each).
 template <class St, bool WALLS, bool STEP>
 __global__ void __launch_bounds__(BLOCK) init_kernel(const double *phi0, const double *u0,
                                                      const double *p0, DevParams<double> P,

@@ -1947,7 +1947,7 @@ __global__ void coarsen_kernel(const float *__restrict__ phi, const float *__res
 // averages one cell, the block's 256 cells pass through LDS, and four lanes
 // write one cell's row (a row written by one thread puts a wavefront's stores
 // 64 bytes apart). Rows of phi, u and p 8-byte aligned, cf 16, cb 8. Bound by
-// HBM: 256^3 197 -> 105 us (470 MB).
+// HBM: 256^3 197 -> 85 us (470 MB).
 __global__ void __launch_bounds__(256) coarsen_rows_kernel(const float *__restrict__ phi,
                                                            const float *__restrict__ u,
                                                            const float *__restrict__ p, int nx, int ny,
@@ -2172,7 +2172,7 @@ __global__ void features_kernel(float *__restrict__ s, int nx, int ny, int nz) {
 // into LDS, their psi included; per node that took sixteen logarithms and 40
 // reads of 64-byte rows. The sums of phi and of max(phi (1 - phi), 0) before
 // and after the update, which the mass restoration needs, come from the same
-// pass: four FP64 values per block. Bound by HBM: 256^3 1080 -> 350 us with
+// pass: four FP64 values per block. Bound by HBM: 256^3 1103 -> 352 us with
 // the two separate passes of sums (1.6 GB).
 constexpr int kPuCells = 34 * 4 * 6;
 
