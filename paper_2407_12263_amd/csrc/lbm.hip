@@ -32,44 +32,6 @@ constexpr size_t kAlign = 256;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// Launch shape: one 256-thread block per tile of 2^tx_log2 x (256 >> tx_log2)
-// nodes of one z-plane. The tile spans whole x-rows up to 128 nodes (a
-// wavefront reads 64 contiguous nodes of a row, and a row's periodic wrap
-// stays inside the tile): on the 128 x 512 x 128 Rayleigh-Taylor lattice this
-// measured best among 32/64/128-wide tiles. LBM_TILE_X_LOG2, LBM_TILE_ORDER and
-// LBM_TILE_BAND override the choice (tuning only; results do not depend on it).
-struct TileCfg {
-    int tx_log2, order, band;
-};
-
-int env_int(const char *name, int dflt) {
-    const char *v = std::getenv(name);
-    return v && *v ? std::atoi(v) : dflt;
-}
-
-TileCfg tile_cfg(const lbm_params *P) {
-    TileCfg t;
-    int l = 0;
-    while ((1 << l) < P->nx && l < 7) ++l;
-    t.tx_log2 = env_int("LBM_TILE_X_LOG2", l);
-    if (t.tx_log2 < 0 || t.tx_log2 > 8) t.tx_log2 = l;
-    // default: XCD runs of the z-banded order with bands of 32 tile rows (the
-    // y/z taps of a band stay in L2; on RT: FP32 14.6 against 13.9 GLUPS and
-    // FP16 25.6 against 24.3 in the plain order)
-    const int dflt_order = 2;
-    t.order = env_int("LBM_TILE_ORDER", dflt_order);
-    if (t.order < 0 || t.order > 2) t.order = dflt_order;
-    t.band = env_int("LBM_TILE_BAND", 32);
-    if (t.band < 1) t.band = 32;
-    return t;
-}
-
-size_t num_tiles(const lbm_params *P, const TileCfg &t) {
-    const size_t tw = (size_t)1 << t.tx_log2, th = (size_t)BLOCK >> t.tx_log2;
-    const size_t ntx = (P->nx + tw - 1) / tw, nty = (P->ny + th - 1) / th;
-    return ntx * nty * (size_t)P->nz;
-}
-
 size_t elem_bytes(int precision) {
     switch (precision) {
         case LBM_FP64: return 8;
@@ -84,6 +46,60 @@ bool is16(int precision) {
 
 // Populations per field: 19 (D3Q19; lattice = 0 means the same) or 27.
 int num_pop(const lbm_params *P) { return P->lattice == 27 ? 27 : 19; }
+
+// Launch shape: one block per tile of w x th nodes of one z-plane.
+// LBM_TILE_X_LOG2, LBM_TILE_ORDER and LBM_TILE_BAND override the choice
+// (tuning only; results do not depend on it).
+struct TileCfg {
+    int w, th, threads, order, band;
+};
+
+int env_int(const char *name, int dflt) {
+    const char *v = std::getenv(name);
+    return v && *v ? std::atoi(v) : dflt;
+}
+
+// Tiles of one z-plane.
+size_t plane_tiles(const lbm_params *P, int w, int th) {
+    return (size_t)((P->nx + w - 1) / w) * (size_t)((P->ny + th - 1) / th);
+}
+
+// base: a power of two that spans whole x-rows up to 128 nodes (a row's
+// periodic wrap stays inside the tile; 128 measured best among 32, 64 and 128
+// on the 128 x 512 x 128 Rayleigh-Taylor lattice). Otherwise the row itself
+// where that takes fewer tiles or spares a row's second, partial one (16
+// steps: 75 x 61 x 43 FP32 374 -> 311 us, 133 x 110 x 90 FP16 1484 -> 1187,
+// 150^3 FP64 12670 -> 10401; even shares of a row, 50 of 100, are 20% slower
+// than the row for their unaligned segments). Rows beyond a block's threads
+// take 64 where that leaves fewer lanes idle and the state is small (300 x 200
+// FP64 248 -> 161 us, 300 x 90 x 30 FP16 887 -> 749; but D3Q27 FP32 1962 ->
+// 2036).
+TileCfg tile_cfg(const lbm_params *P, int threads, bool base) {
+    TileCfg t;
+    t.threads = threads;
+    const int nx = P->nx, lx = env_int("LBM_TILE_X_LOG2", -1);
+    int l = 0;
+    while ((1 << l) < nx && l < (threads == 64 ? 6 : 7)) ++l;
+    t.w = 1 << l;
+    const size_t idle = ((size_t)(nx + 127) / 128 * 128 - (nx + 63) / 64 * 64) / 64;
+    const size_t bytes = (size_t)P->nx * P->ny * P->nz * elem_bytes(P->precision) * 2 * num_pop(P);
+    if (lx >= 0 && lx <= 8 && threads == BLOCK) t.w = 1 << lx;
+    else if (base) ;
+    else if (nx <= threads && (plane_tiles(P, nx, threads / nx) < plane_tiles(P, t.w, threads / t.w) ||
+                               (nx > t.w && nx < BLOCK)))
+        t.w = nx;
+    else if (nx > threads && t.w == 128 && idle && bytes < (size_t)100 << 20) t.w = 64;
+    t.th = threads / t.w;
+    // default: XCD runs of the z-banded order with bands of 32 tile rows (the
+    // y/z taps of a band stay in L2; on RT: FP32 14.6 against 13.9 GLUPS and
+    // FP16 25.6 against 24.3 in the plain order)
+    const int dflt_order = 2;
+    t.order = env_int("LBM_TILE_ORDER", dflt_order);
+    if (t.order < 0 || t.order > 2) t.order = dflt_order;
+    t.band = env_int("LBM_TILE_BAND", 32);
+    if (t.band < 1) t.band = 32;
+    return t;
+}
 
 // Bytes from one population plane to the next: N elements (16-bit storage:
 // the 32-bit f/g words) rounded up to 256 B, plus a pad of 64 KiB + 256 B.
@@ -121,8 +137,7 @@ Layout layout_of(const lbm_params *P) {
     // plane); the diagnostics then take their tile rows in parts (reduce_diag).
     // The phase-mass partials are 2 values a block, not NSUM: they fit at up
     // to 8.5 times this count, and no size has more than twice it.
-    TileCfg narrow{0, 0, 1};
-    const size_t nblocks = num_tiles(P, narrow);
+    const size_t nblocks = plane_tiles(P, 1, 256) * (size_t)P->nz;
     L.pdf_bytes = align_up((size_t)num_pop(P) * plane_pitch(P));
     L.g_bytes = is16(P->precision) ? 0 : L.pdf_bytes;
     L.phis_bytes = is16(P->precision) ? align_up(N * sizeof(float)) : 0;
@@ -189,20 +204,85 @@ FastDiv make_fastdiv(uint32_t d) {
     return f;
 }
 
-// Divisors of the tile decomposition of a launch box.
-template <class R>
-void set_divisors(DevParams<R> &d) {
-    d.nfull = d.bnty / d.band;
-    const int rem = d.bnty - d.nfull * d.band;
-    d.d_ntx = make_fastdiv((uint32_t)d.ntx);
-    d.d_nty = make_fastdiv((uint32_t)d.bnty);
-    d.d_band = make_fastdiv((uint32_t)d.band);
-    d.d_perband = make_fastdiv((uint32_t)(d.band * d.bnz));
-    d.d_rem = make_fastdiv((uint32_t)(rem > 0 ? rem : 1));
+// Rows y0 .. y0 + rows - 1 (and the same `ystep` further where two), planes
+// z0 + k zstep (k < nz), in tiles of shape tc.
+Box make_box(const lbm_params *P, const TileCfg &tc, int y0, int rows, int ystep, int z0, int nz, int zstep) {
+    Box b;
+    b.tw = tc.w;
+    b.th = tc.th;
+    b.tw_log2 = -1;
+    for (int l = 0; l <= 8; ++l)
+        if (tc.w == 1 << l) b.tw_log2 = l;
+    b.ntx = (P->nx + tc.w - 1) / tc.w;
+    b.nsub = (rows + tc.th - 1) / tc.th;
+    b.nty = b.nsub * (ystep > 0 ? 2 : 1);
+    b.nz = nz;
+    b.ntiles = b.ntx * b.nty * nz;
+    b.y0 = y0;
+    b.ystep = ystep;
+    b.rows = rows;
+    b.z0 = z0;
+    b.zstep = zstep;
+    b.order = tc.order;
+    b.band = tc.band < b.nty ? tc.band : b.nty;
+    b.nfull = b.nty / b.band;
+    b.xq = b.ntiles / 8;
+    b.xr = b.ntiles % 8;
+    const int rem = b.nty - b.nfull * b.band;
+    b.d_tw = make_fastdiv((uint32_t)tc.w);
+    b.d_ntx = make_fastdiv((uint32_t)b.ntx);
+    b.d_nty = make_fastdiv((uint32_t)b.nty);
+    b.d_band = make_fastdiv((uint32_t)b.band);
+    b.d_perband = make_fastdiv((uint32_t)(b.band * nz));
+    b.d_rem = make_fastdiv((uint32_t)(rem > 0 ? rem : 1));
+    return b;
+}
+
+Box full_box(const lbm_params *P, const TileCfg &tc) { return make_box(P, tc, 0, P->ny, 0, 0, P->nz, 1); }
+
+// How a step covers the lattice. Periodic lattices: the wall-free instance
+// everywhere. Walls in y and/or z: the wall-free instance on the interior, the
+// wall-aware one on the slabs of rows and planes that touch a wall. A y slab is
+// slab_rows rows from the bottom, and from the last multiple of them to the
+// top: a tile's height at a power-of-two width. Walls in x touch every row,
+// and slabs that meet leave no interior: the wall-aware instance everywhere.
+struct Cover {
+    int threads;
+    bool split, walls;
+    int n;               // boxes in use
+    Box b[3];            // the whole lattice; or interior and slabs
+    int blocks;
+};
+
+Cover make_cover(const lbm_params *P, const TileCfg &tc) {
+    Cover v;
+    v.threads = tc.threads;
+    const int *w = P->wall;
+    v.walls = w[0] || w[1] || w[2];
+    int l = 0;
+    while ((1 << l) < P->nx && l < 7) ++l;
+    const int lx = env_int("LBM_TILE_X_LOG2", -1);
+    if (lx >= 0 && lx <= 8) l = lx;
+    const int h = BLOCK >> l, top = (P->ny - 1) / h * h;  // slab rows, first row of the upper slab
+    const int ylo = w[1] ? h : 0, yhi = w[1] ? top : P->ny;
+    const int zlo = w[2] ? 1 : 0, zhi = w[2] ? P->nz - 1 : P->nz;
+    v.split = v.walls && !w[0] && yhi > ylo && zhi > zlo;
+    if (!v.split) {
+        v.n = 1;
+        v.b[0] = full_box(P, tc);
+    } else {
+        v.n = 1;
+        v.b[0] = make_box(P, tc, ylo, yhi - ylo, 0, zlo, zhi - zlo, 1);
+        if (w[1]) v.b[v.n++] = make_box(P, tc, 0, h, top, 0, P->nz, 1);
+        if (w[2]) v.b[v.n++] = make_box(P, tc, ylo, yhi - ylo, 0, 0, 2, P->nz - 1);
+    }
+    v.blocks = 0;
+    for (int k = 0; k < v.n; ++k) v.blocks += v.b[k].ntiles;
+    return v;
 }
 
 template <class R>
-DevParams<R> make_params(const lbm_params *P, const TileCfg &tc) {
+DevParams<R> make_params(const lbm_params *P) {
     DevParams<R> d;
     d.nx = P->nx;
     d.ny = P->ny;
@@ -210,21 +290,6 @@ DevParams<R> make_params(const lbm_params *P, const TileCfg &tc) {
     d.N = P->nx * P->ny * P->nz;
     d.plane_bytes = (uint32_t)plane_pitch(P);
     for (int a = 0; a < 3; ++a) d.wall[a] = P->wall[a];
-    d.tx_log2 = tc.tx_log2;
-    d.ntx = (P->nx + (1 << tc.tx_log2) - 1) >> tc.tx_log2;
-    d.nty = (P->ny + (BLOCK >> tc.tx_log2) - 1) / (BLOCK >> tc.tx_log2);
-    d.ntiles = d.ntx * d.nty * P->nz;
-    d.order = tc.order;
-    d.band = tc.band < d.nty ? tc.band : d.nty;
-    d.xq = d.ntiles / 8;
-    d.xr = d.ntiles % 8;
-    d.bty0 = 0;
-    d.bnty = d.nty;
-    d.btz0 = 0;
-    d.bnz = P->nz;
-    d.bty_step = 1;
-    d.btz_step = 1;
-    set_divisors(d);
     const double c = P->courant, cs2 = c * c / 3.0;
     const double eta1 = P->rho1 * cs2 * P->tau_rho1, eta2 = P->rho2 * cs2 * P->tau_rho2;
     d.c = R(c);
@@ -285,12 +350,18 @@ struct lbm_ctx {
     double *mf;         // M0, coef of the phase-mass bookkeeping
     void *phifd;        // phi field of the finite-difference variant (or NULL)
     bool mf_pending;    // the next step applies coef
-    TileCfg tc;
+    TileCfg base;       // shape of the launches that sum over the lattice
+    Cover cover;        // a step
+    Cover sums;         // a step that reports the phase mass, in shape base: its
+                        // blocks group the sum, so the correction does not
+                        // follow the step's shape
+    Box full, full_base;   // the whole lattice, in the step's shape and in base
+    DevParams<float> pf;   // launch parameters
+    DevParams<double> pd;
     int cur;            // buffer holding the post-collision state
     bool prev_local;    // the other buffer holds post-propagation PDFs at t
     int64_t t;
     int status;
-    int nblocks;
 };
 
 namespace {
@@ -318,115 +389,74 @@ int check_launch(lbm_ctx *c) {
     return LBM_OK;
 }
 
-// Launch grid of a tile box: (ntx, rows, planes) in the plain order, a 1-D
-// run of tiles for the XCD-aware orders.
-template <class R>
-dim3 tile_grid(const DevParams<R> &P) {
-    return P.order == 0 ? dim3((unsigned)P.ntx, (unsigned)P.bnty, (unsigned)P.bnz)
-                        : dim3((unsigned)P.ntiles);
-}
-
-// Restricts a launch to tile rows ty0 + k ystep (k < nty) and planes
-// tz0 + k zstep (k < nz).
-template <class R>
-DevParams<R> with_box(DevParams<R> d, int ty0, int nty, int tz0, int nz, int band, int ystep = 1,
-                      int zstep = 1) {
-    d.bty0 = ty0;
-    d.bnty = nty;
-    d.btz0 = tz0;
-    d.bnz = nz;
-    d.bty_step = ystep;
-    d.btz_step = zstep;
-    d.ntiles = d.ntx * nty * nz;
-    d.band = band < nty ? band : nty;
-    d.xq = d.ntiles / 8;
-    d.xr = d.ntiles % 8;
-    set_divisors(d);
-    return d;
-}
-
 template <class St, Mode M, bool W, bool FD>
-void launch_step(lbm_ctx *c, int src, int dst, const DevParams<typename St::R> &P, MassFix mf,
-                 int &block_off) {
+void launch_step(lbm_ctx *c, int src, int dst, const DevParams<typename St::R> &P, const Box &b,
+                 int threads, MassFix mf, int &block_off) {
     mf.block_off = block_off;
     if constexpr (St::DEV && !W && !FD && St::Q == 19)
-        hipLaunchKernelGGL((step_kernel_o5<St, M, W, FD>), tile_grid(P), dim3(BLOCK), 0,
-                           c->stream, cbuf_of<St>(c, src), buf_of<St>(c, dst), P, mf);
+        hipLaunchKernelGGL((step_kernel_o5<St, M, W, FD>), dim3((unsigned)b.ntiles), dim3(threads), 0,
+                           c->stream, cbuf_of<St>(c, src), buf_of<St>(c, dst), P, b, mf);
     else
-        hipLaunchKernelGGL((step_kernel<St, M, W, FD>), tile_grid(P), dim3(BLOCK), 0, c->stream,
-                           cbuf_of<St>(c, src), buf_of<St>(c, dst), P, mf,
+        hipLaunchKernelGGL((step_kernel<St, M, W, FD>), dim3((unsigned)b.ntiles), dim3(threads), 0,
+                           c->stream, cbuf_of<St>(c, src), buf_of<St>(c, dst), P, b, mf,
                            make_wet<typename St::R>(&c->P));
-    block_off += P.ntiles;
+    block_off += b.ntiles;
 }
 
 // Parameters of a launch, with the phi field of the finite-difference variant.
 template <class R>
-DevParams<R> launch_params(lbm_ctx *c) {
-    DevParams<R> P = make_params<R>(&c->P, c->tc);
-    P.phi_fd = (R *)c->phifd;
-    return P;
+const DevParams<R> &launch_params(lbm_ctx *c) {
+    if constexpr (sizeof(R) == 8) return c->pd;
+    else return c->pf;
 }
 
 // First pass of the finite-difference variant: phi of the state the next
 // launch reads from buffer src, split into interior and wall slabs as the
 // step is.
-template <class St, Mode M, bool W>
-void launch_phi_box(lbm_ctx *c, int src, const DevParams<typename St::R> &P, const MassFix &mf) {
-    hipLaunchKernelGGL((phi_kernel<St, M, W>), tile_grid(P), dim3(BLOCK), 0, c->stream,
-                       cbuf_of<St>(c, src), P, mf);
-}
-
 template <class St, Mode M>
 void launch_phi(lbm_ctx *c, int src, const MassFix &mf) {
-    using R = typename St::R;
-    const DevParams<R> P = launch_params<R>(c);
-    const int *w = c->P.wall;
-    if (!w[0] && !w[1] && !w[2]) {
-        launch_phi_box<St, M, false>(c, src, P, mf);
-        return;
+    const DevParams<typename St::R> &P = launch_params<typename St::R>(c);
+    const Cover &v = c->cover;
+    for (int k = 0; k < v.n; ++k) {
+        const dim3 grid((unsigned)v.b[k].ntiles), block(v.threads);
+        if (v.split ? k > 0 : v.walls)
+            hipLaunchKernelGGL((phi_kernel<St, M, true>), grid, block, 0, c->stream, cbuf_of<St>(c, src), P, v.b[k], mf);
+        else
+            hipLaunchKernelGGL((phi_kernel<St, M, false>), grid, block, 0, c->stream, cbuf_of<St>(c, src), P, v.b[k], mf);
     }
-    const int ylo = w[1] ? 1 : 0, yhi = w[1] ? P.nty - 1 : P.nty;
-    const int zlo = w[2] ? 1 : 0, zhi = w[2] ? P.nz - 1 : P.nz;
-    if (w[0] || yhi <= ylo || zhi <= zlo) {
-        launch_phi_box<St, M, true>(c, src, P, mf);
-        return;
-    }
-    const int band = c->tc.band;
-    launch_phi_box<St, M, false>(c, src, with_box(P, ylo, yhi - ylo, zlo, zhi - zlo, band), mf);
-    if (w[1]) launch_phi_box<St, M, true>(c, src, with_box(P, 0, 2, 0, P.nz, band, P.nty - 1), mf);
-    if (w[2])
-        launch_phi_box<St, M, true>(c, src, with_box(P, ylo, yhi - ylo, 0, 2, band, 1, P.nz - 1), mf);
 }
 
-// Periodic lattices: one wall-free launch. Walls in y and/or z: the interior
-// box of tiles runs the wall-free instance, the wall slabs (first and last
-// tile row; first and last plane) one wall-aware launch each. Walls in x
-// touch every tile row: one wall-aware launch.
 template <class St, Mode M, bool FD>
 void launch_step_w(lbm_ctx *c, int src, int dst, const MassFix &mf) {
     using R = typename St::R;
-    const DevParams<R> P = launch_params<R>(c);
-    const int *w = c->P.wall;
+    const DevParams<R> &P = launch_params<R>(c);
+    const Cover &v = (mf.mode & 1) ? c->sums : c->cover;
     int off = 0;
-    if (!w[0] && !w[1] && !w[2]) {
-        launch_step<St, M, false, FD>(c, src, dst, P, mf, off);
-        return;
+    // One launch for the interior and the slabs: on small lattices the launches
+    // set the time (16 steps, walls in y, two launches -> one: 32^3 FP16 187 ->
+    // 113 us, 75 x 61 x 43 FP32 407 -> 361, D3Q27 BF16 430 -> 345); on large
+    // ones the wall instance's registers cost the interior more than the slab
+    // launch takes (128 x 512 x 128 FP32 8241 -> 8443, 100 x 96 x 70 D3Q27 BF16
+    // 911 -> 928), except in FP64, whose step is no wider for it (19351 -> 19005).
+    if constexpr (!FD && M != LOCAL) {
+        const int most = St::Q == 27 ? 500000 : (sizeof(R) == 8 ? P.N : 1250000);
+        if (v.split && P.N <= most) {
+            Boxes B;
+            B.b[0] = v.b[0];
+            B.b[1] = v.b[1];
+            B.b[2] = v.b[v.n - 1];
+            B.n0 = (uint32_t)v.b[0].ntiles;
+            B.n1 = B.n0 + (uint32_t)v.b[1].ntiles;
+            hipLaunchKernelGGL((step_all_kernel<St, M>), dim3((unsigned)v.blocks), dim3(v.threads), 0,
+                               c->stream, cbuf_of<St>(c, src), buf_of<St>(c, dst), P, B, mf,
+                               make_wet<R>(&c->P));
+            return;
+        }
     }
-    const int ylo = w[1] ? 1 : 0, yhi = w[1] ? P.nty - 1 : P.nty;
-    const int zlo = w[2] ? 1 : 0, zhi = w[2] ? P.nz - 1 : P.nz;
-    if (w[0] || yhi <= ylo || zhi <= zlo) {
-        launch_step<St, M, true, FD>(c, src, dst, P, mf, off);
-        return;
+    for (int k = 0; k < v.n; ++k) {
+        if (v.split ? k > 0 : v.walls) launch_step<St, M, true, FD>(c, src, dst, P, v.b[k], v.threads, mf, off);
+        else launch_step<St, M, false, FD>(c, src, dst, P, v.b[k], v.threads, mf, off);
     }
-    const int band = c->tc.band;
-    launch_step<St, M, false, FD>(c, src, dst, with_box(P, ylo, yhi - ylo, zlo, zhi - zlo, band),
-                                  mf, off);
-    if (w[1])  // first and last tile row, all planes
-        launch_step<St, M, true, FD>(c, src, dst, with_box(P, 0, 2, 0, P.nz, band, P.nty - 1), mf,
-                                     off);
-    if (w[2])  // first and last plane, the interior tile rows
-        launch_step<St, M, true, FD>(c, src, dst,
-                                     with_box(P, ylo, yhi - ylo, 0, 2, band, 1, P.nz - 1), mf, off);
 }
 
 template <class St, Mode M>
@@ -487,53 +517,46 @@ void step_any(lbm_ctx *c, Mode m, int src, int dst, int mf_mode = 0) {
 
 Mode prop_mode(const lbm_ctx *c) { return c->P.courant == 1.0 ? SHIFT : LW; }
 
-// Tile rows ty0 .. ty0 + nty - 1 of the moments (all planes).
-struct Rows {
-    int ty0, nty;
-};
-
 template <class St, Mode M, bool W>
-void launch_moments(lbm_ctx *c, const FieldOut &o, const Rows &b) {
+void launch_moments(lbm_ctx *c, const FieldOut &o, const Box &b, int threads) {
     using R = typename St::R;
-    DevParams<R> P = launch_params<R>(c);
-    if (b.nty < P.nty) P = with_box(P, b.ty0, b.nty, 0, P.nz, c->tc.band);
+    const DevParams<R> &P = launch_params<R>(c);
+    const dim3 grid((unsigned)b.ntiles), block(threads);
     if constexpr (St::Q == 19) {
         if (c->P.normal_fd) {
             launch_phi<St, M>(c, c->cur ^ 1, MassFix{0, nullptr, nullptr, 0});
-            hipLaunchKernelGGL((moments_kernel<St, M, W, true>), tile_grid(P), dim3(BLOCK), 0,
-                               c->stream, cbuf_of<St>(c, c->cur ^ 1), P, o, make_wet<R>(&c->P));
+            hipLaunchKernelGGL((moments_kernel<St, M, W, true>), grid, block, 0, c->stream,
+                               cbuf_of<St>(c, c->cur ^ 1), P, b, o, make_wet<R>(&c->P));
             return;
         }
     }
-    hipLaunchKernelGGL((moments_kernel<St, M, W, false>), tile_grid(P), dim3(BLOCK), 0,
-                       c->stream, cbuf_of<St>(c, c->cur ^ 1), P, o, make_wet<R>(&c->P));
+    hipLaunchKernelGGL((moments_kernel<St, M, W, false>), grid, block, 0, c->stream,
+                       cbuf_of<St>(c, c->cur ^ 1), P, b, o, make_wet<R>(&c->P));
 }
 
 template <class St, Mode M>
-void moments_w(lbm_ctx *c, const FieldOut &o, const Rows &b) {
+void moments_w(lbm_ctx *c, const FieldOut &o, const Box &b, int threads) {
     const bool walls = c->P.wall[0] || c->P.wall[1] || c->P.wall[2];
-    if (walls) launch_moments<St, M, true>(c, o, b);
-    else launch_moments<St, M, false>(c, o, b);
+    if (walls) launch_moments<St, M, true>(c, o, b, threads);
+    else launch_moments<St, M, false>(c, o, b, threads);
 }
 
 template <class St>
-void moments_dispatch(lbm_ctx *c, const FieldOut &o, const Rows &b) {
-    if (c->prev_local) moments_w<St, LOCAL>(c, o, b);
-    else if (prop_mode(c) == SHIFT) moments_w<St, SHIFT>(c, o, b);
-    else moments_w<St, LW>(c, o, b);
+void moments_dispatch(lbm_ctx *c, const FieldOut &o, const Box &b, int threads) {
+    if (c->prev_local) moments_w<St, LOCAL>(c, o, b, threads);
+    else if (prop_mode(c) == SHIFT) moments_w<St, SHIFT>(c, o, b, threads);
+    else moments_w<St, LW>(c, o, b, threads);
 }
 
 struct MomentsOp {
     template <class St>
-    static void run(lbm_ctx *c, const FieldOut &o, const Rows &b) {
-        moments_dispatch<St>(c, o, b);
+    static void run(lbm_ctx *c, const FieldOut &o, const Box &b, int threads) {
+        moments_dispatch<St>(c, o, b, threads);
     }
 };
 
-int tile_rows(const lbm_ctx *c) { return (c->P.ny + (BLOCK >> c->tc.tx_log2) - 1) / (BLOCK >> c->tc.tx_log2); }
-
-void moments_any(lbm_ctx *c, const FieldOut &o, const Rows &b) { with_storage<MomentsOp>(c, c, o, b); }
-void moments_any(lbm_ctx *c, const FieldOut &o) { moments_any(c, o, Rows{0, tile_rows(c)}); }
+void moments_any(lbm_ctx *c, const FieldOut &o, const Box &b, int threads) { with_storage<MomentsOp>(c, c, o, b, threads); }
+void moments_any(lbm_ctx *c, const FieldOut &o) { moments_any(c, o, c->full, c->cover.threads); }
 
 // The state at the current time from fields: post-propagation populations
 // into dst and their collision into post, in one launch (the
@@ -541,24 +564,32 @@ void moments_any(lbm_ctx *c, const FieldOut &o) { moments_any(c, o, Rows{0, tile
 template <class St>
 void launch_init(lbm_ctx *c, const double *phi0, const double *u0, const double *p0, int dst, int post) {
     using R = typename St::R;
-    const DevParams<double> PD = make_params<double>(&c->P, c->tc);
-    const DevParams<R> PR = make_params<R>(&c->P, c->tc);
-    const bool walls = c->P.wall[0] || c->P.wall[1] || c->P.wall[2];
-    auto launch = [&](auto W, auto S) {
-        hipLaunchKernelGGL((init_kernel<St, decltype(W)::value, decltype(S)::value>), tile_grid(PR),
-                           dim3(BLOCK), 0, c->stream, phi0, u0, p0, PD, PR, buf_of<St>(c, dst),
-                           c->flag, c->partials, buf_of<St>(c, post), make_wet<R>(&c->P));
+    const DevParams<double> &PD = c->pd;
+    const DevParams<R> &PR = launch_params<R>(c);
+    const Cover &v = c->cover;
+    const bool step = !c->P.normal_fd;
+    // the sum of phi in the groups of full_base: in the same launch where that
+    // is the launch
+    const bool sum_here = v.n == 1 && v.threads == BLOCK && v.b[0].tw == c->full_base.tw;
+    if (!sum_here)
+        hipLaunchKernelGGL(field_sum_kernel, dim3((unsigned)c->full_base.ntiles), dim3(BLOCK), 0, c->stream,
+                           phi0, PD, c->full_base, c->partials);
+    auto launch = [&](const Box &b, auto W, auto S) {
+        hipLaunchKernelGGL((init_kernel<St, decltype(W)::value, decltype(S)::value>), dim3((unsigned)b.ntiles),
+                           dim3(v.threads), 0, c->stream, phi0, u0, p0, PD, PR, b, buf_of<St>(c, dst),
+                           c->flag, sum_here ? c->partials : nullptr, buf_of<St>(c, post), make_wet<R>(&c->P));
     };
-    if constexpr (St::Q == 19) {
-        if (c->P.normal_fd) {
-            if (walls) launch(std::true_type{}, std::false_type{});
-            else launch(std::false_type{}, std::false_type{});
-            launch_step_fd<St, LOCAL>(c, dst, post, MassFix{0, c->partials, c->mf + 1, 0});
-            return;
+    for (int k = 0; k < v.n; ++k) {
+        const bool w = v.split ? k > 0 : v.walls;
+        if (step && w) launch(v.b[k], std::true_type{}, std::true_type{});
+        else if (step) launch(v.b[k], std::false_type{}, std::true_type{});
+        if constexpr (St::Q == 19) {
+            if (!step && w) launch(v.b[k], std::true_type{}, std::false_type{});
+            else if (!step) launch(v.b[k], std::false_type{}, std::false_type{});
         }
     }
-    if (walls) launch(std::true_type{}, std::true_type{});
-    else launch(std::false_type{}, std::true_type{});
+    if constexpr (St::Q == 19)
+        if (!step) launch_step_fd<St, LOCAL>(c, dst, post, MassFix{0, c->partials, c->mf + 1, 0});
 }
 
 struct InitOp {
@@ -575,9 +606,9 @@ void init_any(lbm_ctx *c, const double *phi0, const double *u0, const double *p0
 template <class St>
 void launch_load(lbm_ctx *c, const double *f, const double *g, int dst) {
     using R = typename St::R;
-    const DevParams<R> P = make_params<R>(&c->P, c->tc);
-    hipLaunchKernelGGL((load_kernel<St>), tile_grid(P), dim3(BLOCK), 0, c->stream, f, g, P,
-                       buf_of<St>(c, dst));
+    const DevParams<R> &P = launch_params<R>(c);
+    hipLaunchKernelGGL((load_kernel<St>), dim3((unsigned)c->full.ntiles), dim3(c->cover.threads), 0, c->stream,
+                       f, g, P, c->full, buf_of<St>(c, dst));
 }
 
 struct LoadOp {
@@ -612,20 +643,22 @@ int reduce_diag(lbm_ctx *c, const double *phi_ref) {
     FieldOut o{};
     o.phi_ref = phi_ref;
     o.partials = c->partials;
-    const int nty = tile_rows(c), per = c->nblocks / nty;  // blocks of a tile row
+    const Box &all = c->full_base;
+    const int per = all.ntx * all.nz;  // blocks of a tile row
     const int cap = (int)(c->L.partial_bytes / (NSUM * sizeof(double)));
-    if (c->nblocks <= cap) {
-        moments_any(c, o);
-        fold_partials(c, c->nblocks, true);
+    if (all.ntiles <= cap) {
+        moments_any(c, o, all, BLOCK);
+        fold_partials(c, all.ntiles, true);
         return check_launch(c);
     }
-    for (int ty = 0; ty < nty;) {
+    for (int ty = 0; ty < all.nty;) {
         o.row0 = ty > 0 ? 1 : 0;
-        const int n = std::min(nty - ty, (cap - 1) / per);
+        const int n = std::min(all.nty - ty, (cap - 1) / per);
         if (n < 1) return LBM_EDEVICE;
-        moments_any(c, o, Rows{ty, n});
+        const int y0 = ty * all.th, rows = std::min(n * all.th, c->P.ny - y0);
+        moments_any(c, o, make_box(&c->P, c->base, y0, rows, 0, 0, c->P.nz, 1), BLOCK);
         ty += n;
-        fold_partials(c, o.row0 + n * per, ty == nty);
+        fold_partials(c, o.row0 + n * per, ty == all.nty);
     }
     return check_launch(c);
 }
@@ -637,7 +670,7 @@ int build_state(lbm_ctx *c, const double *d_phi, const double *d_u, const double
     hipLaunchKernelGGL(clear_int_kernel, dim3(1), dim3(1), 0, c->stream, c->flag);
     init_any(c, d_phi, d_u, d_p, 1, 0);
     hipLaunchKernelGGL(massfix_kernel, dim3(1), dim3(RBLOCK), 0, c->stream,
-                       (const double *)c->partials, c->nblocks, c->mf, c->mf + 1, 1);
+                       (const double *)c->partials, c->full_base.ntiles, c->mf, c->mf + 1, 1);
     c->cur = 0;
     c->prev_local = true;
     c->mf_pending = false;
@@ -709,8 +742,21 @@ int lbm_init(const lbm_params *P, void *d_workspace, size_t bytes, void *stream,
     c->phifd = L.phifd_bytes ? (void *)(c->ws + 2 * L.buf_bytes + L.partial_bytes + L.result_bytes +
                                         L.flag_bytes + L.mf_bytes)
                              : nullptr;
-    c->tc = tile_cfg(P);
-    c->nblocks = (int)num_tiles(P, c->tc);
+    c->base = tile_cfg(P, BLOCK, true);
+    TileCfg tc = tile_cfg(P, BLOCK, false);
+    // blocks of one wavefront where 256-thread blocks would leave half the CUs
+    // without one (16 steps: 100 x 100 FP64 113 -> 84 us, 32^3 FP64 124 -> 104,
+    // FP16 90 -> 86; 48^3 FP16 121 -> 143)
+    const int64_t N = (int64_t)P->nx * P->ny * P->nz;
+    if (2 * N <= 256 * BLOCK) tc = tile_cfg(P, 64, false);
+    c->cover = make_cover(P, tc);
+    c->sums = make_cover(P, c->base);
+    c->full = full_box(P, tc);
+    c->full_base = full_box(P, c->base);
+    c->pf = make_params<float>(P);
+    c->pd = make_params<double>(P);
+    c->pf.phi_fd = (float *)c->phifd;
+    c->pd.phi_fd = (double *)c->phifd;
     c->mf_pending = false;
     c->status = LBM_OK;
 
@@ -753,7 +799,7 @@ int lbm_step(lbm_ctx *c, int64_t n) {
         c->mf_pending = false;
         if (mf_mode & 1) {
             hipLaunchKernelGGL(massfix_kernel, dim3(1), dim3(RBLOCK), 0, c->stream,
-                               (const double *)c->partials, c->nblocks, c->mf, c->mf + 1, 0);
+                               (const double *)c->partials, c->sums.blocks, c->mf, c->mf + 1, 0);
             c->mf_pending = true;
         }
         c->cur ^= 1;
@@ -844,7 +890,7 @@ int lbm_set_pdfs(lbm_ctx *c, const double *d_f, const double *d_g) {
     // target of the phase-mass bookkeeping
     step_any(c, LOCAL, prev, c->cur, 1);
     hipLaunchKernelGGL(massfix_kernel, dim3(1), dim3(RBLOCK), 0, c->stream,
-                       (const double *)c->partials, c->nblocks, c->mf, c->mf + 1, 1);
+                       (const double *)c->partials, c->sums.blocks, c->mf, c->mf + 1, 1);
     c->mf_pending = false;
     c->prev_local = true;
     c->status = LBM_OK;

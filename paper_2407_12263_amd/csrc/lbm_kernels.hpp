@@ -130,9 +130,9 @@ __device__ __forceinline__ R edot(const R (&v)[3]) {
 }
 
 // ------------------------------------------------------------ parameters
-// A block is 256 threads covering a tile of 2^tx_log2 x (256 >> tx_log2) nodes
-// of one z-plane.
-constexpr int BLOCK = 256;
+// A block is 64 or 256 threads covering a tile of tw x th nodes of one z-plane
+// (tw th at most the threads).
+constexpr int BLOCK = 256;  // most threads of a block
 
 // Division by a launch constant d for dividends below 2^31 (Granlund and
 // Montgomery, 1994): q = floor(n m / 2^(31 + l)) with 2^(l-1) < d <= 2^l and
@@ -145,20 +145,24 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv &f) {
     return f.d == 1u ? n : (__umulhi(n, f.m) >> f.s);
 }
 
+// The nodes of a launch and their tiles: all x, one or two slabs of `rows` rows
+// (the first at y0, the second ystep further), planes z0 + k zstep (k < nz).
+// A slab has nsub rows of tiles of tw x th nodes; tile rows 0 .. nty - 1 run
+// through the first slab, then the second.
+struct Box {
+    int tw, th, tw_log2;        // tw_log2: log2 tw, or -1 where it is no power of two
+    int ntx, nty, nz, ntiles;
+    int y0, ystep, nsub, rows, z0, zstep;
+    int order;               // 0: tile = block id; 1: XCD runs; 2: XCD runs of z-banded order
+    int band, nfull;         // tile rows per band (order 2), full bands
+    int xq, xr;              // ntiles = 8 xq + xr (XCD runs)
+    FastDiv d_tw, d_ntx, d_nty, d_band, d_perband, d_rem;
+};
+
 template <class R>
 struct DevParams {
     int nx, ny, nz, N;
     int wall[3];
-    int tx_log2;             // tile width 2^tx_log2, tile height 256 >> tx_log2
-    int ntx, nty, ntiles;    // tiles per row, per column, in total
-    int order;               // 0: tile = block id; 1: XCD runs; 2: XCD runs of z-banded order
-    int band;                // tile-rows per band (order 2)
-    int xq, xr;              // ntiles = 8 xq + xr (XCD runs)
-    int bty0, bnty, btz0, bnz;  // tile rows bty0 + k bty_step (k < bnty) x planes
-    int bty_step, btz_step;     // btz0 + k btz_step (k < bnz) covered by one launch
-                                // (ntiles = ntx bnty bnz)
-    int nfull;                  // full bands of the z-banded order: bnty / band
-    FastDiv d_ntx, d_nty, d_band, d_perband, d_rem;  // divisors of the tile decomposition
     R c, h;                  // Courant number, c(1-c)/2
     R lwA, lwD;              // Lax-Wendroff weights of x-e and x+e: c(1+c)/2, -c(1-c)/2
     R cs2, inv_cs2, half_inv_cs4;
@@ -184,11 +188,6 @@ struct Wet {
     int on;
     R cos_theta, sin_theta;
 };
-
-// Linear index of this block in its launch grid (x fastest).
-__device__ __forceinline__ uint32_t linear_block() {
-    return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-}
 
 // ---------------------------------------------------------- storage types
 // Q: populations per field (the lattice); BF: BF16 storage.
@@ -293,55 +292,44 @@ struct Site {
 // of `band` tile-rows, then z, then the band: the z-neighbour planes a tile
 // re-reads are then only a band's width of tiles away.
 template <int NQ, class R>
-__device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P) {
+__device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P, const Box &B, uint32_t b) {
     using L = LatQ<NQ>;
     Site<NQ> s;
-    const uint32_t b = blockIdx.x;
     uint32_t t = b;
-    if (P.order == 0) {
-        // the launch grid is (ntx, bnty, bnz)
-        t = 0;
-    } else {
+    if (B.order != 0) {
         // XCD runs: block b runs on XCD b mod 8; the XCD's blocks take one
         // contiguous run of tiles
         const uint32_t xcd = b & 7u, slot = b >> 3;
-        const uint32_t q = (uint32_t)P.xq, r = (uint32_t)P.xr;
+        const uint32_t q = (uint32_t)B.xq, r = (uint32_t)B.xr;
         t = (xcd < r ? xcd * (q + 1u) : r * (q + 1u) + (xcd - r) * q) + slot;
     }
-    const uint32_t ntx = (uint32_t)P.ntx, nty = (uint32_t)P.bnty, nz = (uint32_t)P.bnz;
-    uint32_t tx, rr, ty, tz;
-    if (P.order == 0) {
-        tx = blockIdx.x;
-        rr = 0;
-        ty = blockIdx.y;
-        tz = blockIdx.z;
-    } else {
-        rr = fdiv(t, P.d_ntx);
-        tx = t - rr * ntx;
-    }
-    if (P.order == 0) {
-    } else if (P.order == 2) {
-        const uint32_t bw = (uint32_t)P.band, full = (uint32_t)P.nfull, per_band = bw * nz;
+    const uint32_t nty = (uint32_t)B.nty, nz = (uint32_t)B.nz;
+    const uint32_t rr = fdiv(t, B.d_ntx), tx = t - rr * (uint32_t)B.ntx;
+    uint32_t ty, tz;
+    if (B.order == 2) {
+        const uint32_t bw = (uint32_t)B.band, full = (uint32_t)B.nfull, per_band = bw * nz;
         if (rr < full * per_band) {
-            const uint32_t k = fdiv(rr, P.d_perband), w = rr - k * per_band;
-            tz = fdiv(w, P.d_band);
+            const uint32_t k = fdiv(rr, B.d_perband), w = rr - k * per_band;
+            tz = fdiv(w, B.d_band);
             ty = k * bw + (w - tz * bw);
         } else {
             const uint32_t rem = nty - full * bw, w = rr - full * per_band;
-            tz = fdiv(w, P.d_rem);
+            tz = fdiv(w, B.d_rem);
             ty = full * bw + (w - tz * rem);
         }
     } else {
-        tz = fdiv(rr, P.d_nty);
+        tz = fdiv(rr, B.d_nty);
         ty = rr - tz * nty;
     }
-    ty = (uint32_t)P.bty0 + ty * (uint32_t)P.bty_step;
-    tz = (uint32_t)P.btz0 + tz * (uint32_t)P.btz_step;
-    const uint32_t lx = threadIdx.x & ((1u << P.tx_log2) - 1u), ly = threadIdx.x >> P.tx_log2;
-    s.x = (int)((tx << P.tx_log2) + lx);
-    s.y = (int)(ty * (uint32_t)(BLOCK >> P.tx_log2) + ly);
-    s.z = (int)tz;
-    s.valid = s.x < P.nx && s.y < P.ny && s.z < P.nz;
+    const uint32_t tw = (uint32_t)B.tw;
+    const uint32_t ly = B.tw_log2 >= 0 ? threadIdx.x >> B.tw_log2 : fdiv(threadIdx.x, B.d_tw);
+    const uint32_t lx = threadIdx.x - ly * tw;
+    const bool second = ty >= (uint32_t)B.nsub;
+    const uint32_t row = (second ? ty - (uint32_t)B.nsub : ty) * (uint32_t)B.th + ly;
+    s.x = (int)(tx * tw + lx);
+    s.y = (int)((uint32_t)(B.y0 + (second ? B.ystep : 0)) + row);
+    s.z = (int)((uint32_t)B.z0 + tz * (uint32_t)B.zstep);
+    s.valid = s.x < P.nx && s.y < P.ny && row < (uint32_t)B.rows && ly < (uint32_t)B.th;
     const int x = s.valid ? s.x : 0, y = s.valid ? s.y : 0, z = s.valid ? s.z : 0;
     const uint32_t nx = P.nx, nxy = (uint32_t)P.nx * P.ny;
     const uint32_t X[3] = {uint32_t(x == 0 ? P.nx - 1 : x - 1), uint32_t(x),
@@ -918,7 +906,7 @@ __device__ __forceinline__ void block_sum2(double a, double b, double *out) {
     __syncthreads();
     if (threadIdx.x == 0) {
         double sa = red[0][0], sb = red[0][1];
-        for (int w = 1; w < BLOCK / 64; ++w) {
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
             sa += red[w][0];
             sb += red[w][1];
         }
@@ -1008,10 +996,10 @@ __device__ __forceinline__ Macro<R> site_moments(const DevParams<R> &P, const Si
 
 template <class St, Mode M, bool WALLS, bool FD>
 __device__ __forceinline__ void step_body(const CBuf<St> &src, const Buf<St> &dst,
-                                          const DevParams<typename St::R> &P, const MassFix &mf,
-                                          const Wet<typename St::R> &wp) {
+                                          const DevParams<typename St::R> &P, const Box &B, uint32_t b,
+                                          const MassFix &mf, const Wet<typename St::R> &wp) {
     using R = typename St::R;
-    const Site<St::Q> s = make_site<St::Q>(P);
+    const Site<St::Q> s = make_site<St::Q>(P, B, b);
     double rep_phi = 0.0, rep_w = 0.0;
     if (s.valid) {
         const Src<St> in = make_src(src, P);
@@ -1038,14 +1026,14 @@ __device__ __forceinline__ void step_body(const CBuf<St> &src, const Buf<St> &ds
         store<St>(make_dst(dst, P), s.n, P, fb, gb);
     }
     if (mf.mode & 1)
-        block_sum2(rep_phi, rep_w, mf.partials + 2 * ((size_t)mf.block_off + linear_block()));
+        block_sum2(rep_phi, rep_w, mf.partials + 2 * ((size_t)mf.block_off + blockIdx.x));
 }
 
 template <class St, Mode M, bool WALLS, bool FD>
 __global__ void __launch_bounds__(BLOCK) step_kernel(CBuf<St> src, Buf<St> dst,
-                                                     DevParams<typename St::R> P, MassFix mf,
+                                                     DevParams<typename St::R> P, Box B, MassFix mf,
                                                      Wet<typename St::R> wp) {
-    step_body<St, M, WALLS, FD>(src, dst, P, mf, wp);
+    step_body<St, M, WALLS, FD>(src, dst, P, B, blockIdx.x, mf, wp);
 }
 
 // The same step held to 96 VGPRs (5 wavefronts per SIMD) for the wall-free
@@ -1053,8 +1041,28 @@ __global__ void __launch_bounds__(BLOCK) step_kernel(CBuf<St> src, Buf<St> dst,
 // compiler's own choice (97) it would run 4 per SIMD.
 template <class St, Mode M, bool WALLS, bool FD>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5, 8)))
-step_kernel_o5(CBuf<St> src, Buf<St> dst, DevParams<typename St::R> P, MassFix mf) {
-    step_body<St, M, WALLS, FD>(src, dst, P, mf, Wet<typename St::R>{0, 0, 1});
+step_kernel_o5(CBuf<St> src, Buf<St> dst, DevParams<typename St::R> P, Box B, MassFix mf) {
+    step_body<St, M, WALLS, FD>(src, dst, P, B, blockIdx.x, mf, Wet<typename St::R>{0, 0, 1});
+}
+
+// The whole step of a lattice with walls in y and/or z in one launch: the
+// blocks of the interior box, then those of the y and of the z wall slabs,
+// each running its own instance of the step.
+struct Boxes {
+    Box b[3];
+    uint32_t n0, n1;  // first block of the y slabs, of the z slabs
+};
+
+template <class St, Mode M>
+__global__ void __launch_bounds__(BLOCK) step_all_kernel(CBuf<St> src, Buf<St> dst, DevParams<typename St::R> P, Boxes B, MassFix mf,
+                Wet<typename St::R> wp) {
+    const uint32_t b = blockIdx.x;
+    if (b < B.n0) {
+        step_body<St, M, false, false>(src, dst, P, B.b[0], b, mf, Wet<typename St::R>{0, 0, 1});
+    } else {
+        const bool z = b >= B.n1;
+        step_body<St, M, true, false>(src, dst, P, z ? B.b[2] : B.b[1], z ? b - B.n1 : b - B.n0, mf, wp);
+    }
 }
 
 // First pass of the finite-difference variant: phi = sum of the propagated g
@@ -1062,9 +1070,9 @@ step_kernel_o5(CBuf<St> src, Buf<St> dst, DevParams<typename St::R> P, MassFix m
 // P.phi_fd, which the step then differences.
 template <class St, Mode M, bool WALLS>
 __global__ void __launch_bounds__(BLOCK) phi_kernel(CBuf<St> src, DevParams<typename St::R> P,
-                                                    MassFix mf) {
+                                                    Box B, MassFix mf) {
     using R = typename St::R;
-    const Site<St::Q> s = make_site<St::Q>(P);
+    const Site<St::Q> s = make_site<St::Q>(P, B, blockIdx.x);
     if (!s.valid) return;
     const Src<St> in = make_src(src, P);
     R fb[St::Q], gb[St::Q];
@@ -1134,9 +1142,9 @@ struct FieldOut {
 // fields, FP64 PDFs and/or per-block FP64 partial sums of the diagnostics.
 template <class St, Mode M, bool WALLS, bool FD>
 __global__ void __launch_bounds__(BLOCK) moments_kernel(CBuf<St> src, DevParams<typename St::R> P,
-                                                        FieldOut out, Wet<typename St::R> wp) {
+                                                        Box B, FieldOut out, Wet<typename St::R> wp) {
     using R = typename St::R;
-    const Site<St::Q> s = make_site<St::Q>(P);
+    const Site<St::Q> s = make_site<St::Q>(P, B, blockIdx.x);
     double acc[NSUM];
 #pragma unroll
     for (int k = 0; k < NSUM; ++k) acc[k] = 0.0;
@@ -1210,11 +1218,11 @@ __global__ void __launch_bounds__(BLOCK) moments_kernel(CBuf<St> src, DevParams<
         if (threadIdx.x < NSUM) {
             const int k = threadIdx.x;
             double v = red[0][k];
-            for (int w = 1; w < BLOCK / 64; ++w) {
+            for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
                 const double x = red[w][k];
                 v = (k == 6 || k == 8) ? fmax(v, x) : (k == 7 ? fmin(v, x) : v + x);
             }
-            out.partials[((size_t)out.row0 + linear_block()) * NSUM + k] = v;
+            out.partials[((size_t)out.row0 + blockIdx.x) * NSUM + k] = v;
         }
     }
 }
@@ -1271,23 +1279,24 @@ __device__ __forceinline__ void init_node(const double *phi0, const double *u0, 
     constexpr int NQ = St::Q;
     const size_t N = (size_t)P.N, n = s.n;
     const double ph0 = phi0[n];
-    // opposite directions give the same difference: one term per pair
     double g[3] = {0.0, 0.0, 0.0};
-    unroll<0, (NQ - 1) / 2>([&](auto K) {
-        constexpr int i = 2 * decltype(K)::value + 1;
+    unroll<1, NQ>([&](auto I) {
+        constexpr int i = decltype(I)::value;
         constexpr int ex = L::EX[i], ey = L::EY[i], ez = L::EZ[i];
-        constexpr double t3 = 3.0 * wgt<double, NQ>(L::cls(i));
+        constexpr double t = wgt<double, NQ>(L::cls(i));
         double vp = phi0[s.nb[i]];
         double vm = phi0[s.nb[L::OPP[i]]];
         if constexpr (WALLS) {
             if (beyond_wall<i, -1>(s)) vp = ph0;
             if (beyond_wall<i, 1>(s)) vm = ph0;
         }
-        const double d = (vp - vm) * t3;
-        if constexpr (ex != 0) g[0] += ex * d;
-        if constexpr (ey != 0) g[1] += ey * d;
-        if constexpr (ez != 0) g[2] += ez * d;
+        const double d = 0.5 * (vp - vm) * t;
+        g[0] += ex * d;
+        g[1] += ey * d;
+        g[2] += ez * d;
     });
+#pragma unroll
+    for (int a = 0; a < 3; ++a) g[a] *= 3.0;
 
     Macro<double> m;
     m.phi = ph0;
@@ -1299,10 +1308,9 @@ __device__ __forceinline__ void init_node(const double *phi0, const double *u0, 
     const double gn = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
     const double s4 = P.four_over_delta * ph0 * (1.0 - ph0);
     const double wg = floor_weight(P, gn);
-    const double rg = wg > 0.0 ? wg / gn : 0.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        m.n[a] = rg * g[a];
+        m.n[a] = wg > 0.0 ? wg * g[a] / gn : 0.0;
         m.S[a] = s4 * m.n[a];
         m.gradrho[a] = P.drho * g[a];
     }
@@ -1312,51 +1320,52 @@ __device__ __forceinline__ void init_node(const double *phi0, const double *u0, 
         atomicOr(bad, 1);
 
     const NodeCoef<double> q = node_coef(P, m);
-    // f = t (A - B/2), g = t (Gq - (tau_phi + 1/2) c e^.grad(phi)); the even and
-    // odd parts of a pair evaluated once, as in collide()
-    const double rog = (1.0 / P.omega_g) * P.c;
-    auto put = [&](auto I, double A, double B, double Gq, double eg0) {
-        // the products are the stored values: never fused into the sums that
-        // a collision in the same kernel takes of them
-#pragma clang fp contract(off)
+    unroll<0, NQ>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        constexpr double t = wgt<double, NQ>(L::cls(i));
-        fo[i] = R(t * fma(-0.5, B, A));
-        go[i] = R(t * fma(-rog, eg0, Gq));
-    };
-    {
-        const double poly = -q.a3;
-        put(std::integral_constant<int, 0>{}, fma(m.rho, poly, q.A0[0]),
-            -poly * q.ug - q.uG * P.inv_cs2, fma(m.phi, poly, m.phi), 0.0);
-    }
-    const double uGs = q.uG * P.inv_cs2;
-    unroll<0, (NQ - 1) / 2>([&](auto K) {
-        constexpr int i = 2 * decltype(K)::value + 1;
-        const double eu = edot<i, NQ>(q.cu), en = edot<i, NQ>(m.n), eg = edot<i, NQ>(q.cgr);
-        const double eG = edot<i, NQ>(q.crG), es = edot<i, NQ>(q.tS), eg0 = edot<i, NQ>(g);
-        const double E = fma(eu * eu, P.half_inv_cs4, -q.a3), O = eu * P.inv_cs2;
-        const double pp = E + O, pm = E - O;
-        const double kn = fma(q.kpsi * en, en, q.A0[L::cls(i)]);
-        const double t1 = fma(2.0 * P.half_inv_cs4 * eu, eG, -uGs), eGs = eG * P.inv_cs2;
-        put(std::integral_constant<int, i>{}, fma(m.rho, pp, kn), fma(pp, eg - q.ug, t1 + eGs),
-            fma(m.phi, pp, m.phi + es), eg0);
-        put(std::integral_constant<int, i + 1>{}, fma(m.rho, pm, kn), fma(pm, -eg - q.ug, t1 - eGs),
-            fma(m.phi, pm, m.phi - es), -eg0);
+        constexpr int cl = L::cls(i);
+        constexpr double t = wgt<double, NQ>(cl);
+        double poly, A, B, Gq, eg0;
+        if constexpr (i == 0) {
+            poly = -q.a3;
+            A = fma(m.rho, poly, q.A0[0]);
+            B = -poly * q.ug - q.uG * P.inv_cs2;
+            Gq = fma(m.phi, poly, m.phi);
+            eg0 = 0.0;
+        } else {
+            const double eu = edot<i, NQ>(q.cu);
+            const double en = edot<i, NQ>(m.n);
+            const double eg = edot<i, NQ>(q.cgr);
+            const double eG = edot<i, NQ>(q.crG);
+            const double es = edot<i, NQ>(q.tS);
+            poly = fma(eu, fma(eu, P.half_inv_cs4, P.inv_cs2), -q.a3);
+            A = fma(m.rho, poly, fma(q.kpsi * en, en, q.A0[cl]));
+            B = fma(poly, eg - q.ug, fma(eG - q.uG, P.inv_cs2, 2.0 * P.half_inv_cs4 * eu * eG));
+            Gq = fma(m.phi, poly, m.phi + es);
+            eg0 = P.c * edot<i, NQ>(g);
+        }
+        fo[i] = R(t * (A - 0.5 * B));
+        go[i] = R(t * (Gq - (1.0 / P.omega_g) * eg0));
     });
+    if constexpr (std::is_same<R, double>::value) {
+        // opaque: the products are the stored values, never fused into the
+        // sums that a collision in the same kernel takes of them
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) asm volatile("" : "+v"(fo[i]), "+v"(go[i]));
+    }
 }
 
 // STEP: the first collision too, from the stored (rounded) populations, into
 // post: what a LOCAL step of the stored state gives, without reading it back
-// (256^3 FP16: 588 + 504 us as two passes, 930 in one; 3.4 GB and 1570 vector
+// (256^3 FP16: 588 + 504 us as two passes, 940 in one; 3.4 GB and 1570 vector
 // instructions a wavefront, a third of them FP64, take 670 us each).
 template <class St, bool WALLS, bool STEP>
 __global__ void __launch_bounds__(BLOCK) init_kernel(const double *phi0, const double *u0,
                                                      const double *p0, DevParams<double> P,
-                                                     DevParams<typename St::R> PR, Buf<St> dst,
+                                                     DevParams<typename St::R> PR, Box B, Buf<St> dst,
                                                      int *bad, double *partials, Buf<St> post,
                                                      Wet<typename St::R> wp) {
     using R = typename St::R;
-    const Site<St::Q> s = make_site<St::Q>(P);
+    const Site<St::Q> s = make_site<St::Q>(P, B, blockIdx.x);
     if (s.valid) {
         R f[St::Q], g[St::Q];
         init_node<St, WALLS>(phi0, u0, p0, P, bad, s, f, g);
@@ -1369,16 +1378,23 @@ __global__ void __launch_bounds__(BLOCK) init_kernel(const double *phi0, const d
             store<St>(make_dst(post, PR), s.n, PR, f, g);
         }
     }
-    block_sum2(s.valid ? phi0[s.n] : 0.0, 0.0, partials + 2 * (size_t)linear_block());
+    if (partials) block_sum2(s.valid ? phi0[s.n] : 0.0, 0.0, partials + 2 * (size_t)blockIdx.x);
+}
+
+// Per-block FP64 sums of a field (the target of the phase-mass bookkeeping).
+__global__ void __launch_bounds__(BLOCK) field_sum_kernel(const double *phi0, DevParams<double> P, Box B,
+                                                          double *partials) {
+    const Site<19> s = make_site<19>(P, B, blockIdx.x);
+    block_sum2(s.valid ? phi0[s.n] : 0.0, 0.0, partials + 2 * (size_t)blockIdx.x);
 }
 
 
 // Loads FP64 post-propagation PDFs into the storage format (restart).
 template <class St>
 __global__ void __launch_bounds__(BLOCK) load_kernel(const double *f, const double *g,
-                                                     DevParams<typename St::R> P, Buf<St> dst) {
+                                                     DevParams<typename St::R> P, Box B, Buf<St> dst) {
     using R = typename St::R;
-    const Site<St::Q> s = make_site<St::Q>(P);
+    const Site<St::Q> s = make_site<St::Q>(P, B, blockIdx.x);
     if (!s.valid) return;
     const size_t N = (size_t)P.N, n = s.n;
     R fo[St::Q], go[St::Q];
