@@ -72,6 +72,17 @@ int sur_conv3d_pool(const void *x, int32_t cin, const void *w, const float *bias
                     int32_t nx, int32_t ny, int32_t nz, int32_t relu, void *y_bf16, void *y_pool,
                     void *stream);
 
+/* The data gradient of that decoder convolution, with the adjoint of the
+ * upsampling: of dx = sur_conv3d(dy, flip = 1) with cup + cskip channels (w the
+ * [27][cup + cskip][cin] packing, cin the channels of dy), the first cup
+ * channels go through sur_upsample2_bwd_mask (dup_bf16 [P/8][cup], act BF16
+ * [P/8][cup]) and the others are stored in FP32 dskip [P][cskip]; bitwise the
+ * two calls in turn, without storing the first cup channels of dx. Needs the
+ * tiled kernel (nx a multiple of 16, ny and nz of 4, 16-byte aligned dy, w and
+ * dskip) and 8-byte aligned act and dup_bf16; otherwise SUR_EINVAL. */
+int sur_conv3d_dgrad_cat(const void *dy, int32_t cin, const void *w, int32_t cup, int32_t cskip, int32_t nx,
+                         int32_t ny, int32_t nz, const void *act, void *dup_bf16, float *dskip, void *stream);
+
 /* Floats of scratch that sur_conv3d_wgrad needs for these sizes. */
 size_t sur_wgrad_scratch_floats(int32_t cin, int32_t cout, int32_t nx, int32_t ny, int32_t nz);
 
@@ -81,6 +92,14 @@ size_t sur_wgrad_scratch_floats(int32_t cin, int32_t cout, int32_t nx, int32_t n
 int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, int32_t nx,
                      int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
                      float *dbias, void *stream);
+
+/* The same of the concat [up2(xc), xf] (xc BF16 [P/8][cc], xf [P][fc]) read in
+ * place, bitwise sur_conv3d_wgrad of the written concat with cin = cc + fc.
+ * Needs nx a multiple of 16, ny and nz of 4, at least 256 points, cout at most
+ * 64 and 16-byte aligned xc, xf and dy; otherwise SUR_EINVAL. */
+int sur_conv3d_wgrad_cat(const void *xc, int32_t cc, const void *xf, int32_t fc, const void *dy, int32_t cout,
+                         int32_t nx, int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
+                         float *dbias, void *stream);
 
 /* BF16 packings of FP32 master weights w[27][cout][cin]: wf (same layout)
  * and wd[27][cin][cout] (per-tap transpose, for the data gradient). */

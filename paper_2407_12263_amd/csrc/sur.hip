@@ -446,7 +446,18 @@ constexpr int conv_min_waves() { return WPF ? 2 : (NT == 1 ? 4 : 1); }
 // KB) is re-read 2.1 times instead of 2.5, and a block's staging and
 // barriers serve twice the points. With a few input chunks their weights
 // all stay in LDS (G.wres), staged once per kernel.
-template <int NT, bool FLIP, bool POW2, bool CAT, bool WPF, bool POOL, int WV = 4>
+// With UP (the data gradient of a decoder level's first convolution, whose
+// input was the concat of an upsampled tensor and a skip) the first cc output
+// channels are not stored at the fine points: the eight values of each
+// 2 x 2 x 2 cell are summed in FP32 in the order x, then y, then z (the
+// adjoint of the upsampling), masked by mask (the coarse activation, BF16
+// [P / 8][cc]) and stored as BF16 in yp; the others are stored in FP32 in yf
+// ([P][cout - cc]). Bound by staging and products as the plain form, but the
+// memory traffic is a third: 128^3 16 -> 32 + 16 stores 142 MB and reads 8 of
+// masks where all of dx is 403 MB written and 268 read again; 160 us against
+// 147 + 78 for the two passes (64^3 32 -> 48 + 32: 59 against 51 + 12; 32^3
+// 48 -> 64 + 48: 16.5 against 17 + 8).
+template <int NT, bool FLIP, bool POW2, bool CAT, bool WPF, bool POOL, int WV = 4, bool UP = false>
 __global__ void __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(conv_min_waves<NT, WPF>(), 8)))
 conv3d_tiled_kernel(
     const uint16_t *__restrict__ x, int cin, const uint16_t *__restrict__ xc, int cc,
@@ -554,7 +565,8 @@ conv3d_tiled_kernel(
     // before them (loads complete in order): the bias is loaded once, and
     // the data gradient's mask words before that halo (PREMASK; not in the
     // four-wavefront one-tile form, whose 128 VGPRs have no room for them).
-    constexpr bool PREMASK = FLIP && (WV == 8 || NT > 1 || WPF);
+    static_assert(!UP || (FLIP && !CAT && !POOL), "the fused upsampling adjoint is a data gradient's");
+    constexpr bool PREMASK = FLIP && !UP && (WV == 8 || NT > 1 || WPF);
     float bvv[NT][4];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
@@ -580,6 +592,14 @@ conv3d_tiled_kernel(
             for (int mt = 0; mt < 4; ++mt) mrow[nt][mt] = *(const uint2 *)(mask + out_off(x0, y0, z0, mt, nt));
         }
     };
+    // UP: element of channel tile nt of the cell of row pair pr (even lanes and
+    // wavefronts), and the cells' mask words, loaded as the mask rows are
+    auto cell_off = [&](int x0, int y0, int z0, int pr, int nt) -> uint32_t {
+        const uint32_t cell = (uint32_t)(((x0 + r) >> 1) + (G.nx >> 1) * (((y0 >> 1) + pr) + (G.ny >> 1) * ((z0 + wave) >> 1)));
+        return cell * (uint32_t)cc + (uint32_t)(cob + nt * 16 + 4 * q);
+    };
+    const int nup = UP ? min(max((cc - cob) >> 4, 0), ntiles) : 0;  // tiles of summed channels
+    uint2 um[UP ? NT : 1][2];
     f4 acc[4][NT];
     for (int k = 0; k < nmine; ++k) {
         for (int chunk = 0; chunk < nchunk; ++chunk) {
@@ -594,6 +614,17 @@ conv3d_tiled_kernel(
             __syncthreads();
             if constexpr (PREMASK)
                 if (mask && chunk + 1 == nchunk) load_mask(k);
+            if constexpr (UP) {
+                if (chunk + 1 == nchunk && !(wave & 1)) {
+                    int x0, y0, z0;
+                    tile_origin<POW2, TZ>(G, (int)blockIdx.x + k * (int)gridDim.x, x0, y0, z0);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        if (nt < nup)
+#pragma unroll
+                            for (int pr = 0; pr < 2; ++pr) um[nt][pr] = *(const uint2 *)(mask + cell_off(x0, y0, z0, pr, nt));
+                }
+            }
             if (chunk + 1 < nchunk) {
                 load_halo(k, chunk + 1);
                 if (WPF) load_weights((chunk + 1) * 16);
@@ -627,6 +658,70 @@ conv3d_tiled_kernel(
         // x0 + px of row mt of its plane, in register j of acc[mt][nt]
         int x0, y0, z0;
         tile_origin<POW2, TZ>(G, (int)blockIdx.x + k * (int)gridDim.x, x0, y0, z0);
+        if constexpr (UP) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                if (nt < nup || nt >= ntiles) continue;
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) {
+                    const uint32_t p = POW2 ? (uint32_t)((x0 + r) | ((y0 + mt) << G.lx) | ((z0 + wave) << G.lxy))
+                                            : (uint32_t)((x0 + r) + G.nx * ((y0 + mt) + G.ny * (z0 + wave)));
+                    *(f4 *)(yf + p * (uint32_t)(cout - cc) + (uint32_t)(cob + nt * 16 - cc + 4 * q)) = acc[mt][nt];
+                }
+            }
+            if (nup == 0) continue;  // the same for the whole block
+            // as the pooling below: the x pair in the next lane, the y pair in
+            // the lane's next row, the z pair in the next wavefront, which
+            // hands its four values over in LDS (the halo, free once every
+            // wavefront is here: at most 4 KB per pair of wavefronts and tile)
+            float *ex = (float *)tile;
+            const int pair = wave >> 1;
+            auto slot = [&](int nt, int pr) {
+                return (f4 *)(ex + ((((pair * NT + nt) * 2 + pr) * 32) + (q * 8 + (r >> 1))) * 16);
+            };
+            __syncthreads();
+            f4 sum[NT][2];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                if (nt >= nup) break;
+#pragma unroll
+                for (int pr = 0; pr < 2; ++pr) {
+                    f4 n0, n1;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        n0[j] = __shfl_xor(acc[2 * pr][nt][j], 1, 64);
+                        n1[j] = __shfl_xor(acc[2 * pr + 1][nt][j], 1, 64);
+                    }
+                    if ((wave & 1) && !(r & 1)) {
+                        f4 *e = slot(nt, pr);
+                        e[0] = acc[2 * pr][nt];
+                        e[1] = n0;
+                        e[2] = acc[2 * pr + 1][nt];
+                        e[3] = n1;
+                    }
+                    sum[nt][pr] = (((f4{0.f, 0.f, 0.f, 0.f} + acc[2 * pr][nt]) + n0) + acc[2 * pr + 1][nt]) + n1;
+                }
+            }
+            __syncthreads();
+            if (!(wave & 1) && !(r & 1)) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (nt >= nup) break;
+#pragma unroll
+                    for (int pr = 0; pr < 2; ++pr) {
+                        const f4 *e = slot(nt, pr);
+                        const f4 s = (((sum[nt][pr] + e[0]) + e[1]) + e[2]) + e[3];
+                        const uint32_t mw[2] = {um[nt][pr].x, um[nt][pr].y};
+                        uint32_t h[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            h[j] = f2bf(bf2f((uint16_t)(mw[j >> 1] >> (16 * (j & 1)))) > 0.f ? s[j] : 0.f);
+                        *(uint2 *)(yp + cell_off(x0, y0, z0, pr, nt)) = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+                    }
+                }
+            }
+            continue;
+        }
         float rv[POOL && !POOL1 ? NT : 1][4][4];  // the stored BF16 values, for the pooling
         // the rows; MODE 1: bias, ReLU and BF16 output only (the forward's
         // hidden layers), 2: bias and FP32 output only (its last layer), 3
@@ -1150,13 +1245,15 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
 // partial dW goes to part[block][t][o][i] and the partials are summed in
 // fixed order. One M tile keeps four wavefronts per SIMD (the LDS allows
 // four blocks per CU).
-template <int MT, bool RAG, bool FLUSH = false>
+// CAT: the input is the decoder's concat [up2(xc), x] read in place, as in the
+// forward: chunks below ccat from the coarse tensor at the parent point.
+template <int MT, bool RAG, bool FLUSH = false, bool CAT = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 1 && !FLUSH ? 4 : 1, 8)))
 wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
                    const uint16_t *__restrict__ dy, int cout,
                    int nx, int ny, int nz,
                    float *__restrict__ part,
-                   float *__restrict__ bpart) {
+                   float *__restrict__ bpart, const uint16_t *__restrict__ xc = nullptr, int ccat = 0) {
     constexpr int kRow = kWgRow;                // hx row length in XhT
     constexpr int kCh = kWgCh;                  // XhT channel stride (1744 B)
     constexpr int kXh = 16 * kCh;               // XhT elements
@@ -1250,6 +1347,16 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
                     if (y0 - 1 + hy > ny || z0 - 1 + hz > nz || x0 - 1 + hx > nx) continue;
                 }
                 const int gy = wrap(y0 - 1 + hy, ny), gz = wrap(z0 - 1 + hz, nz);
+                if constexpr (CAT) {
+                    const int X0 = wrap(x0 - 1 + hx, nx), X1 = wrap(x0 + hx, nx);
+                    const bool up = cc < ccat;
+                    const int row = up ? (nx >> 1) * ((gy >> 1) + (ny >> 1) * (gz >> 1)) : nx * (gy + ny * gz);
+                    const int st = up ? ccat : cin - ccat;
+                    const uint16_t *b = up ? xc + cc + e0 : x + (cc - ccat) + e0;
+                    xv[it][0] = *(const uint4 *)(b + (row + (up ? X0 >> 1 : X0)) * st);
+                    xv[it][1] = *(const uint4 *)(b + (row + (up ? X1 >> 1 : X1)) * st);
+                    continue;
+                }
                 const int g0 = wrap(x0 - 1 + hx, nx) + nx * (gy + ny * gz);
                 xv[it][0] = *(const uint4 *)(x + g0 * cin + cc + e0);
                 if (RAG && x0 + hx > nx) continue;
@@ -2422,10 +2529,13 @@ int conv_waves(int cin, int cout, int nx, int ny, int nz, int cus) {
 // Launches conv3d_tiled_kernel; xc != NULL selects the concat form (cc
 // channels of the upsampled coarse tensor first, then cin - cc of x);
 // y_pool != NULL the pooled output as well (forward form, BF16 output; with
-// one output tile only on eight wavefronts or in the small-grid form).
+// one output tile only on eight wavefronts or in the small-grid form); up the
+// data gradient with the upsampling's adjoint (two output tiles or the
+// small-grid form).
 void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const void *w,
                        const float *bias, int cout, int nx, int ny, int nz, bool flip, int relu,
-                       const void *mask, void *y_bf16, float *y_f32, void *y_pool, hipStream_t st) {
+                       const void *mask, void *y_bf16, float *y_f32, void *y_pool, hipStream_t st,
+                       bool up = false) {
     const long P = (long)nx * ny * nz;
     // one N tile per block for 16 output channels (fewer registers), two otherwise
     int nt = cout <= 16 ? 1 : kNT;
@@ -2455,7 +2565,7 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
     // only, both give the same bits)
     const char *wrv = std::getenv("SUR_CONV_WRES");
     const int nchunk = cin / 16;
-    const bool pool1 = y_pool && (nt == 1 || nwv == 8);
+    const bool pool1 = !up && y_pool && (nt == 1 || nwv == 8);
     const bool wres = nwv == 8 && nchunk > 1 && conv_tiled_lds(nt, nwv, nchunk, pool1) <= (nt == 1 ? 80 : 160) * 1024 &&
                       !(wrv && *wrv == '0');
     const size_t lds = conv_tiled_lds(nt, nwv, wres ? nchunk : 1, pool1);
@@ -2498,7 +2608,23 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
 #define SUR_CONV_WV8N2(FL, P2, CT, PL)                                                         \
     hipLaunchKernelGGL((conv3d_tiled_kernel<kNT, FL, P2, CT, false, PL, 8>), grid, dim3(512), lds, st, \
                        xb, cin, xcb, cc, wb, bias, cout, G, relu, mb, yb, y_f32, yp)
-    if (nwv == 8 && nt == kNT) {
+#define SUR_CONV_UP(NTV, WP, WVV)                                                                       \
+    do {                                                                                              \
+        if (pow2)                                                                                     \
+            hipLaunchKernelGGL((conv3d_tiled_kernel<NTV, true, true, false, WP, false, WVV, true>), grid, \
+                               dim3(64 * WVV), lds, st, xb, cin, xcb, cc, wb, bias, cout, G, relu, mb, yb, \
+                               y_f32, yp);                                                            \
+        else                                                                                          \
+            hipLaunchKernelGGL((conv3d_tiled_kernel<NTV, true, false, false, WP, false, WVV, true>), grid, \
+                               dim3(64 * WVV), lds, st, xb, cin, xcb, cc, wb, bias, cout, G, relu, mb, yb, \
+                               y_f32, yp);                                                            \
+    } while (0)
+    if (up) {
+        if (nwv == 8) SUR_CONV_UP(kNT, false, 8);
+        else if (splitn) SUR_CONV_UP(1, true, 4);
+        else if (wpf) SUR_CONV_UP(kNT, true, 4);
+        else SUR_CONV_UP(kNT, false, 4);
+    } else if (nwv == 8 && nt == kNT) {
         if (pool1) {
             if (pow2) SUR_CONV_WV8N2(false, true, false, true); else SUR_CONV_WV8N2(false, false, false, true);
         } else if (xc) {
@@ -2535,6 +2661,7 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
         if (flip) SUR_CONV_NT2(true, false, false);
         else SUR_CONV_NT2(false, false, false);
     }
+#undef SUR_CONV_UP
 #undef SUR_CONV_WV8
 #undef SUR_CONV_WV8N2
 #undef SUR_CONV_NT2
@@ -2697,6 +2824,18 @@ int sur_conv3d_pool(const void *x, int32_t cin, const void *w, const float *bias
     return launched();
 }
 
+int sur_conv3d_dgrad_cat(const void *dy, int32_t cin, const void *w, int32_t cup, int32_t cskip, int32_t nx,
+                         int32_t ny, int32_t nz, const void *act, void *dup_bf16, float *dskip, void *stream) {
+    clear_stale_error();
+    if (!dy || !w || !act || !dup_bf16 || !dskip || cin <= 0 || cup <= 0 || cskip <= 0 || cin % 16 ||
+        cup % 16 || cskip % 16 || !dims_ok(nx, ny, nz) || !conv_tiled_ok(dy, cin, w, cup + cskip, nx, ny, nz) ||
+        (((uintptr_t)act | (uintptr_t)dup_bf16) & 7) != 0 || !aligned16(dskip))
+        return SUR_EINVAL;
+    conv_tiled_launch(dy, cin, nullptr, cup, w, nullptr, cup + cskip, nx, ny, nz, true, 0, act, nullptr, dskip,
+                      dup_bf16, (hipStream_t)stream, true);
+    return launched();
+}
+
 size_t sur_wgrad_scratch_floats(int32_t cin, int32_t cout, int32_t nx, int32_t ny, int32_t nz) {
     const long P = (long)nx * ny * nz;
     const long parts = std::max(wgrad_chunks(P), wgrad_tiled_blocks(cin, P));
@@ -2707,9 +2846,15 @@ size_t sur_wgrad_scratch_floats(int32_t cin, int32_t cout, int32_t nx, int32_t n
                     kSumSeg * (long)cout);
 }
 
-int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, int32_t nx,
-                     int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
-                     float *dbias, void *stream) {
+}  // extern "C"
+
+namespace {
+
+// sur_conv3d_wgrad; xc != NULL selects the concat form (cc channels of the
+// upsampled coarse tensor first, then cin - cc of x).
+int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void *dy, int32_t cout,
+              int32_t nx, int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
+              float *dbias, void *stream) {
     clear_stale_error();
     if (!x || !dy || !scratch || !dw || cin <= 0 || cout <= 0 || cin % 16 || cout % 16 ||
         cout > 64 || !dims_ok(nx, ny, nz))
@@ -2734,16 +2879,28 @@ int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, i
         // 7.2e-8; and 32 blocks instead of 8) take the flushed form (1.6e-7
         // and 7.1e-8); in between the plain form is as exact and faster
         const long tiles = rag_tiles(nx, ny, nz);
-        if (rag && (tiles > 8 * nch || P < 4096)) {
+        const uint16_t *xcb = (const uint16_t *)xc;
+        if (xc) {
+#define SUR_WG_CAT(M)                                                                              \
+    hipLaunchKernelGGL((wgrad_tiled_kernel<M, false, false, true>), grid, dim3(256), 0, s, xb, cin, \
+                       db, cout, nx, ny, nz, scratch, bp, xcb, cc)
+            switch (cout / 16) {
+                case 1: SUR_WG_CAT(1); break;
+                case 2: SUR_WG_CAT(2); break;
+                case 3: SUR_WG_CAT(3); break;
+                default: SUR_WG_CAT(4); break;
+            }
+#undef SUR_WG_CAT
+        } else if (rag && (tiles > 8 * nch || P < 4096)) {
             const dim3 gz(grid.x, grid.y, (unsigned)(cout / 16));
             hipLaunchKernelGGL((wgrad_tiled_kernel<1, true, true>), gz, dim3(256), 0, s, xb, cin, db,
-                               cout, nx, ny, nz, scratch, bp);
+                               cout, nx, ny, nz, scratch, bp, nullptr, 0);
         } else
 #define SUR_WG_LAUNCH(M)                                                                             \
     if (rag) hipLaunchKernelGGL((wgrad_tiled_kernel<M, true>), grid, dim3(256), 0, s, xb, cin, db,   \
-                                cout, nx, ny, nz, scratch, bp);                                      \
+                                cout, nx, ny, nz, scratch, bp, nullptr, 0);                          \
     else hipLaunchKernelGGL((wgrad_tiled_kernel<M, false>), grid, dim3(256), 0, s, xb, cin, db, cout, \
-                            nx, ny, nz, scratch, bp)
+                            nx, ny, nz, scratch, bp, nullptr, 0)
         switch (cout / 16) {
             case 1: SUR_WG_LAUNCH(1); break;
             case 2: SUR_WG_LAUNCH(2); break;
@@ -2807,6 +2964,26 @@ int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, i
         hipLaunchKernelGGL(sum_chunks_kernel, grid1(cout, 32), dim3(256), 0, s, (const float *)bp, nb, (long)cout, dbias);
     }
     return launched();
+}
+
+}  // namespace
+
+extern "C" {
+
+int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, int32_t nx,
+                     int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
+                     float *dbias, void *stream) {
+    return wgrad_run(x, cin, nullptr, 0, dy, cout, nx, ny, nz, scratch, scratch_floats, dw, dbias, stream);
+}
+
+int sur_conv3d_wgrad_cat(const void *xc, int32_t cc, const void *xf, int32_t fc, const void *dy, int32_t cout,
+                         int32_t nx, int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
+                         float *dbias, void *stream) {
+    clear_stale_error();
+    if (!xc || !xf || !dy || cc <= 0 || fc <= 0 || cc % 16 || fc % 16 || cout <= 0 || !dims_ok(nx, ny, nz) ||
+        nx % kTX || ny % kTY || nz % kTZ || !aligned16(xc) || !wgrad_tiled_ok(xf, cc + fc, dy, cout, nx, ny, nz))
+        return SUR_EINVAL;
+    return wgrad_run(xf, cc + fc, xc, cc, dy, cout, nx, ny, nz, scratch, scratch_floats, dw, dbias, stream);
 }
 
 int sur_pack_weights_all(const float *w, int32_t nlayers, const int64_t *w_off, const int32_t *cin,

@@ -46,6 +46,8 @@ def load_library(path: str | None = None):
     lib.sur_wgrad_scratch_floats.argtypes = [i32, i32, i32, i32, i32]
     lib.sur_wgrad_scratch_floats.restype = sz
     lib.sur_conv3d_wgrad.argtypes = [vp, i32, vp, i32, i32, i32, i32, vp, sz, vp, vp, vp]
+    lib.sur_conv3d_dgrad_cat.argtypes = [vp, i32, vp, i32, i32, i32, i32, i32, vp, vp, vp, vp]
+    lib.sur_conv3d_wgrad_cat.argtypes = [vp, i32, vp, i32, vp, i32, i32, i32, i32, vp, sz, vp, vp, vp]
     lib.sur_pack_weights.argtypes = [vp, i32, i32, vp, vp, vp]
     lib.sur_pool2.argtypes = [vp, i32, i32, i32, i32, vp, vp]
     lib.sur_pool2_bwd.argtypes = [vp, i32, i32, i32, i32, vp, vp]
@@ -72,7 +74,7 @@ def load_library(path: str | None = None):
     lib.sur_prolong_update_scratch_doubles.argtypes = [i32, i32, i32]
     lib.sur_prolong_update_scratch_doubles.restype = sz
     lib.sur_prolong_update.argtypes = [vp, vp, i32, i32, i32, vp, C.c_double, vp, vp, vp, vp, vp, vp]
-    for n in ["sur_features", "sur_prolong_update", "sur_apply_residual", "sur_residual_target", "sur_fix_mass", "sur_conv3d", "sur_conv3d_cat", "sur_conv3d_pool", "sur_conv3d_wgrad", "sur_pack_weights", "sur_pool2", "sur_pool2_bwd",
+    for n in ["sur_features", "sur_prolong_update", "sur_apply_residual", "sur_residual_target", "sur_fix_mass", "sur_conv3d", "sur_conv3d_cat", "sur_conv3d_pool", "sur_conv3d_wgrad", "sur_conv3d_dgrad_cat", "sur_conv3d_wgrad_cat", "sur_pack_weights", "sur_pool2", "sur_pool2_bwd",
               "sur_upsample2", "sur_upsample2_bwd", "sur_copy_channels", "sur_add_channels",
               "sur_to_bf16", "sur_relu_mask", "sur_mse", "sur_adam", "sur_coarsen",
               "sur_prolong_add", "sur_checks", "sur_checks_noalloc", "sur_pool2_bwd_skip", "sur_upsample2_bwd_mask",
@@ -118,8 +120,8 @@ def sur_conv3d_pool(x, cin, w, bias, cout, grid, relu=0, y_bf16=None, y_pool=Non
 
 
 def conv_cat_fits(grid):
-    """Whether sur_conv3d_cat and sur_conv3d_pool take these (fine-grid)
-    sizes: their tiled kernel's 16 x 4 x 4 point tile."""
+    """Whether the concat and pooling forms of the convolution take these
+    (fine-grid) sizes: their tiled kernel's 16 x 4 x 4 point tile."""
     nx, ny, nz = grid
     return nx % 16 == 0 and ny % 4 == 0 and nz % 4 == 0
 
@@ -133,6 +135,19 @@ def sur_conv3d_wgrad(x, cin, dy, cout, grid, scratch, dw, dbias):
     _ok(load_library().sur_conv3d_wgrad(_p(x), cin, _p(dy), cout, nx, ny, nz, _p(scratch),
                                         scratch.numel(), _p(dw), _p(dbias), _stream()),
         "sur_conv3d_wgrad")
+
+
+def sur_conv3d_dgrad_cat(dy, cin, w, cup, cskip, grid, act, dup_bf16, dskip):
+    nx, ny, nz = grid
+    _ok(load_library().sur_conv3d_dgrad_cat(_p(dy), cin, _p(w), cup, cskip, nx, ny, nz, _p(act),
+                                            _p(dup_bf16), _p(dskip), _stream()), "sur_conv3d_dgrad_cat")
+
+
+def sur_conv3d_wgrad_cat(xc, cc, xf, fc, dy, cout, grid, scratch, dw, dbias):
+    nx, ny, nz = grid
+    _ok(load_library().sur_conv3d_wgrad_cat(_p(xc), cc, _p(xf), fc, _p(dy), cout, nx, ny, nz,
+                                            _p(scratch), scratch.numel(), _p(dw), _p(dbias),
+                                            _stream()), "sur_conv3d_wgrad_cat")
 
 
 def sur_pack_weights(w, cin, cout, wf, wd):
@@ -357,8 +372,10 @@ class UNet:
         for lv in range(self.nlev - 1):
             self.act[f"pool{lv}"] = bf(self.P[lv + 1], self.channels[lv])
         for lv in range(self.nlev - 1):
-            # [upsampled output of level lv + 1, skip of level lv]
-            self.act[f"cat{lv}"] = bf(self.P[lv], self.channels[lv + 1] + self.channels[lv])
+            # [upsampled output of level lv + 1, skip of level lv], where the
+            # convolutions do not read it in place
+            if not self._cat_in_place(lv):
+                self.act[f"cat{lv}"] = bf(self.P[lv], self.channels[lv + 1] + self.channels[lv])
         self.out = f32(self.P[0], NCH)
         sc = 0
         for k, (name, ci, co, relu) in enumerate(self.layers):
@@ -381,13 +398,20 @@ class UNet:
     def n_params(self):
         return sum(w.numel() + b.numel() for w, b in zip(self.w, self.b))
 
+    def _cat_in_place(self, lv):
+        """Whether level lv's decoder reads its concat in place: the kernels'
+        tile divides the grid and their 32-bit element indices reach."""
+        return (conv_cat_fits(self.grids[lv])
+                and self.P[lv] * (self.channels[lv] + self.channels[lv + 1]) < 2**31 - 1)
+
     # -------------------------------------------------------------- forward
     def forward(self, x_bf16, keep_cat=False):
         """x_bf16: int16 tensor [P0, 16] (BF16 bits). Returns the FP32 output
         [P0, 16] (the residual in scaled units). The decoder convolutions read
-        their concat in place (sur_conv3d_cat) unless keep_cat is set (the
-        training step: the weight gradient reads the concat) or the grid does
-        not fit that kernel; both ways give the same bits."""
+        their concat in place (sur_conv3d_cat), and so does the backward pass,
+        unless the grid does not fit those kernels (the concat is then
+        written); both ways give the same bits. keep_cat: a backward pass of
+        this forward will follow (the training step)."""
         k = 0
         h = x_bf16
         hc = NCH
@@ -409,11 +433,10 @@ class UNet:
                 if not pooled:
                     sur_pool2(h, hc, g, self.act[f"pool{lv}"])
                 h = self.act[f"pool{lv}"]
-        self._cat_kept = True
+        self._cat_kept = keep_cat
         for lv in range(self.nlev - 2, -1, -1):
             skip = self.act[f"enc{lv}b"]
-            if not keep_cat and conv_cat_fits(self.grids[lv]):
-                self._cat_kept = False
+            if self._cat_in_place(lv):
                 name, ci, co, relu = self.layers[k]
                 sur_conv3d_cat(h, hc, skip, self.channels[lv], self.wf[k], self.b[k], co,
                                self.grids[lv], relu=1, y_bf16=self.act[name])
@@ -461,7 +484,7 @@ class UNet:
 
     def backward(self, dout):
         """dout: FP32 [P0, 16] gradient at the output. Fills gw, gb. Needs the
-        concat buffers of the last forward (forward with keep_cat=True)."""
+        last forward to have been one with keep_cat=True."""
         if not getattr(self, "_cat_kept", False):
             raise RuntimeError("UNet.backward needs the forward pass run with keep_cat=True")
         torch = self.torch
@@ -475,25 +498,29 @@ class UNet:
                              out_bf16=True)
         dskip = [None] * (nlev - 1)
         for lv in range(0, nlev - 1):
-            for part in "ba":
-                k -= 1
-                name, ci, co, relu = self.layers[k]
-                x_in = self.act[f"cat{lv}"] if part == "a" else self.act[self.layers[k - 1][0]]
-                if part == "b":
-                    mask = self.act[self.layers[k - 1][0]]
-                else:
-                    mask = None  # input is the concat: split below, masks come from its parts
-                dh = self._conv_back(k, x_in, dh, self.grids[lv], mask, out_bf16=part == "b")
-            cup = dh.shape[1] - self.channels[lv]
-            # skip part: gradient w.r.t. enc{lv}b output, channels cup .. of dh
-            # (added and masked later with the encoder's pooled path)
-            dskip[lv] = (dh, dh.shape[1], cup)
-            # upsampled part: gradient w.r.t. the lower level's output, a ReLU
-            # activation (bottom or decoder b of lv + 1); BF16, it only feeds
-            # that layer's backward
+            # upsampled part of the level's input: gradient w.r.t. the lower
+            # level's output, a ReLU activation (bottom or decoder b of lv + 1);
+            # BF16, it only feeds that layer's backward. Skip part: gradient
+            # w.r.t. enc{lv}b output, FP32 (added and masked later with the
+            # encoder's pooled path)
             below = f"enc{lv + 1}b" if lv + 1 == nlev - 1 else f"dec{lv + 1}b"
+            cup, cskip = self.channels[lv + 1], self.channels[lv]
+            k -= 1
+            mask = self.act[self.layers[k - 1][0]]
+            dh = self._conv_back(k, mask, dh, self.grids[lv], mask, out_bf16=True)
+            k -= 1
+            name, ci, co, relu = self.layers[k]
             du = torch.empty((self.P[lv + 1], cup), dtype=torch.int16, device=self.dev)
-            sur_upsample2_bwd_mask(dh, dh.shape[1], 0, cup, self.grids[lv + 1], self.act[below], du)
+            if self._cat_in_place(lv):
+                sur_conv3d_wgrad_cat(self.act[below], cup, self.act[f"enc{lv}b"], cskip, dh, co,
+                                     self.grids[lv], self.scratch, self.gw[k], self.gb[k])
+                ds = torch.empty((self.P[lv], cskip), dtype=torch.float32, device=self.dev)
+                sur_conv3d_dgrad_cat(dh, co, self.wd[k], cup, cskip, self.grids[lv], self.act[below], du, ds)
+                dskip[lv] = (ds, cskip, 0)
+            else:
+                dh = self._conv_back(k, self.act[f"cat{lv}"], dh, self.grids[lv], None)
+                dskip[lv] = (dh, ci, cup)
+                sur_upsample2_bwd_mask(dh, ci, 0, cup, self.grids[lv + 1], self.act[below], du)
             dh = du
         for lv in range(nlev - 1, -1, -1):
             if lv < nlev - 1:

@@ -1,0 +1,79 @@
+"""The decoder's first convolution read and differentiated in place: the weight
+gradient of the concat [up2(xc), xf] without writing it, and the data gradient
+with the upsampling's adjoint in the same pass. Both make the same products and
+sums in the same order as the separate passes, so every bit is compared."""
+import pytest
+
+from gpu_common import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sur():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_12263_amd import surrogate
+    surrogate.load_library()
+    return surrogate
+
+
+def _bf16(shape, seed, scale=1.0):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return (scale * torch.randn(shape, generator=g, device="cuda")).to(torch.bfloat16).view(torch.int16)
+
+
+# (grid, cup, cskip, channels out): one tile; small-grid blocks of one output
+# tile; two-tile blocks of four wavefronts, with one input chunk and with
+# several, odd tile counts, a block of both kinds of channels; eight wavefronts
+SHAPES = [((16, 4, 4), 16, 16, 16), ((32, 32, 32), 64, 48, 48), ((16, 12, 20), 48, 32, 32),
+          ((48, 20, 12), 32, 48, 16), ((80, 60, 28), 48, 32, 32), ((112, 76, 92), 32, 16, 16),
+          ((112, 76, 92), 16, 64, 48), ((64, 64, 64), 48, 32, 32), ((128, 64, 64), 48, 16, 16),
+          ((128, 128, 128), 32, 16, 16)]
+
+
+@pytest.mark.parametrize("grid,cup,cskip,co", SHAPES)
+def test_decoder_backward_in_place_bits(sur, grid, cup, cskip, co):
+    import torch
+    say(f"[decoder] {grid} {cup}+{cskip}->{co}")
+    P, ci = grid[0] * grid[1] * grid[2], cup + cskip
+    half = tuple(n // 2 for n in grid)
+    dy, wd = _bf16((P, co), 1), _bf16((27, ci, co), 2, 0.1)
+    act = torch.relu(_bf16((P // 8, cup), 3).view(torch.bfloat16)).view(torch.int16)
+    dx = torch.empty((P, ci), dtype=torch.float32, device="cuda")
+    sur.sur_conv3d(dy, co, wd, None, ci, grid, flip=1, y_f32=dx)
+    want = torch.zeros((P // 8, cup), dtype=torch.int16, device="cuda")
+    sur.sur_upsample2_bwd_mask(dx, ci, 0, cup, half, act, want)
+    got = torch.full_like(want, 7)
+    skip = torch.full((P, cskip), 7.0, device="cuda")
+    sur.sur_conv3d_dgrad_cat(dy, co, wd, cup, cskip, grid, act, got, skip)
+    assert torch.equal(got, want)
+    assert torch.equal(skip.view(torch.int32), dx[:, cup:].contiguous().view(torch.int32))
+
+    xc, xf = _bf16((P // 8, cup), 4), _bf16((P, cskip), 5)
+    cat = torch.empty((P, ci), dtype=torch.int16, device="cuda")
+    sur.sur_concat_up2(xc, cup, xf, cskip, grid, cat)
+    scr = torch.empty(sur.sur_wgrad_scratch_floats(ci, co, grid), device="cuda")
+    out = []
+    for cat_form in (0, 1):
+        dw, db = torch.zeros((27, co, ci), device="cuda"), torch.zeros(co, device="cuda")
+        if cat_form:
+            sur.sur_conv3d_wgrad_cat(xc, cup, xf, cskip, dy, co, grid, scr, dw, db)
+        else:
+            sur.sur_conv3d_wgrad(cat, ci, dy, co, grid, scr, dw, db)
+        out.append((dw, db))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_decoder_backward_refusals(sur):
+    import torch
+    say("[decoder] sizes and operands that the in-place forms refuse")
+    z = lambda n, dt=torch.int16: torch.zeros(n, dtype=dt, device="cuda")
+    P = 16 * 4 * 4
+    args = dict(dy=z(P * 16), cin=16, w=z(27 * 32 * 16), cup=16, cskip=16, grid=(16, 4, 4),
+                act=z(P // 8 * 16), dup_bf16=z(P // 8 * 16), dskip=z(P * 16, torch.float32))
+    for bad in (dict(grid=(8, 4, 8)), dict(cup=8), dict(act=z(P // 8 * 16 + 1)[1:]), dict(dskip=None)):
+        with pytest.raises(RuntimeError):
+            sur.sur_conv3d_dgrad_cat(**(args | bad))
