@@ -195,7 +195,7 @@ typedef float fl2 __attribute__((ext_vector_type(2)));
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
 constexpr int kTX = 16, kTY = 4, kTZ = 4;
 constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2, kHP = kHX * kHY * kHZ;
-constexpr int kNT = 2;  // 16-channel output tiles per block at most (LDS <= 48.4 KB)
+constexpr int kNT = 2;  // 16-channel output tiles per block, three in some eight-wavefront blocks
 
 static_assert(kHP * 2 > 1280 && kHP * 2 <= 1536, "six 16-byte halo pieces per thread");
 
@@ -454,9 +454,9 @@ constexpr int conv_min_waves() { return WPF ? 2 : (NT == 1 ? 4 : 1); }
 // [P / 8][cc]) and stored as BF16 in yp; the others are stored in FP32 in yf
 // ([P][cout - cc]). Bound by staging and products as the plain form, but the
 // memory traffic is a third: 128^3 16 -> 32 + 16 stores 142 MB and reads 8 of
-// masks where all of dx is 403 MB written and 268 read again; 160 us against
-// 147 + 78 for the two passes (64^3 32 -> 48 + 32: 59 against 51 + 12; 32^3
-// 48 -> 64 + 48: 16.5 against 17 + 8).
+// masks where all of dx is 403 MB written and 268 read again; 98 us against
+// 117 + 78 for the two passes (64^3 32 -> 48 + 32: 46 against 43 + 11; 32^3
+// 48 -> 64 + 48: 16 against 17 + 8).
 template <int NT, bool FLIP, bool POW2, bool CAT, bool WPF, bool POOL, int WV = 4, bool UP = false>
 __global__ void __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(conv_min_waves<NT, WPF>(), 8)))
 conv3d_tiled_kernel(
@@ -525,7 +525,7 @@ conv3d_tiled_kernel(
     const int ls = ntiles == 2 ? 5 : 4;
     auto stage_weights = [&](int cc, int off) {
         for (int c = threadIdx.x; c < 27 * nco * 2; c += NTH) {
-            const int row = c >> 1, sl = row >> ls, o = row & (nco - 1);
+            const int row = c >> 1, sl = ntiles == 3 ? row / 48 : row >> ls, o = row - sl * nco;
             wl[off + 2 * (sl * NCO + o) + (c & 1)] =
                 *(const uint4 *)(w + (slot_tap(sl, FLIP) * cout + cob + o) * cin + cc + 8 * (c & 1));
         }
@@ -592,8 +592,8 @@ conv3d_tiled_kernel(
             for (int mt = 0; mt < 4; ++mt) mrow[nt][mt] = *(const uint2 *)(mask + out_off(x0, y0, z0, mt, nt));
         }
     };
-    // UP: element of channel tile nt of the cell of row pair pr (even lanes and
-    // wavefronts), and the cells' mask words, loaded as the mask rows are
+    // UP: element of channel tile nt of the cell of row pair pr, and the cells'
+    // mask words (of the upper plane's wavefronts), loaded as the mask rows are
     auto cell_off = [&](int x0, int y0, int z0, int pr, int nt) -> uint32_t {
         const uint32_t cell = (uint32_t)(((x0 + r) >> 1) + (G.nx >> 1) * (((y0 >> 1) + pr) + (G.ny >> 1) * ((z0 + wave) >> 1)));
         return cell * (uint32_t)cc + (uint32_t)(cob + nt * 16 + 4 * q);
@@ -615,7 +615,7 @@ conv3d_tiled_kernel(
             if constexpr (PREMASK)
                 if (mask && chunk + 1 == nchunk) load_mask(k);
             if constexpr (UP) {
-                if (chunk + 1 == nchunk && !(wave & 1)) {
+                if (chunk + 1 == nchunk && (wave & 1)) {
                     int x0, y0, z0;
                     tile_origin<POW2, TZ>(G, (int)blockIdx.x + k * (int)gridDim.x, x0, y0, z0);
 #pragma unroll
@@ -650,6 +650,8 @@ conv3d_tiled_kernel(
             __builtin_amdgcn_s_setprio(1);
             if (NT == 1 || ntiles == NT)
                 conv_kloop<NT, NT, NT == 1>(tile, wl, baseA0, baseA1, baseA2, baseA3, bB, second, acc);
+            else if (NT == 3 && ntiles == 2)
+                conv_kloop<2, NT, false>(tile, wl, baseA0, baseA1, baseA2, baseA3, bB, second, acc);
             else
                 conv_kloop<1, NT, false>(tile, wl, baseA0, baseA1, baseA2, baseA3, bB, second, acc);
             __builtin_amdgcn_s_setprio(0);
@@ -670,53 +672,52 @@ conv3d_tiled_kernel(
                 }
             }
             if (nup == 0) continue;  // the same for the whole block
-            // as the pooling below: the x pair in the next lane, the y pair in
-            // the lane's next row, the z pair in the next wavefront, which
-            // hands its four values over in LDS (the halo, free once every
-            // wavefront is here: at most 4 KB per pair of wavefronts and tile)
-            float *ex = (float *)tile;
+            // the x pair is in the next lane, the y pair in the lane's next
+            // row; the wavefront of the lower plane hands the sum of its four
+            // values over in LDS (the halo, free once every wavefront is
+            // here: 512 B per pair of wavefronts, tile and row pair) and that
+            // of the upper plane adds its own in order
+            f4 *ex = (f4 *)tile;
             const int pair = wave >> 1;
-            auto slot = [&](int nt, int pr) {
-                return (f4 *)(ex + ((((pair * NT + nt) * 2 + pr) * 32) + (q * 8 + (r >> 1))) * 16);
+            auto slot = [&](int nt, int pr) -> f4 & {
+                return ex[((pair * NT + nt) * 2 + pr) * 32 + q * 8 + (r >> 1)];
+            };
+            auto add_plane = [&](f4 sum, int nt, int pr) {
+                f4 n0, n1;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    n0[j] = __shfl_xor(acc[2 * pr][nt][j], 1, 64);
+                    n1[j] = __shfl_xor(acc[2 * pr + 1][nt][j], 1, 64);
+                }
+                return (((sum + acc[2 * pr][nt]) + n0) + acc[2 * pr + 1][nt]) + n1;
             };
             __syncthreads();
-            f4 sum[NT][2];
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                if (nt >= nup) break;
-#pragma unroll
-                for (int pr = 0; pr < 2; ++pr) {
-                    f4 n0, n1;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        n0[j] = __shfl_xor(acc[2 * pr][nt][j], 1, 64);
-                        n1[j] = __shfl_xor(acc[2 * pr + 1][nt][j], 1, 64);
-                    }
-                    if ((wave & 1) && !(r & 1)) {
-                        f4 *e = slot(nt, pr);
-                        e[0] = acc[2 * pr][nt];
-                        e[1] = n0;
-                        e[2] = acc[2 * pr + 1][nt];
-                        e[3] = n1;
-                    }
-                    sum[nt][pr] = (((f4{0.f, 0.f, 0.f, 0.f} + acc[2 * pr][nt]) + n0) + acc[2 * pr + 1][nt]) + n1;
-                }
-            }
-            __syncthreads();
-            if (!(wave & 1) && !(r & 1)) {
+            if (!(wave & 1)) {
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     if (nt >= nup) break;
 #pragma unroll
                     for (int pr = 0; pr < 2; ++pr) {
-                        const f4 *e = slot(nt, pr);
-                        const f4 s = (((sum[nt][pr] + e[0]) + e[1]) + e[2]) + e[3];
+                        const f4 s = add_plane(f4{0.f, 0.f, 0.f, 0.f}, nt, pr);
+                        if (!(r & 1)) slot(nt, pr) = s;
+                    }
+                }
+            }
+            __syncthreads();
+            if (wave & 1) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (nt >= nup) break;
+#pragma unroll
+                    for (int pr = 0; pr < 2; ++pr) {
+                        const f4 s = add_plane(slot(nt, pr), nt, pr);
                         const uint32_t mw[2] = {um[nt][pr].x, um[nt][pr].y};
                         uint32_t h[4];
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             h[j] = f2bf(bf2f((uint16_t)(mw[j >> 1] >> (16 * (j & 1)))) > 0.f ? s[j] : 0.f);
-                        *(uint2 *)(yp + cell_off(x0, y0, z0, pr, nt)) = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+                        if (!(r & 1))
+                            *(uint2 *)(yp + cell_off(x0, y0, z0, pr, nt)) = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
                     }
                 }
             }
@@ -2514,7 +2515,7 @@ int device_cus() {
 
 // Wavefronts per block of conv3d_tiled_kernel: eight on 16 x 4 x 8 tiles
 // for one output tile and at least four such tiles per CU; for two output
-// tiles (one block per CU) where the tiles make whole rounds of the CUs
+// or three tiles (one block per CU) where the tiles make whole rounds of the CUs
 // and at most eight input chunks (up to four keep their weights in LDS);
 // else four (SUR_CONV_WV=4 keeps four; for comparisons only, both give the
 // same bits).
@@ -2530,8 +2531,7 @@ int conv_waves(int cin, int cout, int nx, int ny, int nz, int cus) {
 // channels of the upsampled coarse tensor first, then cin - cc of x);
 // y_pool != NULL the pooled output as well (forward form, BF16 output; with
 // one output tile only on eight wavefronts or in the small-grid form); up the
-// data gradient with the upsampling's adjoint (two output tiles or the
-// small-grid form).
+// data gradient with the upsampling's adjoint (at least two output tiles).
 void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const void *w,
                        const float *bias, int cout, int nx, int ny, int nz, bool flip, int relu,
                        const void *mask, void *y_bf16, float *y_f32, void *y_pool, hipStream_t st,
@@ -2543,6 +2543,23 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
     const int cus = device_cus();
     const int nwv = conv_waves(cin, cout, nx, ny, nz, cus);
     const long tiles = P / (kTX * kTY * nwv);
+    // three output tiles per eight-wavefront block where that makes fewer
+    // columns of blocks (3, 5, 6, 7, ... tiles): the halo is staged and its
+    // fragments read once for three tiles, and no column has half the work
+    // of another. Not where the weights of all chunks fit the LDS beside the
+    // halo for two tiles but not for three. Two tiles -> three, forward, data
+    // gradient with a mask, us: 128^3 16 -> 48 142 -> 91, 172 -> 131; 48 -> 48
+    // 322 -> 232, 348 -> 265; 80 -> 48 680 -> 520, 723 -> 564; 64^3 48 -> 80
+    // 73 -> 58, 88 -> 66; 64 -> 48 at 128^3, left out, 428 -> 426, 450 -> 454.
+    // (SUR_CONV_NT3=0 keeps two; for comparisons only, both give the same bits)
+    const char *n3 = std::getenv("SUR_CONV_NT3");
+    const int no = cout / 16;
+    if (nwv == 8 && !xc && (up || !y_pool) && (no + 2) / 3 < (no + 1) / 2 &&
+        (conv_tiled_lds(3, 8, cin / 16) <= 160 * 1024 || conv_tiled_lds(kNT, 8, cin / 16) > 160 * 1024) &&
+        !(n3 && *n3 == '0')) {
+        nt = 3;
+        ncb = (no + 2) / 3;
+    }
     long nblk = std::max(1L, std::min(tiles, (long)conv_blocks(nt, cin / 16, cus, nwv) / ncb));
     // grids of fewer two-tile blocks than two per CU (the 32^3 and 16^3
     // levels, a block's one item sets the time): one output tile per block
@@ -2608,6 +2625,9 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
 #define SUR_CONV_WV8N2(FL, P2, CT, PL)                                                         \
     hipLaunchKernelGGL((conv3d_tiled_kernel<kNT, FL, P2, CT, false, PL, 8>), grid, dim3(512), lds, st, \
                        xb, cin, xcb, cc, wb, bias, cout, G, relu, mb, yb, y_f32, yp)
+#define SUR_CONV_WV8N3(FL, P2)                                                                 \
+    hipLaunchKernelGGL((conv3d_tiled_kernel<3, FL, P2, false, false, false, 8>), grid, dim3(512), lds, st, \
+                       xb, cin, xcb, cc, wb, bias, cout, G, relu, mb, yb, y_f32, yp)
 #define SUR_CONV_UP(NTV, WP, WVV)                                                                       \
     do {                                                                                              \
         if (pow2)                                                                                     \
@@ -2620,10 +2640,17 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
                                y_f32, yp);                                                            \
     } while (0)
     if (up) {
-        if (nwv == 8) SUR_CONV_UP(kNT, false, 8);
+        if (nwv == 8 && nt == 3) SUR_CONV_UP(3, false, 8);
+        else if (nwv == 8) SUR_CONV_UP(kNT, false, 8);
         else if (splitn) SUR_CONV_UP(1, true, 4);
         else if (wpf) SUR_CONV_UP(kNT, true, 4);
         else SUR_CONV_UP(kNT, false, 4);
+    } else if (nwv == 8 && nt == 3) {
+        if (flip) {
+            if (pow2) SUR_CONV_WV8N3(true, true); else SUR_CONV_WV8N3(true, false);
+        } else {
+            if (pow2) SUR_CONV_WV8N3(false, true); else SUR_CONV_WV8N3(false, false);
+        }
     } else if (nwv == 8 && nt == kNT) {
         if (pool1) {
             if (pow2) SUR_CONV_WV8N2(false, true, false, true); else SUR_CONV_WV8N2(false, false, false, true);
@@ -2664,6 +2691,7 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
 #undef SUR_CONV_UP
 #undef SUR_CONV_WV8
 #undef SUR_CONV_WV8N2
+#undef SUR_CONV_WV8N3
 #undef SUR_CONV_NT2
 #undef SUR_CONV_POW2
 #undef SUR_CONV_LAUNCH

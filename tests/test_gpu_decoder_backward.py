@@ -77,3 +77,27 @@ def test_decoder_backward_refusals(sur):
     for bad in (dict(grid=(8, 4, 8)), dict(cup=8), dict(act=z(P // 8 * 16 + 1)[1:]), dict(dskip=None)):
         with pytest.raises(RuntimeError):
             sur.sur_conv3d_dgrad_cat(**(args | bad))
+
+
+# three output tiles per block: 3, 5 and 7 tiles (the last block has 3, 2 and
+# 1), one input chunk and several, weights resident and staged per item, sizes
+# that are powers of two and not
+@pytest.mark.parametrize("grid,cin,cout", [((64, 64, 64), 16, 48), ((48, 64, 256), 16, 80),
+                                           ((48, 64, 256), 48, 48), ((64, 64, 64), 32, 112),
+                                           ((64, 64, 64), 80, 80)])
+def test_three_output_tiles_bits_of_two(sur, grid, cin, cout, monkeypatch):
+    import torch
+    say(f"[conv] {grid} {cin}->{cout} three output tiles per block")
+    P = grid[0] * grid[1] * grid[2]
+    x, w, m = _bf16((P, cin), 1), _bf16((27, cout, cin), 2, 0.1), _bf16((P, cout), 3)
+    b = _bf16(cout, 4).view(torch.bfloat16).float()
+    out = []
+    for form in "01":
+        monkeypatch.setenv("SUR_CONV_NT3", form)
+        y = [torch.zeros((P, cout), dtype=torch.int16, device="cuda") for _ in range(2)]
+        f = torch.zeros((P, cout), device="cuda")
+        sur.sur_conv3d(x, cin, w, b, cout, grid, relu=1, y_bf16=y[0], y_f32=f)
+        sur.sur_conv3d(x, cin, w, None, cout, grid, flip=1, mask=m, y_bf16=y[1])
+        out.append(y + [f.view(torch.int32)])
+    for a, c in zip(*out):
+        assert int((a != 0).sum()) > 0 and torch.equal(a, c)
