@@ -1457,6 +1457,315 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
     }
 }
 
+// A staged tile of wgrad_cols_kernel, in bytes: 32 B (16 channels) per
+// point, rows of kHX (+ 1 unused) or kTX (+ 1) points, planes of kHY rows or
+// kTY (+ 2 unused points), one such box per 16 channels. The reads below take
+// 4 consecutive y of two planes z and z + 2 in a half-wavefront, 32 B each:
+// with these strides they fall on all 64 banks.
+constexpr int kWcRow = 32 * (kHX + 1), kWcPl = kHY * kWcRow;
+constexpr int kWcX = kHZ * kWcPl + 64;
+constexpr int kWcDRow = 32 * (kTX + 1), kWcDPl = kTY * kWcDRow + 64;
+constexpr int kWcD = kTZ * kWcDPl;
+constexpr bool wc_banks(int row, int pl) {
+    int used = 0;
+    for (int y = 0; y < 4; ++y)
+        for (int z = 0; z < 4; z += 2) used |= 1 << ((y * row + z * pl) / 32 % 8);
+    return used == 255;
+}
+static_assert(wc_banks(kWcRow, kWcPl) && wc_banks(kWcDRow, kWcDPl), "each 32 B on its own banks");
+
+typedef short s4 __attribute__((ext_vector_type(4)));
+typedef short s8 __attribute__((ext_vector_type(8)));
+#define SUR_LDS __attribute__((address_space(3)))
+
+// Fragment (operand of the 16x16x32 MFMA, channel lane & 15) of two columns:
+// the transposing reads give the lane four points each, those whose 8-byte
+// quarters the 16 lanes of its quarter address: here the four y of a plane,
+// and of the plane behind it pl bytes further.
+__device__ __forceinline__ bf8 wgrad_cols_frag(const SUR_LDS char *p, int pl) {
+    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SUR_LDS s4 *)(p));
+    const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SUR_LDS s4 *)(p + pl));
+    return __builtin_bit_cast(bf8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// The K steps of one tile for wavefront w4 of a chunk's four. Step j takes the
+// tile's columns x = j and j + 8, 16 points (y, z) each; the halo's columns
+// hx = j + dx + 1 and + 8 under the tap are then a fragment that the three dx
+// of neighbouring steps share, so ten fragments serve a tap row's 24 products,
+// and no product needs a shift of its operands. The wavefront takes the tap
+// rows (dy, dz) w4 and w4 + 4 in every step and row 8 in the steps 2 w4 and
+// 2 w4 + 1 (so the nine rows are spread evenly; the four parts of row 8's sums
+// are added at the end). ap: the lane's place in the staged output gradient at
+// step 0, xp the same in the staged halo of the three rows (of row 8 at step
+// 2 w4). Accumulator 3 rr + d takes the tap dx = d - 1 of row rr, 9 (with bias,
+// in row 8's steps) dY times ones: each column holds the channel sums. mid()
+// runs half way.
+template <int MT, class F>
+__device__ __forceinline__ void wgrad_cols_steps(const SUR_LDS char *ap, const SUR_LDS char *const (&xp)[3],
+                                            int w4, bool bias, f4 (&acc)[10][MT], F &&mid) {
+    bf8 h[2][10];
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr) {
+        h[rr][0] = wgrad_cols_frag(xp[rr], kWcPl);
+        h[rr][1] = wgrad_cols_frag(xp[rr] + 32, kWcPl);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (j == 4) mid();
+        bf8 a[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) a[mt] = wgrad_cols_frag(ap + mt * kWcD + 32 * j, kWcDPl);
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr) {
+            h[rr][j + 2] = wgrad_cols_frag(xp[rr] + 32 * (j + 2), kWcPl);
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[3 * rr + d][mt] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], h[rr][j + d], acc[3 * rr + d][mt], 0, 0, 0);
+        }
+    }
+    bf8 g[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g[k] = wgrad_cols_frag(xp[2] + 32 * k, kWcPl);
+    const bf8 ones = __builtin_bit_cast(bf8, uint4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const bf8 a = wgrad_cols_frag(ap + mt * kWcD + 64 * w4 + 32 * k, kWcDPl);
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                acc[6 + d][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, g[k + d], acc[6 + d][mt], 0, 0, 0);
+            if (bias) acc[9][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[9][mt], 0, 0, 0);
+        }
+    }
+}
+
+// Weight gradient on large grids of whole tiles with at least two input chunks
+// and at most 32 output channels: as wgrad_tiled_kernel, with NG chunks of a
+// tile in one block of 4 NG wavefronts (wavefronts 4 g .. 4 g + 3 take chunk g),
+// one block per CU. The tile is staged as it lies in memory (16 channels of a
+// point together), each point's chunks read by neighbouring lanes, where blocks
+// of one chunk read 32 B of every point's row; transposing LDS reads make the
+// fragments; a K step takes two whole columns of the tile, so that the three dx
+// taps share fragments and no operand is shifted or shuffled in registers (61
+// instead of 220 vector instructions beside the MFMAs per chunk and tile); and
+// two LDS buffers let the staging run beside the products. The nine tap rows
+// are spread evenly over a chunk's four wavefronts. Bound by the reads of the
+// halos (a copy that makes no products takes 83% of the time at 128^3 48 -> 16).
+// Against the other kernel, with the reductions, us: 128^3 48 -> 16 146 -> 104,
+// 32 -> 16 96 -> 78, 80 -> 16 258 -> 182, 32 -> 32 134 -> 115; 64^3 80 -> 32
+// 56 -> 51. One chunk per block, more output channels and small grids gain
+// nothing (128^3 16 -> 16 51 and 53, 64^3 48 -> 48 48 and 92 us).
+// part and bpart as there; CAT: the input is the concat [up2(xc), x].
+template <int MT, int NG, bool CAT>
+__global__ void __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(NG, NG)))
+wgrad_cols_kernel(const uint16_t *__restrict__ x, int cin,
+                  const uint16_t *__restrict__ dy, int cout,
+                  int nx, int ny, int nz,
+                  float *__restrict__ part,
+                  float *__restrict__ bpart, const uint16_t *__restrict__ xc, int ccat) {
+    constexpr int kAcc = 10;  // two tap rows, a part of the ninth, the bias
+    constexpr int kTh = 256 * NG;
+    constexpr int kBuf = NG * kWcX + MT * kWcD;
+    __shared__ __attribute__((aligned(16))) char xht[2 * kBuf];
+    char *const dyt = xht + NG * kWcX;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    // chunks of this block, this wavefront's, its part of it
+    const int cb = blockIdx.y * NG * 16, nc = min(NG, (cin - cb) >> 4);
+    const int cg = __builtin_amdgcn_readfirstlane(wave >> 2), w4 = __builtin_amdgcn_readfirstlane(wave & 3);
+    const int ntx = nx / kTX, nty = ny / kTY, ntile = ntx * nty * (nz / kTZ);
+    f4 acc[kAcc][MT];
+#pragma unroll
+    for (int u = 0; u < kAcc; ++u)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[u][mt] = f4{0.f, 0.f, 0.f, 0.f};
+    // bias gradient (blocks of the first input chunk): dY times ones
+    const bool do_bias = bpart != nullptr && blockIdx.y == 0 && cg == 0;
+    // the lane's places in the staged dY and halo at the first K step: its
+    // quarter q takes the column (q >> 1) of the step's two and the planes
+    // 2 (q & 1) and + 1; the lane addresses 8 B of point y = r >> 2
+    const SUR_LDS char *const ap = (const SUR_LDS char *)dyt + (2 * (q & 1)) * kWcDPl + (r >> 2) * kWcDRow + 256 * (q >> 1) + 8 * (r & 3);
+    const SUR_LDS char *xq[3];
+#pragma unroll
+    for (int rr = 0; rr < 3; ++rr) {
+        const int rid = rr < 2 ? w4 + 4 * rr : 8;
+        xq[rr] = (const SUR_LDS char *)xht + cg * kWcX + (rid / 3 + 2 * (q & 1)) * kWcPl + (rid % 3 + (r >> 2)) * kWcRow +
+                 256 * (q >> 1) + 8 * (r & 3) + (rr == 2 ? 64 * w4 : 0);
+    }
+    // the forward's XCD slabs of tile rows where the rows and the grid allow
+    // (tile % 8 is then the block's XCD for every input chunk, so the chunks
+    // of a tile and its neighbours read their halos through one L2)
+    const int nys = nty % 8 == 0 && gridDim.x % 8 == 0 ? nty / 8 : 0;
+    auto origin = [&](int tile, int &x0, int &y0, int &z0) {
+        int bx, by, bz;
+        if (nys) {
+            const int u = tile >> 3, rest = u / ntx;
+            bx = u - rest * ntx;
+            by = (tile & 7) * nys + rest % nys;
+            bz = rest / nys;
+        } else {
+            const int rest = tile / ntx;
+            bx = tile - rest * ntx;
+            by = rest % nty;
+            bz = rest / nty;
+        }
+        x0 = bx * kTX;
+        y0 = by * kTY;
+        z0 = bz * kTZ;
+    };
+    // a tile's global reads, held in registers until its staging, in pieces of 16 B (8 channels of a point):
+    // neighbouring lanes take the pieces of a point, then the next point's
+    constexpr int kXIt = (kHP * 2 * NG + kTh - 1) / kTh, kDIt = (512 * MT + kTh - 1) / kTh;
+    const int xp = threadIdx.x % (2 * NG);  // the thread's piece, the same in every iteration
+    // the thread's halo point of iteration it; false for none
+    auto xpiece = [&](int it, int &hx, int &hy, int &hz) {
+        const int p = (int)threadIdx.x / (2 * NG) + 128 * it, row = p / kHX;
+        hx = p - row * kHX;
+        hz = row / kHY;
+        hy = row - hz * kHY;
+        return p < kHP && (xp >> 1) < nc;
+    };
+    auto dpiece = [](int it, int &px, int &py, int &pz, int &oc) {
+        const int c = threadIdx.x + kTh * it, p = c / (2 * MT);
+        px = p & 15;
+        py = (p >> 4) & 3;
+        pz = p >> 6;
+        oc = c % (2 * MT);
+        return c < 512 * MT;
+    };
+    // the thread's input as a tensor of nxc x nyc x nzc points: with CAT its
+    // chunk's source, the coarse tensor's points being half the fine ones'
+    const int xc0 = cb + 8 * xp;
+    const bool up = CAT && xc0 < ccat;
+    const int sh = up ? 1 : 0, nxc = nx >> sh, nyc = ny >> sh, nzc = nz >> sh;
+    const int xst = CAT ? (up ? ccat : cin - ccat) : cin;
+    const uint16_t *const xb = CAT ? (up ? xc : x) : x;
+    const int xch = CAT && !up ? xc0 - ccat : xc0;
+    // bytes from the tile's first point to the pieces' (unsigned, modulo 2^32)
+    uint32_t xoff[kXIt], doff[kDIt];
+#pragma unroll
+    for (int it = 0; it < kXIt; ++it) {
+        int hx, hy, hz;
+        xpiece(it, hx, hy, hz);
+        xoff[it] = 2u * (uint32_t)((((hx - 1) >> sh) + nxc * (((hy - 1) >> sh) + nyc * ((hz - 1) >> sh))) * xst + xch);
+    }
+#pragma unroll
+    for (int it = 0; it < kDIt; ++it) {
+        int px, py, pz, oc;
+        dpiece(it, px, py, pz, oc);
+        doff[it] = 2u * (uint32_t)((px + nx * (py + ny * pz)) * cout + 8 * oc);
+    }
+    auto at = [](const uint16_t *b, uint32_t bytes) { return *(const uint4 *)((const char *)b + bytes); };
+    uint4 xv[kXIt], dv[kDIt];
+    auto fetch = [&](int tile) {
+        int x0, y0, z0;
+        origin(tile, x0, y0, z0);
+        const bool edge = x0 == 0 || y0 == 0 || z0 == 0 || x0 + kTX == nx || y0 + kTY == ny || z0 + kTZ == nz;
+        const uint32_t base = 2u * (uint32_t)(((x0 >> sh) + nxc * ((y0 >> sh) + nyc * (z0 >> sh))) * xst);
+        const uint32_t X = 2u * nxc * xst, Y = X * nyc, Z = Y * nzc;  // a period, in bytes
+#pragma unroll
+        for (int it = 0; it < kXIt; ++it) {
+            int hx, hy, hz;
+            if (!xpiece(it, hx, hy, hz)) continue;
+            uint32_t o = base + xoff[it];
+            if (edge) {
+                if (hx == 0 && x0 == 0) o += X;
+                if (hx == kHX - 1 && x0 + kTX == nx) o -= X;
+                if (hy == 0 && y0 == 0) o += Y;
+                if (hy == kHY - 1 && y0 + kTY == ny) o -= Y;
+                if (hz == 0 && z0 == 0) o += Z;
+                if (hz == kHZ - 1 && z0 + kTZ == nz) o -= Z;
+            }
+            xv[it] = at(xb, o);
+        }
+        const uint32_t dbase = 2u * (uint32_t)((x0 + nx * (y0 + ny * z0)) * cout);
+#pragma unroll
+        for (int it = 0; it < kDIt; ++it) {
+            int px, py, pz, oc;
+            if (dpiece(it, px, py, pz, oc)) dv[it] = at(dy, dbase + doff[it]);
+        }
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int it = 0; it < kXIt; ++it) {
+            int hx, hy, hz;
+            if (xpiece(it, hx, hy, hz))
+                *(uint4 *)(xht + buf + (xp >> 1) * kWcX + hz * kWcPl + hy * kWcRow + 32 * hx + 16 * (xp & 1)) = xv[it];
+        }
+#pragma unroll
+        for (int it = 0; it < kDIt; ++it) {
+            int px, py, pz, oc;
+            if (dpiece(it, px, py, pz, oc))
+                *(uint4 *)(dyt + buf + (oc >> 1) * kWcD + pz * kWcDPl + py * kWcDRow + 32 * px + 16 * (oc & 1)) = dv[it];
+        }
+    };
+    // Two buffers: half way through a tile's MFMAs the next tile, read since
+    // the middle of the previous one, goes to the other buffer and the reads of
+    // the one after it go out. The barrier at the end of a tile covers both.
+    const int step = gridDim.x;
+    int buf = 0;
+    if ((int)blockIdx.x < ntile) {
+        fetch(blockIdx.x);
+        stage(0);
+    }
+    if ((int)blockIdx.x + step < ntile) fetch((int)blockIdx.x + step);
+    for (int tile = blockIdx.x; tile < ntile; tile += step) {
+        __syncthreads();
+        auto mid = [&]() __attribute__((always_inline)) {
+            if (tile + step < ntile) stage(kBuf - buf);
+            if (tile + 2 * step < ntile) fetch(tile + 2 * step);
+        };
+        if (cg < nc) {
+            const SUR_LDS char *const xb3[3] = {xq[0] + buf, xq[1] + buf, xq[2] + buf};
+            wgrad_cols_steps<MT>(ap + buf, xb3, w4, do_bias, acc, mid);
+        } else {
+            mid();
+        }
+        buf = kBuf - buf;
+    }
+    // D[m = 4 q + j][n = r] of tap t, M tile mt: dW[t][mt 16 + 4 q + j][.. + r]
+    auto put = [&](int t, int mt, const f4 &v) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            part[(((long)blockIdx.x * 27 + t) * cout + mt * 16 + 4 * q + j) * cin + cb + 16 * cg + r] = v[j];
+    };
+    if (cg < nc) {
+#pragma unroll
+        for (int u = 0; u < 6; ++u)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) put(u % 3 + 3 * (w4 + 4 * (u / 3)), mt, acc[u][mt]);
+    }
+    // row 8 and the bias: the parts of a chunk's four wavefronts meet in LDS
+    // and are added in their order, one tap at a time
+    f4 *const ex = (f4 *)xht + cg * 4 * MT * 64;
+    float *const exb = (float *)(xht + NG * 4 * MT * 64 * 16);  // [wave][16 MT]
+    static_assert(NG * 4 * MT * 64 * 16 + 4 * 16 * MT * 4 <= kBuf, "fits the staged tile's place");
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        __syncthreads();
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) ex[(w4 * MT + mt) * 64 + lane] = acc[6 + d][mt];
+        if (d == 0 && do_bias && r == 0)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) exb[w4 * 16 * MT + mt * 16 + 4 * q + j] = acc[9][mt][j];
+        __syncthreads();
+        if (w4 < MT && cg < nc) {
+            const f4 v = ((ex[w4 * 64 + lane] + ex[(MT + w4) * 64 + lane]) + ex[(2 * MT + w4) * 64 + lane]) +
+                        ex[(3 * MT + w4) * 64 + lane];
+            put(24 + d, w4, v);
+        }
+        if (d == 0 && bpart && blockIdx.y == 0 && threadIdx.x < 16 * MT)
+            bpart[(long)blockIdx.x * cout + threadIdx.x] =
+                ((exb[threadIdx.x] + exb[16 * MT + threadIdx.x]) + exb[32 * MT + threadIdx.x]) + exb[48 * MT + threadIdx.x];
+    }
+}
+
 // dw[e] = sum over chunks of part[chunk][e] (fixed order).
 // A block sums 32 consecutive elements; its 8 thread groups take the chunks
 // g, g + 8, g + 16, ... in order and are combined in group order (fixed
@@ -2502,6 +2811,27 @@ bool conv_tiled_ok(const void *x, int cin, const void *w, int cout, int nx, int 
            ((uintptr_t)x & 15) == 0 && ((uintptr_t)w & 15) == 0;
 }
 
+// Partial sums that sur_wgrad_scratch_floats provides for.
+long wgrad_rows_max(int cin, long P) { return std::max(wgrad_chunks(P), wgrad_tiled_blocks(cin, P)); }
+
+// Input chunks per block of wgrad_cols_kernel and its blocks (*nblk) per group
+// of chunks, or 0 for wgrad_tiled_kernel: where a block here has fewer than
+// twelve tiles (64^3 48 -> 16, 6 tiles: 29.4 us there, 30.5 here; 80 -> 16,
+// 10 tiles: 43 and 44; 80 -> 32, 12 tiles: 60 and 58; 96^3 32 -> 16, 13 tiles:
+// 51 and 44), and for 48 -> 32, whose two unequal groups of chunks need fewer,
+// longer sums (128^3: relative error 7.2e-7 against 7.1e-7). Three chunks per
+// block where the registers allow (one output tile) and they do not make pairs.
+int wgrad_group(int cin, int cout, bool rag, long tiles, long rows, int cus, long *nblk) {
+    const int no = cin / 16;
+    if (rag || no < 2 || cout > 32 || (cout == 32 && no == 3) || cus <= 0) return 0;
+    const int ng = cout == 16 && no != 2 && no != 4 ? 3 : 2;
+    long nb = std::min((long)cus / ((no + ng - 1) / ng), rows);
+    if (nb >= 8) nb = nb / 8 * 8;
+    if (nb < 1 || tiles < 12 * nb) return 0;
+    *nblk = nb;
+    return ng;
+}
+
 // Compute units of the current device (0 if the runtime cannot say).
 int device_cus() {
     int dev = 0, cus = 0;
@@ -2908,7 +3238,24 @@ int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void
         // and 7.1e-8); in between the plain form is as exact and faster
         const long tiles = rag_tiles(nx, ny, nz);
         const uint16_t *xcb = (const uint16_t *)xc;
-        if (xc) {
+        const int ng = wgrad_group(cin, cout, rag, tiles, wgrad_rows_max(cin, P), device_cus(), &nch);
+        if (ng) {
+            const dim3 gg((unsigned)nch, (unsigned)((cin / 16 + ng - 1) / ng));
+            bp = dbias ? scratch + nch * n : nullptr;
+#define SUR_WG_COLS(M, N)                                                                              \
+    do {                                                                                               \
+        if (xc)                                                                                        \
+            hipLaunchKernelGGL((wgrad_cols_kernel<M, N, true>), gg, dim3(256 * N), 0, s, xb, cin, db, cout, \
+                               nx, ny, nz, scratch, bp, xcb, cc);                                      \
+        else                                                                                           \
+            hipLaunchKernelGGL((wgrad_cols_kernel<M, N, false>), gg, dim3(256 * N), 0, s, xb, cin, db, cout, \
+                               nx, ny, nz, scratch, bp, xcb, cc);                                      \
+    } while (0)
+            if (cout == 32) SUR_WG_COLS(2, 2);
+            else if (ng == 2) SUR_WG_COLS(1, 2);
+            else SUR_WG_COLS(1, 3);
+#undef SUR_WG_COLS
+        } else if (xc) {
 #define SUR_WG_CAT(M)                                                                              \
     hipLaunchKernelGGL((wgrad_tiled_kernel<M, false, false, true>), grid, dim3(256), 0, s, xb, cin, \
                        db, cout, nx, ny, nz, scratch, bp, xcb, cc)

@@ -79,6 +79,43 @@ def test_decoder_backward_refusals(sur):
             sur.sur_conv3d_dgrad_cat(**(args | bad))
 
 
+# weight gradients of grouped input chunks: groups of two and three, a last
+# group of one and of two chunks, one and two output tiles, sizes that are powers
+# of two and not, a tile count that the blocks do not divide; each with and
+# without the concat read in place
+@pytest.mark.parametrize("grid,cup,cskip,co", [((96, 96, 96), 16, 16, 16), ((96, 80, 100), 32, 16, 16),
+                                               ((96, 96, 96), 48, 16, 16), ((64, 80, 100), 48, 32, 32),
+                                               ((96, 96, 96), 16, 16, 32), ((96, 96, 96), 64, 16, 16)])
+def test_grouped_weight_gradient(sur, grid, cup, cskip, co):
+    """Against FP64 products: the sums of P products of unit normals in FP32
+    blocks of at most 3 P / 256 tiles err by about sqrt(adds) 2^-25 of a sum;
+    2e-6 is above twice the largest error that the sizes allow. The concat
+    form makes the same sums: every bit."""
+    import torch
+    say(f"[wgrad] {grid} {cup}+{cskip}->{co} grouped chunks")
+    P, ci = grid[0] * grid[1] * grid[2], cup + cskip
+    dy, xc, xf = _bf16((P, co), 1), _bf16((P // 8, cup), 4), _bf16((P, cskip), 5)
+    cat = torch.empty((P, ci), dtype=torch.int16, device="cuda")
+    sur.sur_concat_up2(xc, cup, xf, cskip, grid, cat)
+    scr = torch.full((sur.sur_wgrad_scratch_floats(ci, co, grid),), float("nan"), device="cuda")
+    out = []
+    for cat_form in (0, 1):
+        dw, db = torch.zeros((27, co, ci), device="cuda"), torch.zeros(co, device="cuda")
+        if cat_form:
+            sur.sur_conv3d_wgrad_cat(xc, cup, xf, cskip, dy, co, grid, scr, dw, db)
+        else:
+            sur.sur_conv3d_wgrad(cat, ci, dy, co, grid, scr, dw, db)
+        out.append((dw, db))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    X = cat.view(torch.bfloat16).double().view(grid[2], grid[1], grid[0], ci)
+    D = dy.view(torch.bfloat16).double()
+    for t in range(27):
+        ref = D.t() @ torch.roll(X, (1 - t // 9, 1 - t // 3 % 3, 1 - t % 3), (0, 1, 2)).reshape(-1, ci)
+        assert float((out[0][0][t] - ref).norm() / ref.norm()) < 2e-6, t
+    ref = D.sum(0)
+    assert float((out[0][1] - ref).norm() / ref.norm()) < 2e-6
+
+
 # three output tiles per block: 3, 5 and 7 tiles (the last block has 3, 2 and
 # 1), one input chunk and several, weights resident and staged per item, sizes
 # that are powers of two and not
