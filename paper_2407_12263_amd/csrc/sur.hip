@@ -1807,59 +1807,61 @@ __global__ void __launch_bounds__(256) sum_chunks2_kernel(const float *__restric
     else sum_chunks_block(part_b, rows_b, n_b, out_b, b - nblk_a);
 }
 
-// Per-block partial sums of dy over points for each channel: thread
-// (tid % cout) owns a channel, (tid / cout) a strided slice of the block's points.
-// First pass of the same fixed-order sum for wide rows (n a multiple of 4):
-// block (x, k) sums rows [k L, min((k + 1) L, nrows)) of elements
-// [128 x, 128 x + 128), four per thread with 16-byte loads, in 8 interleaved
-// groups combined in order, into row k of mid; sum_chunks_kernel then adds
-// the rows of mid in order. More blocks and wider loads keep more bytes in
-// flight than one pass over all rows.
+// The same fixed-order sum for wide rows (n a multiple of 4) with more bytes in
+// flight: a block sums 32 elements, four per thread with 16-byte loads, over
+// kSumSeg segments of L rows, each in 8 interleaved groups combined in order;
+// the segments are then added in order. Bound by the read of the partials just
+// written (128^3 16 -> 16: 21 MB). One launch where there was one for the
+// segments and one for their sum, and none apart for the bias: with the
+// products, us, 32^3 32 -> 48 22.4 -> 20.3, 16^3 48 -> 64 17.2 -> 14.9, 64^3
+// 32 -> 32 31.8 -> 29.7.
 constexpr int kSumSeg = 8;
-// Blocks with blockIdx.x >= nblk_a take a second array (part_b, n4_b, mid_b)
+// Blocks with blockIdx.x >= nblk_a take a second array (part_b, n4_b, out_b)
 // with the same rows and segments (the bias partials beside the weights').
-__global__ void __launch_bounds__(256) sum_rows4_kernel(const float4 *__restrict__ part,
-                                                        long nrows, long n4, int L,
-                                                        float4 *__restrict__ mid, long nblk_a,
-                                                        const float4 *__restrict__ part_b,
-                                                        long n4_b, float4 *__restrict__ mid_b) {
-    __shared__ float4 red[8][32];
-    const int l = threadIdx.x & 31, g = threadIdx.x >> 5;
+__global__ void __launch_bounds__(512) sum_rows4_kernel(const float4 *__restrict__ part,
+                                                         long nrows, long n4, int L,
+                                                         float *__restrict__ out, long nblk_a,
+                                                         const float4 *__restrict__ part_b,
+                                                         long n4_b, float *__restrict__ out_b) {
+    __shared__ float4 red[8 * kSumSeg][8];
+    const int l = threadIdx.x & 7, sg = threadIdx.x >> 3;
     long bx = blockIdx.x;
     if (bx >= nblk_a) {
         bx -= nblk_a;
         part = part_b;
         n4 = n4_b;
-        mid = mid_b;
+        out = out_b;
     }
-    const long e = bx * 32 + l;
-    const long r0 = (long)blockIdx.y * L, r1 = r0 + L < nrows ? r0 + L : nrows;
+    const long e = bx * 8 + l;
+    const long r0 = (long)(sg >> 3) * L, r1 = r0 + L < nrows ? r0 + L : nrows;
+    auto add = [](float4 a, const float4 &b) { return float4{a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w}; };
     float4 acc = float4{0.f, 0.f, 0.f, 0.f};
     if (e < n4) {
 #pragma unroll 4
-        for (long r = r0 + g; r < r1; r += 8) {
-            const float4 v = part[r * n4 + e];
-            acc.x += v.x;
-            acc.y += v.y;
-            acc.z += v.z;
-            acc.w += v.w;
-        }
+        for (long r = r0 + (sg & 7); r < r1; r += 8) acc = add(acc, part[r * n4 + e]);
     }
-    red[g][l] = acc;
+    red[sg][l] = acc;
     __syncthreads();
-    if (g == 0 && e < n4) {
+    if (sg < kSumSeg) {
+        float4 t = red[8 * sg][l];
+#pragma unroll
+        for (int k = 1; k < 8; ++k) t = add(t, red[8 * sg + k][l]);
+        red[8 * sg][l] = t;
+    }
+    __syncthreads();
+    if (sg == 0 && e < n4) {
         float4 t = red[0][l];
 #pragma unroll
-        for (int k = 1; k < 8; ++k) {
-            t.x += red[k][l].x;
-            t.y += red[k][l].y;
-            t.z += red[k][l].z;
-            t.w += red[k][l].w;
-        }
-        mid[(long)blockIdx.y * n4 + e] = t;
+        for (int k = 1; k < kSumSeg; ++k) t = add(t, red[8 * k][l]);
+        out[4 * e] = t.x;
+        out[4 * e + 1] = t.y;
+        out[4 * e + 2] = t.z;
+        out[4 * e + 3] = t.w;
     }
 }
 
+// Per-block partial sums of dy over points for each channel: thread
+// (tid % cout) owns a channel, (tid / cout) a strided slice of the block's points.
 __global__ void __launch_bounds__(256) bias_partial_kernel(const uint16_t *__restrict__ dy, int cout,
                                                            long P, long chunk,
                                                            float *__restrict__ part) {
@@ -3295,48 +3297,27 @@ int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void
             default: hipLaunchKernelGGL(wgrad_kernel<4>, grid, dim3(256), 0, s, xb, cin, db, cout, nx, ny, nz, kWgradChunk, scratch); break;
         }
     }
-    {
-        // two passes: kSumSeg row segments into mid, then mid's rows in order
-        // (n = 27 cin cout is a multiple of 4; the partial rows are 16-byte
-        // aligned when the scratch is)
-        const long bparts = std::max((long)grid1(P, 1024).x, wgrad_tiled_blocks(cin, P));
-        float *mid = scratch + nch * n + bparts * (long)cout;
-        if (aligned16(scratch) && aligned16(mid) && n % 4 == 0 && nch >= 2 * kSumSeg) {
-            const long n4 = n / 4;
-            const int L = (int)((nch + kSumSeg - 1) / kSumSeg);
-            const long na4 = (n4 + 31) / 32;
-            // the bias partials (rows of cout, 16-byte aligned: cout % 16 == 0)
-            // take the same two passes, in the same launches
-            float *mid_b = mid + kSumSeg * n;
-            const bool with_b = tiled_bp && aligned16(tiled_bp);
-            const long nb4 = with_b ? ((long)cout / 4 + 31) / 32 : 0;
-            const dim3 g1((unsigned)(na4 + nb4), (unsigned)kSumSeg);
-            hipLaunchKernelGGL(sum_rows4_kernel, g1, dim3(256), 0, s, (const float4 *)scratch, nch,
-                               n4, L, (float4 *)mid, na4, (const float4 *)tiled_bp,
-                               (long)cout / 4, (float4 *)mid_b);
-            if (with_b) {  // dw's and dbias's last passes in one launch
-                const long na = grid1(n, 32).x;
-                hipLaunchKernelGGL(sum_chunks2_kernel, dim3((unsigned)(na + grid1(cout, 32).x)),
-                                   dim3(256), 0, s, (const float *)mid, (long)kSumSeg, n, dw, na,
-                                   (const float *)mid_b, (long)kSumSeg, (long)cout, dbias);
-                tiled_bp = nullptr;
-            } else {
-                hipLaunchKernelGGL(sum_chunks_kernel, grid1(n, 32), dim3(256), 0, s,
-                                   (const float *)mid, (long)kSumSeg, n, dw);
-            }
-        } else {
-            hipLaunchKernelGGL(sum_chunks_kernel, grid1(n, 32), dim3(256), 0, s,
-                               (const float *)scratch, nch, n, dw);
-        }
-    }
-    if (tiled_bp)
-        hipLaunchKernelGGL(sum_chunks_kernel, grid1(cout, 32), dim3(256), 0, s,
-                           (const float *)tiled_bp, nch, (long)cout, dbias);
-    if (dbias && !bias_done) {
-        const long nb = grid1(P, 1024).x;
-        float *bp = scratch + nch * n;
+    // the bias partials, where wanted: one row per block of the tiled kernels,
+    // or per 1024 points
+    float *bp = dbias ? (bias_done ? tiled_bp : scratch + nch * n) : nullptr;
+    const long nb = bias_done ? nch : (long)grid1(P, 1024).x;
+    if (bp && !bias_done)
         hipLaunchKernelGGL(bias_partial_kernel, dim3((unsigned)nb), dim3(256), 0, s, db, cout, P, 1024L, bp);
-        hipLaunchKernelGGL(sum_chunks_kernel, grid1(cout, 32), dim3(256), 0, s, (const float *)bp, nb, (long)cout, dbias);
+    long bcols = bp ? cout : 0;
+    if (aligned16(scratch) && nch >= 2 * kSumSeg) {
+        // n = 27 cin cout and cout are multiples of 4, so every row is aligned
+        const long na = (n / 4 + 7) / 8;
+        if (bp && nb != nch) {
+            hipLaunchKernelGGL(sum_chunks_kernel, grid1(cout, 32), dim3(256), 0, s, (const float *)bp, nb, (long)cout, dbias);
+            bcols = 0;
+        }
+        hipLaunchKernelGGL(sum_rows4_kernel, dim3((unsigned)(na + (bcols / 4 + 7) / 8)), dim3(512), 0, s,
+                           (const float4 *)scratch, nch, n / 4, (int)((nch + kSumSeg - 1) / kSumSeg), dw, na,
+                           (const float4 *)bp, bcols / 4, dbias);
+    } else {
+        const long na = grid1(n, 32).x;
+        hipLaunchKernelGGL(sum_chunks2_kernel, dim3((unsigned)(na + (bcols + 31) / 32)), dim3(256), 0, s,
+                           (const float *)scratch, nch, n, dw, na, (const float *)bp, nb, bcols, dbias);
     }
     return launched();
 }
