@@ -2226,18 +2226,28 @@ __global__ void __launch_bounds__(256) mse_kernel(const float *__restrict__ pred
         // 16 stored channels: four lanes per point, lane j of a quad taking
         // channels 4j .. 4j + 3, so a wavefront's 16-byte accesses cover 16
         // consecutive points' rows; the block's 256 points in four passes
-        // (the same arithmetic per channel as below)
+        // (the same arithmetic per channel as below), whose loads go out
+        // together (bound by the memory: 128^3, 335 MB, 77 -> 70 us)
         const float inv = 1.0f / (float)((double)P * cu);
         const int j = threadIdx.x & 3;
+        const long p0 = (long)blockIdx.x * blockDim.x + (threadIdx.x >> 2);
+        const bool used = 4 * j < cu;
+        float4 a[4], b[4];
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            const long pp = (long)blockIdx.x * blockDim.x + it * 64 + (threadIdx.x >> 2);
+            const long pp = p0 + it * 64 < P ? p0 + it * 64 : P - 1;  // a point past the end loads the last
+            if (used) {
+                a[it] = ((const float4 *)(pred + pp * 16))[j];
+                b[it] = ((const float4 *)(tgt + pp * 16))[j];
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const long pp = p0 + it * 64;
             if (pp < P) {
                 float gg[4] = {0.f, 0.f, 0.f, 0.f};
-                if (4 * j < cu) {
-                    const float4 a = ((const float4 *)(pred + pp * 16))[j];
-                    const float4 b = ((const float4 *)(tgt + pp * 16))[j];
-                    const float pa[4] = {a.x, a.y, a.z, a.w}, tb[4] = {b.x, b.y, b.z, b.w};
+                if (used) {
+                    const float pa[4] = {a[it].x, a[it].y, a[it].z, a[it].w}, tb[4] = {b[it].x, b[it].y, b[it].z, b[it].w};
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int ch = 4 * j + k;
