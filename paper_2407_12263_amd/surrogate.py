@@ -90,7 +90,12 @@ def _p(t):
 
 
 def _stream():
+    # the current stream's handle without a Stream object around it: 0.3 us of
+    # host time instead of 3 in every call, where the small networks' time is
+    # the host's (a training step at 16^3, 600 -> 450 us)
     import torch
+    if torch.cuda.is_initialized():
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
