@@ -167,6 +167,11 @@ int lbm_step(lbm_ctx *ctx, int64_t n);
  * (any may be NULL); dtype 0 = double, 1 = float. Asynchronous. */
 int lbm_fields(lbm_ctx *ctx, void *d_phi, void *d_u, void *d_p, int32_t dtype);
 
+/* lbm_fields with every value stored twice, the second time to d_phi2, d_u2 and
+ * d_p2 (any may be NULL, each needs its first): a copy without reading back. */
+int lbm_fields_twice(lbm_ctx *ctx, void *d_phi, void *d_u, void *d_p, void *d_phi2, void *d_u2, void *d_p2,
+                     int32_t dtype);
+
 /* Computes the diagnostics at t; d_phi_ref (device FP64, N) may be NULL.
  * Blocks until the result is on the host. */
 int lbm_diagnostics(lbm_ctx *ctx, const double *d_phi_ref, lbm_diag *out);

@@ -95,9 +95,7 @@ class Coupler:
     def save_base(self):
         """Keeps the solver's FP64 fields: the base the coarse change is
         added to (and a copy to go back to if the solver rejects the result)."""
-        lbm.lbm_fields(self.solver.ctx, self.phi64, self.u64, self.p64, 0)
-        for a, b in zip(self.backup, (self.phi64, self.u64, self.p64)):
-            a.copy_(b)
+        lbm.lbm_fields_twice(self.solver.ctx, (self.phi64, self.u64, self.p64), self.backup, 0)
 
     def save_base_restore(self):
         for a, b in zip(self.backup, (self.phi64, self.u64, self.p64)):

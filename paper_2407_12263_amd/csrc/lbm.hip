@@ -827,13 +827,22 @@ int lbm_step(lbm_ctx *c, int64_t n) {
 }
 
 int lbm_fields(lbm_ctx *c, void *d_phi, void *d_u, void *d_p, int32_t dtype) {
+    return lbm_fields_twice(c, d_phi, d_u, d_p, nullptr, nullptr, nullptr, dtype);
+}
+
+int lbm_fields_twice(lbm_ctx *c, void *d_phi, void *d_u, void *d_p, void *d_phi2, void *d_u2, void *d_p2,
+                     int32_t dtype) {
     clear_stale_error();
-    if (!c || (dtype != 0 && dtype != 1)) return LBM_EINVAL;
+    if (!c || (dtype != 0 && dtype != 1) || (d_phi2 && !d_phi) || (d_u2 && !d_u) || (d_p2 && !d_p))
+        return LBM_EINVAL;
     if (c->status == LBM_EDEVICE) return LBM_ESTATE;
     FieldOut o{};
     o.phi = d_phi;
     o.u = d_u;
     o.p = d_p;
+    o.phi2 = d_phi2;
+    o.u2 = d_u2;
+    o.p2 = d_p2;
     o.dtype = dtype;
     moments_any(c, o);
     return check_launch(c);

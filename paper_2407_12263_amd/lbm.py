@@ -95,6 +95,7 @@ def load_library(path: str | None = None):
                              C.POINTER(vp)]
     lib.lbm_step.argtypes = [vp, C.c_int64]
     lib.lbm_fields.argtypes = [vp, vp, vp, vp, C.c_int32]
+    lib.lbm_fields_twice.argtypes = [vp, vp, vp, vp, vp, vp, vp, C.c_int32]
     lib.lbm_diagnostics.argtypes = [vp, vp, C.POINTER(LbmDiag)]
     lib.lbm_get_pdfs.argtypes = [vp, vp, vp]
     lib.lbm_set_pdfs.argtypes = [vp, vp, vp]
@@ -196,6 +197,13 @@ def lbm_step(ctx, n: int):
 def lbm_fields(ctx, phi=None, u=None, p=None, dtype: int = 0):
     ptr = lambda t: None if t is None else C.c_void_p(t.data_ptr())
     _check(load_library().lbm_fields(ctx, ptr(phi), ptr(u), ptr(p), int(dtype)), "lbm_fields")
+
+
+def lbm_fields_twice(ctx, fields, again, dtype: int = 0):
+    """lbm_fields into (phi, u, p) ``fields`` and, in the same pass, ``again``."""
+    _check(load_library().lbm_fields_twice(
+        ctx, *(None if t is None else C.c_void_p(t.data_ptr()) for t in (*fields, *again)),
+        int(dtype)), "lbm_fields_twice")
 
 
 def lbm_diagnostics(ctx, phi_ref=None) -> dict:

@@ -149,3 +149,25 @@ def test_coarsen_row_stores_equal_the_general_kernel(sur):
         sur.sur_coarsen(phi, u, p, grid, scale, f, b)
         got.append((f, b))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("prec,dtype,walls", [("fp64", 0, 0), ("fp16", 0, 1), ("bf16", 1, 0), ("fp32", 1, 1)])
+def test_fields_stored_twice(prec, dtype, walls):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    say(f"[state] fields stored twice {prec} dtype {dtype}")
+    phi, u, p = _fields(37, 21, 6, 2)
+    s = lbm.Solver(dict(nx=37, ny=21, nz=6, precision=prec, wall=(0, walls, 0), rho2=0.5), phi, u, p)
+    s.step(3)
+    new = lambda: [torch.full(a.shape, -7.0, dtype=(torch.float64, torch.float32)[dtype], device="cuda")
+                   for a in (phi, u, p)]
+    want, a, b, c = new(), new(), new(), new()
+    lbm.lbm_fields(s.ctx, *want, dtype)
+    lbm.lbm_fields_twice(s.ctx, a, b, dtype)
+    lbm.lbm_fields_twice(s.ctx, c, (None, c[1].clone(), None), dtype)
+    with pytest.raises(lbm.LbmError):
+        lbm.lbm_fields_twice(s.ctx, (a[0], None, a[2]), b, dtype)
+    torch.cuda.synchronize()
+    for w, x, y, z in zip(want, a, b, c):
+        assert torch.equal(w, x) and torch.equal(w, y) and torch.equal(w, z)
