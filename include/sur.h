@@ -93,8 +93,15 @@ int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, i
                      int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
                      float *dbias, void *stream);
 
+/* The same with the sums in an order that stays as it is over versions of this
+ * library, for training runs that have to repeat; slower where the sizes are no
+ * multiples of 16 x 4 x 4 and on large grids with several input chunks. */
+int sur_conv3d_wgrad_ordered(const void *x, int32_t cin, const void *dy, int32_t cout, int32_t nx,
+                             int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
+                             float *dbias, void *stream);
+
 /* The same of the concat [up2(xc), xf] (xc BF16 [P/8][cc], xf [P][fc]) read in
- * place, bitwise sur_conv3d_wgrad of the written concat with cin = cc + fc.
+ * place, bitwise sur_conv3d_wgrad_ordered of the written concat, cin = cc + fc.
  * Needs nx a multiple of 16, ny and nz of 4, at least 256 points, cout at most
  * 64 and 16-byte aligned xc, xf and dy; otherwise SUR_EINVAL. */
 int sur_conv3d_wgrad_cat(const void *xc, int32_t cc, const void *xf, int32_t fc, const void *dy, int32_t cout,

@@ -1559,14 +1559,14 @@ __device__ __forceinline__ void wgrad_cols_steps(const SUR_LDS char *ap, const S
 // 32 -> 16 96 -> 78, 80 -> 16 258 -> 182, 32 -> 32 134 -> 115; 64^3 80 -> 32
 // 56 -> 51. One chunk per block, more output channels and small grids gain
 // nothing (128^3 16 -> 16 51 and 53, 64^3 48 -> 48 48 and 92 us).
-// part and bpart as there; CAT: the input is the concat [up2(xc), x].
-template <int MT, int NG, bool CAT>
+// part and bpart as there.
+template <int MT, int NG>
 __global__ void __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(NG, NG)))
 wgrad_cols_kernel(const uint16_t *__restrict__ x, int cin,
                   const uint16_t *__restrict__ dy, int cout,
                   int nx, int ny, int nz,
                   float *__restrict__ part,
-                  float *__restrict__ bpart, const uint16_t *__restrict__ xc, int ccat) {
+                  float *__restrict__ bpart) {
     constexpr int kAcc = 10;  // two tap rows, a part of the ninth, the bias
     constexpr int kTh = 256 * NG;
     constexpr int kBuf = NG * kWcX + MT * kWcD;
@@ -1637,21 +1637,13 @@ wgrad_cols_kernel(const uint16_t *__restrict__ x, int cin,
         oc = c % (2 * MT);
         return c < 512 * MT;
     };
-    // the thread's input as a tensor of nxc x nyc x nzc points: with CAT its
-    // chunk's source, the coarse tensor's points being half the fine ones'
-    const int xc0 = cb + 8 * xp;
-    const bool up = CAT && xc0 < ccat;
-    const int sh = up ? 1 : 0, nxc = nx >> sh, nyc = ny >> sh, nzc = nz >> sh;
-    const int xst = CAT ? (up ? ccat : cin - ccat) : cin;
-    const uint16_t *const xb = CAT ? (up ? xc : x) : x;
-    const int xch = CAT && !up ? xc0 - ccat : xc0;
     // bytes from the tile's first point to the pieces' (unsigned, modulo 2^32)
     uint32_t xoff[kXIt], doff[kDIt];
 #pragma unroll
     for (int it = 0; it < kXIt; ++it) {
         int hx, hy, hz;
         xpiece(it, hx, hy, hz);
-        xoff[it] = 2u * (uint32_t)((((hx - 1) >> sh) + nxc * (((hy - 1) >> sh) + nyc * ((hz - 1) >> sh))) * xst + xch);
+        xoff[it] = 2u * (uint32_t)((hx - 1 + nx * (hy - 1 + ny * (hz - 1))) * cin + cb + 8 * xp);
     }
 #pragma unroll
     for (int it = 0; it < kDIt; ++it) {
@@ -1665,8 +1657,8 @@ wgrad_cols_kernel(const uint16_t *__restrict__ x, int cin,
         int x0, y0, z0;
         origin(tile, x0, y0, z0);
         const bool edge = x0 == 0 || y0 == 0 || z0 == 0 || x0 + kTX == nx || y0 + kTY == ny || z0 + kTZ == nz;
-        const uint32_t base = 2u * (uint32_t)(((x0 >> sh) + nxc * ((y0 >> sh) + nyc * (z0 >> sh))) * xst);
-        const uint32_t X = 2u * nxc * xst, Y = X * nyc, Z = Y * nzc;  // a period, in bytes
+        const uint32_t base = 2u * (uint32_t)((x0 + nx * (y0 + ny * z0)) * cin);
+        const uint32_t X = 2u * nx * cin, Y = X * ny, Z = Y * nz;  // a period, in bytes
 #pragma unroll
         for (int it = 0; it < kXIt; ++it) {
             int hx, hy, hz;
@@ -1680,7 +1672,7 @@ wgrad_cols_kernel(const uint16_t *__restrict__ x, int cin,
                 if (hz == 0 && z0 == 0) o += Z;
                 if (hz == kHZ - 1 && z0 + kTZ == nz) o -= Z;
             }
-            xv[it] = at(xb, o);
+            xv[it] = at(x, o);
         }
         const uint32_t dbase = 2u * (uint32_t)((x0 + nx * (y0 + ny * z0)) * cout);
 #pragma unroll
@@ -3221,10 +3213,16 @@ size_t sur_wgrad_scratch_floats(int32_t cin, int32_t cout, int32_t nx, int32_t n
 namespace {
 
 // sur_conv3d_wgrad; xc != NULL selects the concat form (cc channels of the
-// upsampled coarse tensor first, then cin - cc of x).
+// upsampled coarse tensor first, then cin - cc of x). ordered: the sums in one
+// order for all time (wgrad_tiled_kernel on whole tiles, the per-tap product
+// elsewhere), which the training step keeps: Adam divides a gradient by its own
+// size, so that a last-bit difference of a gradient near zero moves a weight
+// by up to the learning rate, and a BF16 weight that rounds the other way the
+// next forward pass by 1e-3 (two steps on 112 x 48 x 112, 72 x 56 x 40 and
+// 24 x 40 x 32 grids: 7 of 24 seeds, with errors against FP64 sums no larger).
 int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void *dy, int32_t cout,
               int32_t nx, int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
-              float *dbias, void *stream) {
+              float *dbias, void *stream, bool ordered) {
     clear_stale_error();
     if (!x || !dy || !scratch || !dw || cin <= 0 || cout <= 0 || cin % 16 || cout % 16 ||
         cout > 64 || !dims_ok(nx, ny, nz))
@@ -3237,7 +3235,7 @@ int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void
     const long n = 27L * cin * cout;
     bool bias_done = false;
     float *tiled_bp = nullptr;  // bias partials of the tiled kernel, summed with dw's last pass
-    if (wgrad_tiled_ok(x, cin, dy, cout, nx, ny, nz)) {
+    if (wgrad_tiled_ok(x, cin, dy, cout, nx, ny, nz) && !(ordered && (nx % kTX || ny % kTY || nz % kTZ))) {
         nch = wgrad_tiled_blocks(cin, P);
         const dim3 grid((unsigned)nch, (unsigned)(cin / 16));
         // the bias partials follow the weight partials: one per block
@@ -3250,19 +3248,13 @@ int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void
         // and 7.1e-8); in between the plain form is as exact and faster
         const long tiles = rag_tiles(nx, ny, nz);
         const uint16_t *xcb = (const uint16_t *)xc;
-        const int ng = wgrad_group(cin, cout, rag, tiles, wgrad_rows_max(cin, P), device_cus(), &nch);
+        const int ng = ordered ? 0 : wgrad_group(cin, cout, rag, tiles, wgrad_rows_max(cin, P), device_cus(), &nch);
         if (ng) {
             const dim3 gg((unsigned)nch, (unsigned)((cin / 16 + ng - 1) / ng));
             bp = dbias ? scratch + nch * n : nullptr;
 #define SUR_WG_COLS(M, N)                                                                              \
-    do {                                                                                               \
-        if (xc)                                                                                        \
-            hipLaunchKernelGGL((wgrad_cols_kernel<M, N, true>), gg, dim3(256 * N), 0, s, xb, cin, db, cout, \
-                               nx, ny, nz, scratch, bp, xcb, cc);                                      \
-        else                                                                                           \
-            hipLaunchKernelGGL((wgrad_cols_kernel<M, N, false>), gg, dim3(256 * N), 0, s, xb, cin, db, cout, \
-                               nx, ny, nz, scratch, bp, xcb, cc);                                      \
-    } while (0)
+    hipLaunchKernelGGL((wgrad_cols_kernel<M, N>), gg, dim3(256 * N), 0, s, xb, cin, db, cout, nx, ny, nz, \
+                       scratch, bp)
             if (cout == 32) SUR_WG_COLS(2, 2);
             else if (ng == 2) SUR_WG_COLS(1, 2);
             else SUR_WG_COLS(1, 3);
@@ -3339,7 +3331,13 @@ extern "C" {
 int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, int32_t nx,
                      int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
                      float *dbias, void *stream) {
-    return wgrad_run(x, cin, nullptr, 0, dy, cout, nx, ny, nz, scratch, scratch_floats, dw, dbias, stream);
+    return wgrad_run(x, cin, nullptr, 0, dy, cout, nx, ny, nz, scratch, scratch_floats, dw, dbias, stream, false);
+}
+
+int sur_conv3d_wgrad_ordered(const void *x, int32_t cin, const void *dy, int32_t cout, int32_t nx,
+                             int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
+                             float *dbias, void *stream) {
+    return wgrad_run(x, cin, nullptr, 0, dy, cout, nx, ny, nz, scratch, scratch_floats, dw, dbias, stream, true);
 }
 
 int sur_conv3d_wgrad_cat(const void *xc, int32_t cc, const void *xf, int32_t fc, const void *dy, int32_t cout,
@@ -3349,7 +3347,7 @@ int sur_conv3d_wgrad_cat(const void *xc, int32_t cc, const void *xf, int32_t fc,
     if (!xc || !xf || !dy || cc <= 0 || fc <= 0 || cc % 16 || fc % 16 || cout <= 0 || !dims_ok(nx, ny, nz) ||
         nx % kTX || ny % kTY || nz % kTZ || !aligned16(xc) || !wgrad_tiled_ok(xf, cc + fc, dy, cout, nx, ny, nz))
         return SUR_EINVAL;
-    return wgrad_run(xf, cc + fc, xc, cc, dy, cout, nx, ny, nz, scratch, scratch_floats, dw, dbias, stream);
+    return wgrad_run(xf, cc + fc, xc, cc, dy, cout, nx, ny, nz, scratch, scratch_floats, dw, dbias, stream, true);
 }
 
 int sur_pack_weights_all(const float *w, int32_t nlayers, const int64_t *w_off, const int32_t *cin,

@@ -47,6 +47,7 @@ def load_library(path: str | None = None):
     lib.sur_wgrad_scratch_floats.restype = sz
     lib.sur_conv3d_wgrad.argtypes = [vp, i32, vp, i32, i32, i32, i32, vp, sz, vp, vp, vp]
     lib.sur_conv3d_dgrad_cat.argtypes = [vp, i32, vp, i32, i32, i32, i32, i32, vp, vp, vp, vp]
+    lib.sur_conv3d_wgrad_ordered.argtypes = lib.sur_conv3d_wgrad.argtypes
     lib.sur_conv3d_wgrad_cat.argtypes = [vp, i32, vp, i32, vp, i32, i32, i32, i32, vp, sz, vp, vp, vp]
     lib.sur_pack_weights.argtypes = [vp, i32, i32, vp, vp, vp]
     lib.sur_pool2.argtypes = [vp, i32, i32, i32, i32, vp, vp]
@@ -74,7 +75,7 @@ def load_library(path: str | None = None):
     lib.sur_prolong_update_scratch_doubles.argtypes = [i32, i32, i32]
     lib.sur_prolong_update_scratch_doubles.restype = sz
     lib.sur_prolong_update.argtypes = [vp, vp, i32, i32, i32, vp, C.c_double, vp, vp, vp, vp, vp, vp]
-    for n in ["sur_features", "sur_prolong_update", "sur_apply_residual", "sur_residual_target", "sur_fix_mass", "sur_conv3d", "sur_conv3d_cat", "sur_conv3d_pool", "sur_conv3d_wgrad", "sur_conv3d_dgrad_cat", "sur_conv3d_wgrad_cat", "sur_pack_weights", "sur_pool2", "sur_pool2_bwd",
+    for n in ["sur_features", "sur_prolong_update", "sur_apply_residual", "sur_residual_target", "sur_fix_mass", "sur_conv3d", "sur_conv3d_cat", "sur_conv3d_pool", "sur_conv3d_wgrad", "sur_conv3d_wgrad_ordered", "sur_conv3d_dgrad_cat", "sur_conv3d_wgrad_cat", "sur_pack_weights", "sur_pool2", "sur_pool2_bwd",
               "sur_upsample2", "sur_upsample2_bwd", "sur_copy_channels", "sur_add_channels",
               "sur_to_bf16", "sur_relu_mask", "sur_mse", "sur_adam", "sur_coarsen",
               "sur_prolong_add", "sur_checks", "sur_checks_noalloc", "sur_pool2_bwd_skip", "sur_upsample2_bwd_mask",
@@ -140,6 +141,13 @@ def sur_conv3d_wgrad(x, cin, dy, cout, grid, scratch, dw, dbias):
     _ok(load_library().sur_conv3d_wgrad(_p(x), cin, _p(dy), cout, nx, ny, nz, _p(scratch),
                                         scratch.numel(), _p(dw), _p(dbias), _stream()),
         "sur_conv3d_wgrad")
+
+
+def sur_conv3d_wgrad_ordered(x, cin, dy, cout, grid, scratch, dw, dbias):
+    nx, ny, nz = grid
+    _ok(load_library().sur_conv3d_wgrad_ordered(_p(x), cin, _p(dy), cout, nx, ny, nz, _p(scratch),
+                                                scratch.numel(), _p(dw), _p(dbias), _stream()),
+        "sur_conv3d_wgrad_ordered")
 
 
 def sur_conv3d_dgrad_cat(dy, cin, w, cup, cskip, grid, act, dup_bf16, dskip):
@@ -478,7 +486,7 @@ class UNet:
         else:
             dyb = torch.empty((P, co), dtype=torch.int16, device=self.dev)
             sur_to_bf16(dy, dyb)
-        sur_conv3d_wgrad(x_in, ci, dyb, co, grid, self.scratch, self.gw[k], self.gb[k])
+        sur_conv3d_wgrad_ordered(x_in, ci, dyb, co, grid, self.scratch, self.gw[k], self.gb[k])
         if out_bf16:
             dx = torch.empty((P, ci), dtype=torch.int16, device=self.dev)
             sur_conv3d(dyb, co, self.wd[k], None, ci, grid, flip=1, relu=0, mask=mask, y_bf16=dx)

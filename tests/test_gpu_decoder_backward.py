@@ -62,7 +62,7 @@ def test_decoder_backward_in_place_bits(sur, grid, cup, cskip, co):
         if cat_form:
             sur.sur_conv3d_wgrad_cat(xc, cup, xf, cskip, dy, co, grid, scr, dw, db)
         else:
-            sur.sur_conv3d_wgrad(cat, ci, dy, co, grid, scr, dw, db)
+            sur.sur_conv3d_wgrad_ordered(cat, ci, dy, co, grid, scr, dw, db)
         out.append((dw, db))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
@@ -81,39 +81,27 @@ def test_decoder_backward_refusals(sur):
 
 # weight gradients of grouped input chunks: groups of two and three, a last
 # group of one and of two chunks, one and two output tiles, sizes that are powers
-# of two and not, a tile count that the blocks do not divide; each with and
-# without the concat read in place
-@pytest.mark.parametrize("grid,cup,cskip,co", [((96, 96, 96), 16, 16, 16), ((96, 80, 100), 32, 16, 16),
-                                               ((96, 96, 96), 48, 16, 16), ((64, 80, 100), 48, 32, 32),
-                                               ((96, 96, 96), 16, 16, 32), ((96, 96, 96), 64, 16, 16)])
-def test_grouped_weight_gradient(sur, grid, cup, cskip, co):
+# of two and not, a tile count that the blocks do not divide
+@pytest.mark.parametrize("grid,ci,co", [((96, 96, 96), 32, 16), ((96, 80, 100), 48, 16), ((96, 96, 96), 64, 16),
+                                        ((64, 80, 100), 80, 32), ((96, 96, 96), 32, 32), ((96, 96, 96), 80, 16)])
+def test_grouped_weight_gradient(sur, grid, ci, co):
     """Against FP64 products: the sums of P products of unit normals in FP32
     blocks of at most 3 P / 256 tiles err by about sqrt(adds) 2^-25 of a sum;
-    2e-6 is above twice the largest error that the sizes allow. The concat
-    form makes the same sums: every bit."""
+    2e-6 is above twice the largest error that the sizes allow."""
     import torch
-    say(f"[wgrad] {grid} {cup}+{cskip}->{co} grouped chunks")
-    P, ci = grid[0] * grid[1] * grid[2], cup + cskip
-    dy, xc, xf = _bf16((P, co), 1), _bf16((P // 8, cup), 4), _bf16((P, cskip), 5)
-    cat = torch.empty((P, ci), dtype=torch.int16, device="cuda")
-    sur.sur_concat_up2(xc, cup, xf, cskip, grid, cat)
+    say(f"[wgrad] {grid} {ci}->{co} grouped chunks")
+    P = grid[0] * grid[1] * grid[2]
+    dy, x = _bf16((P, co), 1), _bf16((P, ci), 4)
     scr = torch.full((sur.sur_wgrad_scratch_floats(ci, co, grid),), float("nan"), device="cuda")
-    out = []
-    for cat_form in (0, 1):
-        dw, db = torch.zeros((27, co, ci), device="cuda"), torch.zeros(co, device="cuda")
-        if cat_form:
-            sur.sur_conv3d_wgrad_cat(xc, cup, xf, cskip, dy, co, grid, scr, dw, db)
-        else:
-            sur.sur_conv3d_wgrad(cat, ci, dy, co, grid, scr, dw, db)
-        out.append((dw, db))
-    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
-    X = cat.view(torch.bfloat16).double().view(grid[2], grid[1], grid[0], ci)
+    dw, db = torch.zeros((27, co, ci), device="cuda"), torch.zeros(co, device="cuda")
+    sur.sur_conv3d_wgrad(x, ci, dy, co, grid, scr, dw, db)
+    X = x.view(torch.bfloat16).double().view(grid[2], grid[1], grid[0], ci)
     D = dy.view(torch.bfloat16).double()
     for t in range(27):
         ref = D.t() @ torch.roll(X, (1 - t // 9, 1 - t // 3 % 3, 1 - t % 3), (0, 1, 2)).reshape(-1, ci)
-        assert float((out[0][0][t] - ref).norm() / ref.norm()) < 2e-6, t
+        assert float((dw[t] - ref).norm() / ref.norm()) < 2e-6, t
     ref = D.sum(0)
-    assert float((out[0][1] - ref).norm() / ref.norm()) < 2e-6
+    assert float((db - ref).norm() / ref.norm()) < 2e-6
 
 
 # three output tiles per block: 3, 5 and 7 tiles (the last block has 3, 2 and
@@ -138,3 +126,23 @@ def test_three_output_tiles_bits_of_two(sur, grid, cin, cout, monkeypatch):
         out.append(y + [f.view(torch.int32)])
     for a, c in zip(*out):
         assert int((a != 0).sum()) > 0 and torch.equal(a, c)
+
+
+# the ordered sums: those of the plain form where both take the tiled kernel;
+# sizes off the tile and grids where the plain form groups chunks, against FP64
+@pytest.mark.parametrize("grid,ci,co,same", [((16, 16, 32), 16, 32, True), ((32, 32, 32), 48, 48, True),
+                                             ((12, 10, 14), 48, 64, False), ((40, 24, 56), 80, 32, False),
+                                             ((96, 96, 96), 32, 16, False)])
+def test_ordered_weight_gradient(sur, grid, ci, co, same):
+    import torch
+    say(f"[wgrad] {grid} {ci}->{co} ordered")
+    P = grid[0] * grid[1] * grid[2]
+    dy, x = _bf16((P, co), 1), _bf16((P, ci), 4)
+    scr = torch.full((sur.sur_wgrad_scratch_floats(ci, co, grid),), float("nan"), device="cuda")
+    out = []
+    for f in (sur.sur_conv3d_wgrad, sur.sur_conv3d_wgrad_ordered):
+        dw, db = torch.zeros((27, co, ci), device="cuda"), torch.zeros(co, device="cuda")
+        f(x, ci, dy, co, grid, scr, dw, db)
+        out.append((dw, db))
+    for a, b in zip(*out):
+        assert torch.equal(a, b) if same else float((a - b).norm() / b.norm()) < 4e-6
