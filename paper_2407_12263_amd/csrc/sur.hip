@@ -2848,7 +2848,12 @@ int device_cus() {
 }
 
 // Wavefronts per block of conv3d_tiled_kernel: eight on 16 x 4 x 8 tiles
-// for one output tile and at least four such tiles per CU; for two output
+// for one output tile and at least half such a tile per CU (us, four -> eight,
+// forward of 16, 48, 80 channels: 64^3 8.3 -> 7.5, 19.2 -> 17.3, 35.2 -> 31.8;
+// 48^3 7.2 -> 7.0, 12.6 -> 11.0, 24.6 -> 18.0; 64 x 48 x 48 7.1 -> 7.4, 15.2 ->
+// 15.4, 25.3 -> 25.9; and they pool in the same pass, which one output tile on
+// four does not: the network at 64^3 139 -> 132, 32 x 64 x 32 128 -> 123; below,
+// the blocks no longer reach half the CUs); for two output
 // or three tiles (one block per CU) where the tiles make whole rounds of the CUs
 // and at most eight input chunks (up to four keep their weights in LDS);
 // else four (SUR_CONV_WV=4 keeps four; for comparisons only, both give the
@@ -2857,7 +2862,7 @@ int conv_waves(int cin, int cout, int nx, int ny, int nz, int cus) {
     const char *v = std::getenv("SUR_CONV_WV");
     const long P = (long)nx * ny * nz, tiles = P / (kTX * kTY * 8);
     if ((v && *v == '4') || nz % 8 || cus <= 0) return 4;
-    if (cout <= 16) return tiles >= 4L * cus ? 8 : 4;
+    if (cout <= 16) return tiles >= cus / 2 ? 8 : 4;
     return cin <= 128 && tiles >= cus && tiles % cus == 0 ? 8 : 4;
 }
 

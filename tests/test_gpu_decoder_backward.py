@@ -128,6 +128,33 @@ def test_three_output_tiles_bits_of_two(sur, grid, cin, cout, monkeypatch):
         assert int((a != 0).sum()) > 0 and torch.equal(a, c)
 
 
+# eight wavefronts for one output tile from half a tile per CU on: the smallest
+# such grid, one below it, and sizes that are no powers of two
+@pytest.mark.parametrize("grid,cc,fc", [((32, 64, 32), 16, 16), ((32, 32, 56), 16, 16), ((48, 48, 48), 32, 16),
+                                        ((64, 48, 48), 48, 32)])
+def test_eight_wavefronts_bits_of_four(sur, grid, cc, fc, monkeypatch):
+    import torch
+    say(f"[conv] {grid} {cc}+{fc}->16 eight wavefronts")
+    P, ci = grid[0] * grid[1] * grid[2], cc + fc
+    x, xc, w, m = _bf16((P, ci), 1), _bf16((P // 8, cc), 5), _bf16((27, 16, ci), 2, 0.1), _bf16((P, 16), 3)
+    xf, b = x[:, cc:].contiguous(), _bf16(16, 4).view(torch.bfloat16).float()
+    out = []
+    for form in ("4", None):
+        if form:
+            monkeypatch.setenv("SUR_CONV_WV", form)
+        else:
+            monkeypatch.delenv("SUR_CONV_WV")
+        y = [torch.zeros((P, 16), dtype=torch.int16, device="cuda") for _ in range(4)]
+        pool = torch.zeros((P // 8, 16), dtype=torch.int16, device="cuda")
+        sur.sur_conv3d(x, ci, w, b, 16, grid, relu=1, y_bf16=y[0])
+        sur.sur_conv3d(x, ci, w, None, 16, grid, flip=1, mask=m, y_bf16=y[1])
+        sur.sur_conv3d_cat(xc, cc, xf, fc, w, b, 16, grid, relu=1, y_bf16=y[2])
+        sur.sur_conv3d_pool(x, ci, w, b, 16, grid, relu=1, y_bf16=y[3], y_pool=pool)
+        out.append(y + [pool])
+    for a, c in zip(*out):
+        assert int((a != 0).sum()) > 0 and torch.equal(a, c)
+
+
 # the ordered sums: those of the plain form where both take the tiled kernel;
 # sizes off the tile and grids where the plain form groups chunks, against FP64
 @pytest.mark.parametrize("grid,ci,co,same", [((16, 16, 32), 16, 32, True), ((32, 32, 32), 48, 48, True),
