@@ -11,6 +11,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "conv_any_plan.hpp"
 #include "sur.h"
 
 namespace {
@@ -899,7 +900,8 @@ size_t conv_tiled_lds(int nt, int wv = 4, int nw = 1, bool pool1 = false) {
 // weights' rows, are cin + 8 elements, an odd multiple of 16 bytes, so that
 // the 8-byte fragment reads of 16 consecutive rows touch every LDS bank once.
 // The weights are staged G taps at a time (all 27 where they fit beside the
-// halo), the next stage's loads held in registers meanwhile. They are the
+// halo), the next stage's loads, at most PW pieces a thread, held in registers
+// meanwhile. They are the
 // MFMA's first operand (lane (r, q) then holds channels 4q .. 4q + 3 of point
 // r: 8-byte stores). NC = cin / 16 is a constant, so that the fragment reads
 // of a tap row are a base and immediates. Bound by one block's chain (staging
@@ -907,7 +909,6 @@ size_t conv_tiled_lds(int nt, int wv = 4, int nw = 1, bool pool1 = false) {
 // exposed staging on the large ones. Against conv3d_kernel (27 gathers of 8
 // bytes per lane and step; two blocks on an 8^3 grid): 8^3 64 -> 64 105 -> 8.7
 // us, 40 x 24 x 56 80 -> 32 85 -> 25 us, 104 x 88 x 120 48 -> 16 336 -> 141 us.
-constexpr int kAnyPW = 6;  // 16-byte weight pieces a thread holds for the next stage
 template <int NC, int MT, int NT>
 __global__ void __launch_bounds__(256) conv3d_any_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
@@ -917,6 +918,7 @@ __global__ void __launch_bounds__(256) conv3d_any_kernel(
     extern __shared__ uint4 lds[];
     constexpr int cin = 16 * NC, C8 = 2 * NC, RS = C8 + 1;  // 16-byte pieces of a row, its LDS stride
     constexpr int RE = 8 * RS;                              // the stride in elements
+    constexpr int PW = any_pieces(NC, NT);                  // pieces a thread holds for the next stage
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, q = lane >> 4;
     const int hx = (1 << ltx) + 2, hy = (16 * MT >> ltx) + 2, hp = hx * hy * 6;
@@ -987,12 +989,12 @@ __global__ void __launch_bounds__(256) conv3d_any_kernel(
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
 
     const int sg = flip ? -RE : RE;
-    u4v pw[kAnyPW];
+    u4v pw[PW];
     for (int t0 = 0; t0 < 27; t0 += G) {
         const bool more = t0 + G < 27;
         __syncthreads();
         if (more) {
-            unroll<0, kAnyPW>([&](auto J) __attribute__((always_inline)) {
+            unroll<0, PW>([&](auto J) __attribute__((always_inline)) {
                 // past the last piece: the last again, not stored
                 pw[decltype(J)::value] = wsrc(t0 + G, min((int)threadIdx.x + 256 * decltype(J)::value, np - 1));
             });
@@ -1027,7 +1029,7 @@ __global__ void __launch_bounds__(256) conv3d_any_kernel(
         }
         if (more) {
             __syncthreads();  // this stage's weights are read
-            unroll<0, kAnyPW>([&](auto J) __attribute__((always_inline)) {
+            unroll<0, PW>([&](auto J) __attribute__((always_inline)) {
                 const int c = threadIdx.x + 256 * decltype(J)::value;
                 if (c < np) *wdst(c) = pw[decltype(J)::value];
             });
@@ -3036,77 +3038,28 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
 #undef SUR_CONV_LAUNCH
 }
 
-constexpr size_t kMaxLds = 160 * 1024;  // of a block, and of a CU
-
-// Points of the tiles 2^ltx x (16 mt / 2^ltx) x 4 that cover a grid.
-long any_padded(int mt, int ltx, int nx, int ny, int nz) {
-    const long tx = 1 << ltx, ty = 16 * mt >> ltx;
-    return (nx + tx - 1) / tx * tx * ((ny + ty - 1) / ty * ty) * ((nz + 3) / 4 * 4);
-}
-
-// Tile width of conv3d_any_kernel: the one that covers the grid with the
-// fewest points, the widest of equals.
-int any_ltx(int mt, int nx, int ny, int nz) {
-    int best = 4;
-    for (int l = 3; l >= 2; --l)
-        if (any_padded(mt, l, nx, ny, nz) < any_padded(mt, best, nx, ny, nz)) best = l;
-    return best;
-}
-
 // Launches conv3d_any_kernel where it applies: 32-bit element indices, the
 // alignments of its accesses, up to 128 input channels. False: nothing launched.
 bool conv_any_launch(const void *x, int cin, const void *w, const float *bias, int cout, int nx,
                      int ny, int nz, int flip, int relu, const void *mask, void *y_bf16,
                      float *y_f32, hipStream_t st) {
     const long P = (long)nx * ny * nz;
-    if (cin > 128 || !elems_ok(P, cin) || !elems_ok(P, cout) || !aligned16(x) || !aligned16(y_f32) ||
+    if (!elems_ok(P, cin) || !elems_ok(P, cout) || !aligned16(x) || !aligned16(y_f32) ||
         !aligned16(w) || ((uintptr_t)mask & 7) || ((uintptr_t)y_bf16 & 7))
         return false;
-    // the widest block tile (most products per fragment read, least halo)
-    // that still gives one and a half blocks per CU; below that the time is
-    // one block's chain, shortest with one run and one output tile
-    const int no = cout / 16;
-    const long cus = device_cus() > 0 ? device_cus() : 256;
-    const int cand[6][2] = {{4, 3}, {4, 2}, {2, 2}, {4, 1}, {2, 1}, {1, 1}};
-    int mt = 0, nt = 0, ltx = 0, tx = 0, ty = 0;
-    long ntile = 0;
-    size_t halo = 0, tap = 0;
-    for (const auto &c : cand) {
-        if (no % c[1]) continue;
-        const int l = any_ltx(c[0], nx, ny, nz);
-        const size_t h = (size_t)((1 << l) + 2) * ((16 * c[0] >> l) + 2) * 6 * (2 * cin + 16);
-        const size_t t = (size_t)16 * c[1] * (2 * cin + 16);
-        if (h + 3 * t > kMaxLds) continue;
-        const long n = any_padded(c[0], l, nx, ny, nz) / (64 * c[0]);
-        mt = c[0];
-        nt = c[1];
-        ltx = l;
-        tx = 1 << l;
-        ty = 16 * mt >> l;
-        ntile = n;
-        halo = h;
-        tap = t;
-        if (2 * n * (no / nt) >= 3 * cus) break;
-    }
-    if (mt == 0) return false;
-    // taps per weight stage: the most that cost no block per CU (a block
-    // alone on its CU leaves it idle while it stages: 48 -> 16 channels on
-    // 104 x 88 x 120, 141 us with 3 taps and two blocks, 214 with all 27 and
-    // one) and that a thread's registers hold
-    const long need = (ntile * (no / nt) + cus - 1) / cus;
-    auto per_cu = [&](int g) { return std::min(need, (long)(kMaxLds / (halo + g * tap))); };
-    int G = 27;
-    while (G > 3 && (per_cu(G) < per_cu(3) || (G < 27 && G * 2 * nt * cin > 256 * kAnyPW))) G /= 3;
-    const size_t lds = halo + G * tap;
+    const int cus = device_cus();
+    const AnyPlan pl = any_plan(cin, cout, nx, ny, nz, cus > 0 ? cus : 256);
+    if (pl.mt == 0) return false;
+    const int tx = 1 << pl.ltx, ty = 16 * pl.mt >> pl.ltx;
     const int ntx = (nx + tx - 1) / tx, nty = (ny + ty - 1) / ty;
-    const dim3 grid((unsigned)ntile, (unsigned)(no / nt));
+    const dim3 grid((unsigned)pl.ntile, (unsigned)(cout / 16 / pl.nt));
 #define SUR_ANY_LAUNCH(C, M, N)                                                                  \
-    hipLaunchKernelGGL((conv3d_any_kernel<C, M, N>), grid, dim3(256), lds, st, (const uint16_t *)x, \
-                       (const uint16_t *)w, bias, cout, nx, ny, nz, ltx, ntx, nty, G, flip, relu,  \
+    hipLaunchKernelGGL((conv3d_any_kernel<C, M, N>), grid, dim3(256), pl.lds, st, (const uint16_t *)x, \
+                       (const uint16_t *)w, bias, cout, nx, ny, nz, pl.ltx, ntx, nty, pl.taps, flip, relu, \
                        (const uint16_t *)mask, (uint16_t *)y_bf16, y_f32)
 #define SUR_ANY_N(C)                             \
     case C:                                      \
-        switch (10 * mt + nt) {                  \
+        switch (10 * pl.mt + pl.nt) {            \
             case 43: SUR_ANY_LAUNCH(C, 4, 3); break; \
             case 42: SUR_ANY_LAUNCH(C, 4, 2); break; \
             case 22: SUR_ANY_LAUNCH(C, 2, 2); break; \

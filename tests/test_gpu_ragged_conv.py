@@ -98,3 +98,14 @@ def test_ragged_weight_gradient(sur, grid, cin, cout):
     bound = 256 * 2.0 ** -24 * P * 2.0 / np.pi
     assert np.abs(dw.cpu().numpy() - rdw).max() <= bound
     assert np.abs(db.cpu().numpy() - rdb).max() <= 256 * 2.0 ** -24 * P * np.sqrt(2.0 / np.pi)
+
+
+# three output tiles of 96 input channels: the weight stage that takes most
+# registers (seven pieces a thread), over one and two columns of blocks, beside
+# the neighbouring channel counts on the same grid
+@pytest.mark.parametrize("flip", [0, 1])
+@pytest.mark.parametrize("grid,cin,cout", [((40, 64, 44), 96, 48), ((40, 40, 40), 96, 96), ((56, 56, 56), 96, 48),
+                                           ((40, 64, 44), 80, 48), ((40, 64, 44), 112, 48),
+                                           ((40, 64, 44), 128, 32)])
+def test_ragged_conv_widest_weight_stages(sur, grid, cin, cout, flip):
+    test_ragged_conv_bits_of_the_general_kernel(sur, grid, cin, cout, flip)
