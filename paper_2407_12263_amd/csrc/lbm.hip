@@ -49,7 +49,8 @@ int num_pop(const lbm_params *P) { return P->lattice == 27 ? 27 : 19; }
 
 // Launch shape: one block per tile of w x th nodes of one z-plane.
 // LBM_TILE_X_LOG2, LBM_TILE_ORDER and LBM_TILE_BAND override the choice
-// (tuning only; results do not depend on it).
+// (tuning only; results do not depend on it; a width whose tiles outnumber the
+// rows of the phase-mass partials is not taken).
 struct TileCfg {
     int w, th, threads, order, band;
 };
@@ -62,6 +63,15 @@ int env_int(const char *name, int dflt) {
 // Tiles of one z-plane.
 size_t plane_tiles(const lbm_params *P, int w, int th) {
     return (size_t)((P->nx + w - 1) / w) * (size_t)((P->ny + th - 1) / th);
+}
+
+// log2 of the tile width that LBM_TILE_X_LOG2 asks for; -1 for the default. A
+// block of a launch that sums the phase mass writes two values; the partials
+// hold NSUM for each tile of width 1.
+int tile_override(const lbm_params *P) {
+    const int l = env_int("LBM_TILE_X_LOG2", -1);
+    if (l < 0 || l > 8 || 2 * plane_tiles(P, 1 << l, BLOCK >> l) > NSUM * plane_tiles(P, 1, BLOCK)) return -1;
+    return l;
 }
 
 // base: a power of two that spans whole x-rows up to 128 nodes (a row's
@@ -77,13 +87,13 @@ size_t plane_tiles(const lbm_params *P, int w, int th) {
 TileCfg tile_cfg(const lbm_params *P, int threads, bool base) {
     TileCfg t;
     t.threads = threads;
-    const int nx = P->nx, lx = env_int("LBM_TILE_X_LOG2", -1);
+    const int nx = P->nx, lx = tile_override(P);
     int l = 0;
     while ((1 << l) < nx && l < (threads == 64 ? 6 : 7)) ++l;
     t.w = 1 << l;
     const size_t idle = ((size_t)(nx + 127) / 128 * 128 - (nx + 63) / 64 * 64) / 64;
     const size_t bytes = (size_t)P->nx * P->ny * P->nz * elem_bytes(P->precision) * 2 * num_pop(P);
-    if (lx >= 0 && lx <= 8 && threads == BLOCK) t.w = 1 << lx;
+    if (lx >= 0 && threads == BLOCK) t.w = 1 << lx;
     else if (base) ;
     else if (nx <= threads && (plane_tiles(P, nx, threads / nx) < plane_tiles(P, t.w, threads / t.w) ||
                                (nx > t.w && nx < BLOCK)))
@@ -136,8 +146,9 @@ Layout layout_of(const lbm_params *P) {
     // sizes have more tiles at the width in use (133 x 154: 154 against 133 a
     // plane); the diagnostics then take their tile rows in parts (reduce_diag).
     // The phase-mass partials are 2 values a block, not NSUM: they fit at up
-    // to 8.5 times this count, and no size has more than twice it.
-    const size_t nblocks = plane_tiles(P, 1, 256) * (size_t)P->nz;
+    // to 8.5 times this count. No size has more than twice it at its default
+    // width, and other widths are taken only where they fit (tile_override).
+    const size_t nblocks = plane_tiles(P, 1, BLOCK) * (size_t)P->nz;
     L.pdf_bytes = align_up((size_t)num_pop(P) * plane_pitch(P));
     L.g_bytes = is16(P->precision) ? 0 : L.pdf_bytes;
     L.phis_bytes = is16(P->precision) ? align_up(N * sizeof(float)) : 0;
@@ -261,8 +272,8 @@ Cover make_cover(const lbm_params *P, const TileCfg &tc) {
     v.walls = w[0] || w[1] || w[2];
     int l = 0;
     while ((1 << l) < P->nx && l < 7) ++l;
-    const int lx = env_int("LBM_TILE_X_LOG2", -1);
-    if (lx >= 0 && lx <= 8) l = lx;
+    const int lx = tile_override(P);
+    if (lx >= 0) l = lx;
     const int h = BLOCK >> l, top = (P->ny - 1) / h * h;  // slab rows, first row of the upper slab
     const int ylo = w[1] ? h : 0, yhi = w[1] ? top : P->ny;
     const int zlo = w[2] ? 1 : 0, zhi = w[2] ? P->nz - 1 : P->nz;

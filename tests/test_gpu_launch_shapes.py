@@ -59,3 +59,38 @@ def test_one_launch_and_split_launches_agree(precision, lattice):
         out.append([a[..., :64].copy() for a in gpu_fields(sol)])
     for a, b in zip(*out):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+# widths whose tiles outnumber the rows of the phase-mass partials (256 wide on
+# three nodes: 256 tiles a plane against 3 rows; walls add slabs), and widths
+# that are taken: the sums stay inside the workspace, the states are the same
+@pytest.mark.parametrize("nx,ny,nz,wall,width", [(3, 256, 2, 0, 8), (3, 256, 2, 1, 7), (1, 250, 3, 0, 8),
+                                                 (2, 300, 1, 0, 6), (40, 64, 3, 1, 8), (40, 64, 3, 0, 3)])
+@pytest.mark.parametrize("precision", ["fp16", "fp64"])
+def test_tile_override_stays_in_the_workspace(nx, ny, nz, wall, width, precision, monkeypatch):
+    import torch
+    from paper_2407_12263_amd import lbm
+    say(f"[shapes] {nx}x{ny}x{nz} {precision} tile width 2^{width}")
+    w = _workload(nx, ny, nz, (0, wall, 0))
+    prm = lbm.make_params(**dict(w.params(), precision=precision, mass_fix_every=1))
+    n = lbm.lbm_workspace_bytes(prm)
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64).cuda()
+    out = []
+    for over in (None, str(width)):
+        if over:
+            monkeypatch.setenv("LBM_TILE_X_LOG2", over)
+        buf = torch.full((n + (1 << 21),), 0xA5, dtype=torch.uint8, device="cuda")
+        ctx = lbm.lbm_init(prm, buf[:n], torch.cuda.current_stream().cuda_stream, dev(w.phi0), dev(w.u0), dev(w.p0))
+        lbm.lbm_step(ctx, 3)
+        d = lbm.lbm_diagnostics(ctx)
+        phi = torch.empty((nz, ny, nx), dtype=torch.float64, device="cuda")
+        lbm.lbm_fields(ctx, phi, None, None, 0)
+        torch.cuda.synchronize()
+        lbm.lbm_destroy(ctx)
+        assert bool((buf[n:] == 0xA5).all())
+        out.append((d["sum_phi"], phi))
+    # the phase mass is summed in the tiles' groups: the correction may differ
+    # in the last bits of an FP64 sum, and a state by its storage's rounding
+    eps = 2.0 ** (-11 if precision == "fp16" else -52)
+    assert abs(out[0][0] - out[1][0]) <= phi.numel() * eps
+    assert float((out[0][1] - out[1][1]).abs().max()) <= 64 * eps
