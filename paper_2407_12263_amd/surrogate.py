@@ -424,7 +424,8 @@ class UNet:
         their concat in place (sur_conv3d_cat), and so does the backward pass,
         unless the grid does not fit those kernels (the concat is then
         written); both ways give the same bits. keep_cat: a backward pass of
-        this forward will follow (the training step)."""
+        this forward will follow (the training step); where every level writes
+        its concat, backward takes either forward."""
         k = 0
         h = x_bf16
         hc = NCH
@@ -446,7 +447,7 @@ class UNet:
                 if not pooled:
                     sur_pool2(h, hc, g, self.act[f"pool{lv}"])
                 h = self.act[f"pool{lv}"]
-        self._cat_kept = keep_cat
+        self._cat_kept = keep_cat or not any(conv_cat_fits(g) for g in self.grids[:-1])
         for lv in range(self.nlev - 2, -1, -1):
             skip = self.act[f"enc{lv}b"]
             if self._cat_in_place(lv):
@@ -497,7 +498,8 @@ class UNet:
 
     def backward(self, dout):
         """dout: FP32 [P0, 16] gradient at the output. Fills gw, gb. Needs the
-        last forward to have been one with keep_cat=True."""
+        last forward to have been one with keep_cat=True, except where no
+        level's grid fits the in-place decoder."""
         if not getattr(self, "_cat_kept", False):
             raise RuntimeError("UNet.backward needs the forward pass run with keep_cat=True")
         torch = self.torch

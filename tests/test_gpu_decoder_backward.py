@@ -173,3 +173,28 @@ def test_ordered_weight_gradient(sur, grid, ci, co, same):
         out.append((dw, db))
     for a, b in zip(*out):
         assert torch.equal(a, b) if same else float((a - b).norm() / b.norm()) < 4e-6
+
+
+# no level fits the in-place decoder; one level (no concat at all); the finest
+# fits and the next one does not; both fit
+@pytest.mark.parametrize("grid,channels,accepted", [((24, 16, 16), (16, 32, 48), True), ((20, 12, 28), (16, 32), True),
+                                                    ((16, 8, 8), (16,), True), ((32, 8, 12), (16, 32, 48), False),
+                                                    ((32, 8, 16), (16, 32, 48), False)])
+def test_backward_after_an_inference_forward(sur, grid, channels, accepted):
+    """A forward pass without keep_cat is enough for the backward pass where
+    every concat is written, and refused where one is read in place."""
+    import torch
+    say(f"[decoder] backward after forward without keep_cat {grid}")
+    net = sur.UNet(grid, channels=channels, seed=3)
+    x, dout = _bf16((net.P[0], 16), 1), _bf16((net.P[0], 16), 2)
+    net.forward(x, keep_cat=True)
+    net.backward(dout)
+    want = net.flat["g"].clone()
+    net.flat["g"].zero_()
+    net.forward(x)
+    if accepted:
+        net.backward(dout)
+        assert int((want != 0).sum()) > 0 and torch.equal(net.flat["g"], want)
+    else:
+        with pytest.raises(RuntimeError):
+            net.backward(dout)
