@@ -198,3 +198,31 @@ def test_backward_after_an_inference_forward(sur, grid, channels, accepted):
     else:
         with pytest.raises(RuntimeError):
             net.backward(dout)
+
+
+# every level in place; the finest in place and the coarser ones written; two
+# levels in place with tiles that are no powers of two
+@pytest.mark.parametrize("grid,channels", [((64, 32, 32), (16, 32, 48)), ((32, 32, 32), (16, 32, 48, 64)),
+                                           ((96, 24, 40), (16, 32, 48))])
+def test_unet_in_place_decoder_equals_the_written_concat(sur, grid, channels, monkeypatch):
+    """A network whose decoders read and differentiate their concat in place
+    against one that writes every concat (and pools apart): the forward pass,
+    and the output, gradients and weights of two training steps."""
+    import torch
+    say(f"[decoder] network {grid}, concats in place and written")
+    P = grid[0] * grid[1] * grid[2]
+    x, tgt, wch = _bf16((P, 16), 1), _bf16((P, 16), 2).view(torch.bfloat16).float(), torch.ones(5, device="cuda")
+    out = []
+    for written in (False, True):
+        if written:
+            monkeypatch.setattr(sur, "conv_cat_fits", lambda g: False)
+        net = sur.UNet(grid, channels=channels, seed=4)
+        assert ("cat0" in net.act) == written
+        got = [net.forward(x).clone()]
+        for _ in range(2):
+            net.train_step(x, tgt, wch)
+            got += [net.out.clone(), net.flat["g"].clone(), net.flat["w"].clone()]
+        out.append(got)
+    for a, b in zip(*out):
+        assert bool(torch.isfinite(a).all()) and int((a != 0).sum()) > 0
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
