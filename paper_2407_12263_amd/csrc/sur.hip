@@ -1173,10 +1173,15 @@ constexpr int kWgDy = 256 + 8;
 // a constant further on. Accumulator 3 rr + d takes the tap dx = d - 1 of
 // row rr. BIAS (a wavefront with two rows) also multiplies dY by ones into
 // accumulator 6, the bias gradient (each column holds the channel sums).
-template <int MT, int NR, bool BIAS>
+// EDGE (grids that the tiles do not divide): the X of points beyond the grid,
+// which their zero output gradients would turn into NaN where it is infinite,
+// is zeroed: em[4 st] masks the lane's eight points of step st (always: a
+// branch in the loop costs more, 40 x 24 x 56 80 -> 32 28 us without, 29.4 with
+// the masks, 33 with a branch and 42 with two loops).
+template <int MT, int NR, bool BIAS, bool EDGE = false>
 __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
                                             const uint16_t *__restrict__ xht, int arow, int xlane,
-                                            int wave, f4 (&acc)[9][MT]) {
+                                            int wave, f4 (&acc)[9][MT], const uint4 *em = nullptr) {
     static_assert(!BIAS || NR == 2, "the bias takes a free accumulator");
     int xrow[NR];
 #pragma unroll
@@ -1192,6 +1197,8 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
             a[mt] = __builtin_bit_cast(bf8, *(const uint4 *)(dyt + arow + mt * 16 * kWgDy + 32 * st));
+        uint4 m{};
+        if constexpr (EDGE) m = em[4 * st];
 #pragma unroll
         for (int rr = 0; rr < NR; ++rr) {
             // the three dx taps of a row start dx + 1 elements into the same
@@ -1199,7 +1206,7 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
             const uint16_t *row = xht + xrow[rr] + soff;
             const uint4 w0 = *(const uint4 *)row;
             const uint32_t w1x = *(const uint32_t *)(row + 8);
-            const uint4 bw[3] = {
+            uint4 bw[3] = {
                 w0,  // dx = -1
                 uint4{__builtin_amdgcn_alignbyte(w0.y, w0.x, 2),  // dx = 0: one element
                       __builtin_amdgcn_alignbyte(w0.z, w0.y, 2),
@@ -1208,6 +1215,7 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
                 uint4{w0.y, w0.z, w0.w, w1x}};  // dx = +1: two elements
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
+                if constexpr (EDGE) bw[d] = uint4{bw[d].x & m.x, bw[d].y & m.y, bw[d].z & m.z, bw[d].w & m.w};
                 const bf8 b = __builtin_bit_cast(bf8, bw[d]);
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
@@ -1226,7 +1234,7 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
 // Weight gradient on the 16 x 4 x 4 point tiles of the forward kernel (partial
 // tiles at the ends of an axis included; against the per-tap product that
 // grids with such tiles took: 8^3 64 -> 64 35 -> 14 us, 40 x 24 x 56 80 -> 32
-// 223 -> 30 us, 104 x 88 x 120 48 -> 16 902 -> 97 us, with its reduction):
+// 223 -> 30 us, 104 x 88 x 120 48 -> 16 902 -> 112 us, with its reduction):
 // dW[t][o][i] = sum_p dY[p][o] X[p + d_t][i] as M = o, N = i, K = points
 // products on the 16x16x32 BF16 MFMA. A persistent block takes work items
 // blockIdx.x, + gridDim.x, ... (tiles in the forward's XCD slabs where the
@@ -1251,7 +1259,7 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
 // CAT: the input is the decoder's concat [up2(xc), x] read in place, as in the
 // forward: chunks below ccat from the coarse tensor at the parent point.
 template <int MT, bool RAG, bool FLUSH = false, bool CAT = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 1 && !FLUSH ? 4 : 1, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 1 && !FLUSH ? 4 : (MT == 3 && RAG ? 2 : 1), 8)))
 wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
                    const uint16_t *__restrict__ dy, int cout,
                    int nx, int ny, int nz,
@@ -1266,12 +1274,14 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
     constexpr int kNTap = 9;                    // taps per wavefront: 3 rows x 3 dx at most
     __shared__ __attribute__((aligned(16))) uint16_t xht[kXh];
     __shared__ __attribute__((aligned(16))) uint16_t dyt[MT * 16 * kDy];
+    __shared__ uint4 emask[RAG ? 32 : 4];  // RAG: the points of a tile that are on the grid
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, q = lane >> 4;
     const int cc = blockIdx.y * 16;
     // RAG (sizes that the tiles do not divide): the last tiles of an axis
     // reach beyond the grid, where the output gradient is staged as zeros, and
-    // so is the halo that no point of the grid reads
+    // so is the halo that no point of the grid reads; the halo that points
+    // within and beyond both read is zeroed for the latter (wgrad_steps)
     const int ntx = RAG ? (nx + kTX - 1) / kTX : nx / kTX, nty = RAG ? (ny + kTY - 1) / kTY : ny / kTY;
     const int ntile = ntx * nty * (RAG ? (nz + kTZ - 1) / kTZ : nz / kTZ);
     f4 acc[kNTap][MT];
@@ -1412,14 +1422,27 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
 #pragma unroll
             for (int e = 0; e < 8; ++e) dst[e * (kDy / 2)] = pair_half(w0[e >> 1], w1[e >> 1], e & 1);
         }
+        if constexpr (RAG) {
+            if (threadIdx.x < 32) {  // masks of step and quarter
+                int x0, y0, z0;
+                origin(tile, x0, y0, z0);
+                const int st = threadIdx.x >> 2, qq = threadIdx.x & 3, px = x0 + 8 * (qq & 1);
+                const bool row = y0 + 2 * (st & 1) + (qq >> 1) < ny && z0 + (st >> 1) < nz;
+                uint32_t m[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    m[j] = (row && px + 2 * j < nx ? 0xffffu : 0u) | (row && px + 2 * j + 1 < nx ? 0xffff0000u : 0u);
+                emask[threadIdx.x] = uint4{m[0], m[1], m[2], m[3]};
+            }
+        }
         __syncthreads();
         // the next tile's reads go out before this tile's MFMAs
         if (tile + (int)gridDim.x < ntile) fetch(tile + (int)gridDim.x);
         // wavefronts at their MFMAs go first (about 1% on the training step)
         __builtin_amdgcn_s_setprio(1);
-        if (wave == 0) wgrad_steps<MT, 3, false>(dyt, xht, arow, xlane, 0, acc);
-        else if (wave < 3 || !do_bias) wgrad_steps<MT, 2, false>(dyt, xht, arow, xlane, wave, acc);
-        else wgrad_steps<MT, 2, true>(dyt, xht, arow, xlane, 3, acc);
+        if (wave == 0) wgrad_steps<MT, 3, false, RAG>(dyt, xht, arow, xlane, 0, acc, emask + q);
+        else if (wave < 3 || !do_bias) wgrad_steps<MT, 2, false, RAG>(dyt, xht, arow, xlane, wave, acc, emask + q);
+        else wgrad_steps<MT, 2, true, RAG>(dyt, xht, arow, xlane, 3, acc, emask + q);
         __builtin_amdgcn_s_setprio(0);
         if constexpr (FLUSH) {
 #pragma unroll

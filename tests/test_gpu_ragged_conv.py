@@ -109,3 +109,34 @@ def test_ragged_weight_gradient(sur, grid, cin, cout):
                                            ((40, 64, 44), 128, 32)])
 def test_ragged_conv_widest_weight_stages(sur, grid, cin, cout, flip):
     test_ragged_conv_bits_of_the_general_kernel(sur, grid, cin, cout, flip)
+
+
+# an end in x only, in each axis, in all; plain and flushed forms; one and
+# three output tiles
+@pytest.mark.parametrize("grid,cin,cout", [((20, 12, 28), 16, 16), ((16, 18, 24), 32, 48), ((32, 12, 18), 16, 16),
+                                           ((13, 17, 18), 48, 32), ((72, 60, 74), 48, 16)])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_ragged_weight_gradient_of_infinite_inputs(sur, grid, cin, cout, axis):
+    """An infinite input at the last and the first point of an axis meets output
+    gradients that are never zero: each dW of its channel is infinite, as the
+    sum over the grid's points has it, and no other is touched."""
+    import torch
+    say(f"[ragged] wgrad {grid} {cin}->{cout}, infinite inputs at the ends of axis {axis}")
+    P = grid[0] * grid[1] * grid[2]
+    scratch = torch.empty(sur.sur_wgrad_scratch_floats(cin, cout, grid), dtype=torch.float32, device="cuda")
+    for at in (0, grid[axis] - 1):
+        x, dy = _bf16((P, cin), 5), _bf16((P, cout), 6)
+        assert int((dy == 0).sum()) == 0
+        where = [grid[0] // 2, grid[1] // 2, grid[2] // 2]
+        where[axis] = at
+        p = where[0] + grid[0] * (where[1] + grid[1] * where[2])
+        x.view(torch.bfloat16)[p, 3] = float("inf")
+        dw = torch.empty((27, cout, cin), dtype=torch.float32, device="cuda")
+        sur.sur_conv3d_wgrad(x, cin, dy, cout, grid, scratch, dw, torch.empty(cout, device="cuda"))
+        z, y, xx = np.meshgrid(*[np.arange(3) - 1] * 3, indexing="ij")
+        # tap d takes the input at p from the output gradient at p - d
+        src = [torch.as_tensor((w - d.ravel()) % n).cuda() for w, d, n in zip(where, (xx, y, z), grid)]
+        sign = torch.sign(dy.view(torch.bfloat16)[src[0] + grid[0] * (src[1] + grid[1] * src[2])].float())
+        assert bool(torch.isinf(dw[:, :, 3]).all()) and torch.equal(torch.sign(dw[:, :, 3]), sign)
+        keep = [c for c in range(cin) if c != 3]
+        assert bool(torch.isfinite(dw[:, :, keep]).all())
