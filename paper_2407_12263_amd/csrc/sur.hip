@@ -1178,10 +1178,10 @@ constexpr int kWgDy = 256 + 8;
 // is zeroed: em[4 st] masks the lane's eight points of step st (always: a
 // branch in the loop costs more, 40 x 24 x 56 80 -> 32 28 us without, 29.4 with
 // the masks, 33 with a branch and 42 with two loops).
-template <int MT, int NR, bool BIAS, bool EDGE = false>
+template <int MT, int NR, bool BIAS, bool EDGE = false, int NST = 8>
 __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
                                             const uint16_t *__restrict__ xht, int arow, int xlane,
-                                            int wave, f4 (&acc)[9][MT], const uint4 *em = nullptr) {
+                                            int wave, f4 (&acc)[9][MT], const uint4 *em = nullptr, int st0 = 0) {
     static_assert(!BIAS || NR == 2, "the bias takes a free accumulator");
     int xrow[NR];
 #pragma unroll
@@ -1191,7 +1191,7 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
     }
     const bf8 ones = __builtin_bit_cast(bf8, uint4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
 #pragma unroll 1
-    for (int st = 0; st < 8; ++st) {
+    for (int st = st0; st < st0 + NST; ++st) {
         const int soff = ((st >> 1) * kHY + 2 * (st & 1)) * kWgRow;
         bf8 a[MT];
 #pragma unroll
@@ -1233,7 +1233,7 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
 
 // Weight gradient on the 16 x 4 x 4 point tiles of the forward kernel (partial
 // tiles at the ends of an axis included; against the per-tap product that
-// grids with such tiles took: 8^3 64 -> 64 35 -> 14 us, 40 x 24 x 56 80 -> 32
+// grids with such tiles took: 8^3 64 -> 64 35 -> 13 us, 40 x 24 x 56 80 -> 32
 // 223 -> 30 us, 104 x 88 x 120 48 -> 16 902 -> 112 us, with its reduction):
 // dW[t][o][i] = sum_p dY[p][o] X[p + d_t][i] as M = o, N = i, K = points
 // products on the 16x16x32 BF16 MFMA. A persistent block takes work items
@@ -1258,7 +1258,7 @@ __device__ __forceinline__ void wgrad_steps(const uint16_t *__restrict__ dyt,
 // four blocks per CU).
 // CAT: the input is the decoder's concat [up2(xc), x] read in place, as in the
 // forward: chunks below ccat from the coarse tensor at the parent point.
-template <int MT, bool RAG, bool FLUSH = false, bool CAT = false>
+template <int MT, bool RAG, int FLUSH = 0, bool CAT = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 1 && !FLUSH ? 4 : (MT == 3 && RAG ? 2 : 1), 8)))
 wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
                    const uint16_t *__restrict__ dy, int cout,
@@ -1289,8 +1289,8 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
     for (int u = 0; u < kNTap; ++u)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[u][mt] = f4{0.f, 0.f, 0.f, 0.f};
-    // FLUSH: each tile's products are summed apart and added to the total
-    // (short chains of FP32 additions), for the output channels from
+    // FLUSH: a tile's products are summed apart, in FLUSH parts, and added to
+    // the total (short chains of FP32 additions), for the output channels from
     // 16 blockIdx.z
     f4 tot[FLUSH ? kNTap : 1][MT];
     const int co0 = FLUSH ? 16 * (int)blockIdx.z : 0;
@@ -1440,19 +1440,23 @@ wgrad_tiled_kernel(const uint16_t *__restrict__ x, int cin,
         if (tile + (int)gridDim.x < ntile) fetch(tile + (int)gridDim.x);
         // wavefronts at their MFMAs go first (about 1% on the training step)
         __builtin_amdgcn_s_setprio(1);
-        if (wave == 0) wgrad_steps<MT, 3, false, RAG>(dyt, xht, arow, xlane, 0, acc, emask + q);
-        else if (wave < 3 || !do_bias) wgrad_steps<MT, 2, false, RAG>(dyt, xht, arow, xlane, wave, acc, emask + q);
-        else wgrad_steps<MT, 2, true, RAG>(dyt, xht, arow, xlane, 3, acc, emask + q);
-        __builtin_amdgcn_s_setprio(0);
-        if constexpr (FLUSH) {
+        constexpr int NST = FLUSH ? 8 / FLUSH : 8;
+#pragma unroll 1
+        for (int st0 = 0; st0 < 8; st0 += NST) {
+            if (wave == 0) wgrad_steps<MT, 3, false, RAG, NST>(dyt, xht, arow, xlane, 0, acc, emask + q, st0);
+            else if (wave < 3 || !do_bias) wgrad_steps<MT, 2, false, RAG, NST>(dyt, xht, arow, xlane, wave, acc, emask + q, st0);
+            else wgrad_steps<MT, 2, true, RAG, NST>(dyt, xht, arow, xlane, 3, acc, emask + q, st0);
+            if constexpr (FLUSH) {
 #pragma unroll
-            for (int u = 0; u < kNTap; ++u)
+                for (int u = 0; u < kNTap; ++u)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    tot[u][mt] += acc[u][mt];
-                    acc[u][mt] = f4{0.f, 0.f, 0.f, 0.f};
-                }
+                    for (int mt = 0; mt < MT; ++mt) {
+                        tot[u][mt] += acc[u][mt];
+                        acc[u][mt] = f4{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
         }
+        __builtin_amdgcn_s_setprio(0);
     }
     if constexpr (FLUSH) {
 #pragma unroll
@@ -2782,12 +2786,25 @@ long rag_tiles(int nx, int ny, int nz) {
 }
 
 // The tiled weight gradient: 32-bit element indices, aligned operands, at
-// most 64 output channels, and more than one tile's worth of points (below,
-// one launch of the per-tap product is as fast: 4^3 64 -> 64, 15 us both).
+// most 64 output channels, and at least one tile's worth of points.
 bool wgrad_tiled_ok(const void *x, int cin, const void *dy, int cout, int nx, int ny, int nz) {
     const long P = (long)nx * ny * nz;
     return cout <= 64 && P >= kTX * kTY * kTZ && elems_ok(P, cin) && elems_ok(P, cout) &&
            aligned16(x) && aligned16(dy);
+}
+
+// Grids that the tiles do not divide and that still take them, by error and
+// time against the per-tap product. From 512 points its chains of additions
+// are longer (relative error of dW, 48 -> 64 on 570 grids: 8^3 7.2e-8 there and
+// 6.5e-8 here, 33 us and 13; 4 x 8 x 8 5.9e-8 and 6.4e-8), with rows of more than
+// one tile from 768 (17 x 5 x 7 1.09 times, 18 x 9 x 4 1.02 times; above, the
+// largest are 16 x 9 x 4 0.98 and 18 x 9 x 5 0.92 times). And at most five times the points in the tiles, four on small grids, since a
+// tile takes a block 3 to 6 us however few points it has (100 x 100 x 1, 4.5
+// times, 48 -> 16 150 and 27 us; 24 x 1 x 24, 5.3 times, 20 and 25; 1000 x 1 x 1,
+// 16 times, 28 and 69; 1 x 300 x 300, 16 times, 48 -> 64 300 and 512).
+bool wgrad_rag_ok(int nx, int ny, int nz) {
+    const long P = (long)nx * ny * nz;
+    return P >= (nx <= kTX ? 512 : 768) && rag_tiles(nx, ny, nz) * (kTX * kTY * kTZ) <= (P < 1024 ? 4 : 5) * P;
 }
 
 // Persistent blocks of the tiled weight gradient per 16-channel input chunk:
@@ -3216,17 +3233,18 @@ int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void
     const long n = 27L * cin * cout;
     bool bias_done = false;
     float *tiled_bp = nullptr;  // bias partials of the tiled kernel, summed with dw's last pass
-    if (wgrad_tiled_ok(x, cin, dy, cout, nx, ny, nz) && !(ordered && (nx % kTX || ny % kTY || nz % kTZ))) {
+    const bool rag = nx % kTX || ny % kTY || nz % kTZ;
+    if (wgrad_tiled_ok(x, cin, dy, cout, nx, ny, nz) && (!rag || (!ordered && wgrad_rag_ok(nx, ny, nz)))) {
         nch = wgrad_tiled_blocks(cin, P);
         const dim3 grid((unsigned)nch, (unsigned)(cin / 16));
         // the bias partials follow the weight partials: one per block
         float *bp = dbias ? scratch + nch * n : nullptr;
-        const bool rag = nx % kTX || ny % kTY || nz % kTZ;
         // long chains of additions (48 -> 16 on 104 x 88 x 120, 25 tiles a
         // block: 5.3e-7 relative error of dW against 2.9e-7 of the per-tap
         // product) and the smallest grids (8^3 64 -> 64: 9.0e-8 against
-        // 7.2e-8; and 32 blocks instead of 8) take the flushed form (1.6e-7
-        // and 7.1e-8); in between the plain form is as exact and faster
+        // 7.2e-8; and 32 blocks instead of 8) take the flushed form (1.6e-7;
+        // in two parts a tile, 6.5e-8, in one 7.1e-8); in between the plain
+        // form is as exact and faster
         const long tiles = rag_tiles(nx, ny, nz);
         const uint16_t *xcb = (const uint16_t *)xc;
         const int ng = ordered ? 0 : wgrad_group(cin, cout, rag, tiles, wgrad_rows_max(cin, P), device_cus(), &nch);
@@ -3242,7 +3260,7 @@ int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void
 #undef SUR_WG_COLS
         } else if (xc) {
 #define SUR_WG_CAT(M)                                                                              \
-    hipLaunchKernelGGL((wgrad_tiled_kernel<M, false, false, true>), grid, dim3(256), 0, s, xb, cin, \
+    hipLaunchKernelGGL((wgrad_tiled_kernel<M, false, 0, true>), grid, dim3(256), 0, s, xb, cin, \
                        db, cout, nx, ny, nz, scratch, bp, xcb, cc)
             switch (cout / 16) {
                 case 1: SUR_WG_CAT(1); break;
@@ -3253,8 +3271,12 @@ int wgrad_run(const void *x, int32_t cin, const void *xc, int32_t cc, const void
 #undef SUR_WG_CAT
         } else if (rag && (tiles > 8 * nch || P < 4096)) {
             const dim3 gz(grid.x, grid.y, (unsigned)(cout / 16));
-            hipLaunchKernelGGL((wgrad_tiled_kernel<1, true, true>), gz, dim3(256), 0, s, xb, cin, db,
-                               cout, nx, ny, nz, scratch, bp, nullptr, 0);
+            if (P < 4096)
+                hipLaunchKernelGGL((wgrad_tiled_kernel<1, true, 2>), gz, dim3(256), 0, s, xb, cin, db, cout, nx, ny, nz,
+                                   scratch, bp, nullptr, 0);
+            else
+                hipLaunchKernelGGL((wgrad_tiled_kernel<1, true, 1>), gz, dim3(256), 0, s, xb, cin, db, cout, nx, ny, nz,
+                                   scratch, bp, nullptr, 0);
         } else
 #define SUR_WG_LAUNCH(M)                                                                             \
     if (rag) hipLaunchKernelGGL((wgrad_tiled_kernel<M, true>), grid, dim3(256), 0, s, xb, cin, db,   \
