@@ -3078,8 +3078,9 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
 #undef SUR_CONV_LAUNCH
 }
 
-// Launches conv3d_any_kernel where it applies: 32-bit element indices, the
-// alignments of its accesses, up to 128 input channels. False: nothing launched.
+// Launches conv3d_any_kernel where it applies (32-bit element indices, the
+// alignments of its accesses, up to 128 input channels) and is the faster one.
+// False: nothing launched.
 bool conv_any_launch(const void *x, int cin, const void *w, const float *bias, int cout, int nx,
                      int ny, int nz, int flip, int relu, const void *mask, void *y_bf16,
                      float *y_f32, hipStream_t st) {
@@ -3089,7 +3090,10 @@ bool conv_any_launch(const void *x, int cin, const void *w, const float *bias, i
         return false;
     const int cus = device_cus();
     const AnyPlan pl = any_plan(cin, cout, nx, ny, nz, cus > 0 ? cus : 256);
-    if (pl.mt == 0) return false;
+    // thin grids, of which most of a tile lies beyond, are the general
+    // kernel's (48 -> 64, general kernel and tiles: 300 x 300 x 1 74 and 120 us,
+    // 2 x 300 x 300 97 and 203, 1 x 1 x 20000 62 and 361)
+    if (pl.mt == 0 || any_us(pl, cin, cout, cus > 0 ? cus : 256) > general_us(cin, cout, P)) return false;
     const int tx = 1 << pl.ltx, ty = 16 * pl.mt >> pl.ltx;
     const int ntx = (nx + tx - 1) / tx, nty = (ny + ty - 1) / ty;
     const dim3 grid((unsigned)pl.ntile, (unsigned)(cout / 16 / pl.nt));

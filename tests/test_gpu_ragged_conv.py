@@ -170,3 +170,12 @@ def test_ragged_weight_gradient_is_as_exact_as_the_ordered(sur, grid, cin, cout)
             f(x, cin, dy, cout, grid, scratch, dw, torch.empty(cout, device="cuda"))
             err[k] += float((dw - ref).norm() / ref.norm())
     assert err[1] <= 1.02 * err[0]
+
+
+# tile widths taken for a second block on a CU or to fit three output tiles;
+# thin grids on either side of the rule that leaves them to the general kernel
+@pytest.mark.parametrize("grid,cin,cout", [((60, 60, 60), 48, 64), ((44, 40, 70), 96, 48), ((52, 60, 38), 112, 48),
+                                           ((1, 1, 2000), 48, 64), ((1, 1, 9000), 48, 64), ((200, 150, 1), 32, 48),
+                                           ((2, 120, 120), 112, 48), ((300, 160, 1), 16, 16)])
+def test_ragged_conv_tile_widths_and_thin_grids(sur, grid, cin, cout):
+    test_ragged_conv_bits_of_the_general_kernel(sur, grid, cin, cout, 0)
