@@ -2889,23 +2889,37 @@ int device_cus() {
     return cus;
 }
 
+// What a convolution's launch is: a forward one, one of the concat form, one
+// that pools or a data gradient.
+enum class ConvCall { plain, cat, other };
+
 // Wavefronts per block of conv3d_tiled_kernel: eight on 16 x 4 x 8 tiles
 // for one output tile and at least half such a tile per CU (us, four -> eight,
-// forward of 16, 48, 80 channels: 64^3 8.3 -> 7.5, 19.2 -> 17.3, 35.2 -> 31.8;
-// 48^3 7.2 -> 7.0, 12.6 -> 11.0, 24.6 -> 18.0; 64 x 48 x 48 7.1 -> 7.4, 15.2 ->
-// 15.4, 25.3 -> 25.9; and they pool in the same pass, which one output tile on
-// four does not: the network at 64^3 139 -> 132, 32 x 64 x 32 128 -> 123; below,
-// the blocks no longer reach half the CUs); for two output
+// forward of 16, 48, 80 channels: 64^3 7.4 -> 6.9, 16.7 -> 15.3, 33.6 -> 30.2;
+// 48^3 6.1 -> 6.1, 12.1 -> 10.6, 24.8 -> 17.7; they pool in the same pass, which
+// one output tile on four does not, 64 x 48 x 48 12.3 -> 7.7, and a data gradient
+// loads its mask before the products, 7.9 -> 7.4; below, the blocks no longer
+// reach half the CUs). But four where a second, part-filled round of CUs gains
+// a forward pass nothing, from one to 1 3/4 tiles per CU: the concat form
+// (64 x 48 x 48 with 48 and 80 channels 13.4 -> 14.4, 19.5 -> 20.6, up to 64 x 64
+// x 48), one input chunk (6.7 -> 6.9), and several up to 1 1/4 tiles where the
+// tiles of a plane fall on the XCDs evenly (64 x 48 x 48 14.7 -> 15.2, 25.3 ->
+// 26.1; 80 x 48 x 40, 60 tiles a plane, 17.0 -> 15.0, 39.8 -> 32.4; 64 x 64 x 48
+// 16.5 -> 16.4, 33.0 -> 30.9). For two output
 // or three tiles (one block per CU) where the tiles make whole rounds of the CUs
 // and at most eight input chunks (up to four keep their weights in LDS);
 // else four (SUR_CONV_WV=4 keeps four; for comparisons only, both give the
 // same bits).
-int conv_waves(int cin, int cout, int nx, int ny, int nz, int cus) {
+int conv_waves(int cin, int cout, int nx, int ny, int nz, int cus, ConvCall call) {
     const char *v = std::getenv("SUR_CONV_WV");
     const long P = (long)nx * ny * nz, tiles = P / (kTX * kTY * 8);
     if ((v && *v == '4') || nz % 8 || cus <= 0) return 4;
-    if (cout <= 16) return tiles >= cus / 2 ? 8 : 4;
-    return cin <= 128 && tiles >= cus && tiles % cus == 0 ? 8 : 4;
+    if (cout > 16) return cin <= 128 && tiles >= cus && tiles % cus == 0 ? 8 : 4;
+    if (call == ConvCall::other) return tiles >= cus / 2 ? 8 : 4;
+    if (tiles > cus && 4 * tiles < 7L * cus &&
+        (call == ConvCall::cat || cin == 16 || (4 * tiles <= 5L * cus && nx / kTX * (ny / kTY) % 8 == 0)))
+        return 4;
+    return tiles > cus / 2 ? 8 : 4;
 }
 
 // Launches conv3d_tiled_kernel; xc != NULL selects the concat form (cc
@@ -2922,7 +2936,8 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
     int nt = cout <= 16 ? 1 : kNT;
     long ncb = (cout + 16 * nt - 1) / (16 * nt);
     const int cus = device_cus();
-    const int nwv = conv_waves(cin, cout, nx, ny, nz, cus);
+    const int nwv = conv_waves(cin, cout, nx, ny, nz, cus,
+                               xc ? ConvCall::cat : (flip || y_pool ? ConvCall::other : ConvCall::plain));
     const long tiles = P / (kTX * kTY * nwv);
     // three output tiles per eight-wavefront block where that makes fewer
     // columns of blocks (3, 5, 6, 7, ... tiles): the halo is staged and its
@@ -3175,7 +3190,7 @@ int sur_conv3d_pool(const void *x, int32_t cin, const void *w, const float *bias
         !dims_ok(nx, ny, nz) || !conv_tiled_ok(x, cin, w, cout, nx, ny, nz) ||
         ((uintptr_t)y_bf16 & 7) != 0 || ((uintptr_t)y_pool & 7) != 0)
         return SUR_EINVAL;
-    if (cout <= 16 && conv_waves(cin, cout, nx, ny, nz, device_cus()) == 4) {
+    if (cout <= 16 && conv_waves(cin, cout, nx, ny, nz, device_cus(), ConvCall::other) == 4) {
         // one output tile on four wavefronts: pooling in the epilogue would
         // take LDS that a fourth block per CU needs, so pool after
         conv_tiled_launch(x, cin, nullptr, 0, w, bias, cout, nx, ny, nz, false, relu, nullptr,

@@ -226,3 +226,11 @@ def test_unet_in_place_decoder_equals_the_written_concat(sur, grid, channels, mo
     for a, b in zip(*out):
         assert bool(torch.isfinite(a).all()) and int((a != 0).sum()) > 0
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+# either side of the range that keeps four wavefronts: more than 1 3/4 tiles per
+# CU, several input chunks with uneven planes, and above 1 1/4 tiles
+@pytest.mark.parametrize("grid,cc,fc", [((64, 64, 56), 16, 16), ((80, 48, 40), 32, 16), ((64, 64, 48), 48, 32),
+                                        ((48, 64, 48), 16, 16)])
+def test_wavefront_rule_bits_of_four(sur, grid, cc, fc, monkeypatch):
+    test_eight_wavefronts_bits_of_four(sur, grid, cc, fc, monkeypatch)
