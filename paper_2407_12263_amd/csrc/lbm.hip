@@ -219,32 +219,29 @@ FastDiv make_fastdiv(uint32_t d) {
 // z0 + k zstep (k < nz), in tiles of shape tc.
 Box make_box(const lbm_params *P, const TileCfg &tc, int y0, int rows, int ystep, int z0, int nz, int zstep) {
     Box b;
-    b.tw = tc.w;
     b.th = tc.th;
     b.tw_log2 = -1;
     for (int l = 0; l <= 8; ++l)
         if (tc.w == 1 << l) b.tw_log2 = l;
-    b.ntx = (P->nx + tc.w - 1) / tc.w;
     b.nsub = (rows + tc.th - 1) / tc.th;
-    b.nty = b.nsub * (ystep > 0 ? 2 : 1);
+    const int ntx = (P->nx + tc.w - 1) / tc.w, nty = b.nsub * (ystep > 0 ? 2 : 1), ntiles = ntx * nty * nz;
+    const int band = tc.band < nty ? tc.band : nty;
     b.nz = nz;
-    b.ntiles = b.ntx * b.nty * nz;
     b.y0 = y0;
     b.ystep = ystep;
     b.rows = rows;
     b.z0 = z0;
     b.zstep = zstep;
     b.order = tc.order;
-    b.band = tc.band < b.nty ? tc.band : b.nty;
-    b.nfull = b.nty / b.band;
-    b.xq = b.ntiles / 8;
-    b.xr = b.ntiles % 8;
-    const int rem = b.nty - b.nfull * b.band;
+    b.nfull = nty / band;
+    b.xq = ntiles / 8;
+    b.xr = ntiles % 8;
+    const int rem = nty - b.nfull * band;
     b.d_tw = make_fastdiv((uint32_t)tc.w);
-    b.d_ntx = make_fastdiv((uint32_t)b.ntx);
-    b.d_nty = make_fastdiv((uint32_t)b.nty);
-    b.d_band = make_fastdiv((uint32_t)b.band);
-    b.d_perband = make_fastdiv((uint32_t)(b.band * nz));
+    b.d_ntx = make_fastdiv((uint32_t)ntx);
+    b.d_nty = make_fastdiv((uint32_t)nty);
+    b.d_band = make_fastdiv((uint32_t)band);
+    b.d_perband = make_fastdiv((uint32_t)(band * nz));
     b.d_rem = make_fastdiv((uint32_t)(rem > 0 ? rem : 1));
     return b;
 }
@@ -288,7 +285,7 @@ Cover make_cover(const lbm_params *P, const TileCfg &tc) {
         if (w[2]) v.b[v.n++] = make_box(P, tc, ylo, yhi - ylo, 0, 0, 2, P->nz - 1);
     }
     v.blocks = 0;
-    for (int k = 0; k < v.n; ++k) v.blocks += v.b[k].ntiles;
+    for (int k = 0; k < v.n; ++k) v.blocks += v.b[k].ntiles();
     return v;
 }
 
@@ -405,13 +402,13 @@ void launch_step(lbm_ctx *c, int src, int dst, const DevParams<typename St::R> &
                  int threads, MassFix mf, int &block_off) {
     mf.block_off = block_off;
     if constexpr (St::DEV && !W && !FD && St::Q == 19)
-        hipLaunchKernelGGL((step_kernel_o5<St, M, W, FD>), dim3((unsigned)b.ntiles), dim3(threads), 0,
+        hipLaunchKernelGGL((step_kernel_o5<St, M, W, FD>), dim3((unsigned)b.ntiles()), dim3(threads), 0,
                            c->stream, cbuf_of<St>(c, src), buf_of<St>(c, dst), P, b, mf);
     else
-        hipLaunchKernelGGL((step_kernel<St, M, W, FD>), dim3((unsigned)b.ntiles), dim3(threads), 0,
+        hipLaunchKernelGGL((step_kernel<St, M, W, FD>), dim3((unsigned)b.ntiles()), dim3(threads), 0,
                            c->stream, cbuf_of<St>(c, src), buf_of<St>(c, dst), P, b, mf,
                            make_wet<typename St::R>(&c->P));
-    block_off += b.ntiles;
+    block_off += b.ntiles();
 }
 
 // Parameters of a launch, with the phi field of the finite-difference variant.
@@ -429,7 +426,7 @@ void launch_phi(lbm_ctx *c, int src, const MassFix &mf) {
     const DevParams<typename St::R> &P = launch_params<typename St::R>(c);
     const Cover &v = c->cover;
     for (int k = 0; k < v.n; ++k) {
-        const dim3 grid((unsigned)v.b[k].ntiles), block(v.threads);
+        const dim3 grid((unsigned)v.b[k].ntiles()), block(v.threads);
         if (v.split ? k > 0 : v.walls)
             hipLaunchKernelGGL((phi_kernel<St, M, true>), grid, block, 0, c->stream, cbuf_of<St>(c, src), P, v.b[k], mf);
         else
@@ -456,8 +453,8 @@ void launch_step_w(lbm_ctx *c, int src, int dst, const MassFix &mf) {
             B.b[0] = v.b[0];
             B.b[1] = v.b[1];
             B.b[2] = v.b[v.n - 1];
-            B.n0 = (uint32_t)v.b[0].ntiles;
-            B.n1 = B.n0 + (uint32_t)v.b[1].ntiles;
+            B.n0 = (uint32_t)v.b[0].ntiles();
+            B.n1 = B.n0 + (uint32_t)v.b[1].ntiles();
             hipLaunchKernelGGL((step_all_kernel<St, M>), dim3((unsigned)v.blocks), dim3(v.threads), 0,
                                c->stream, cbuf_of<St>(c, src), buf_of<St>(c, dst), P, B, mf,
                                make_wet<R>(&c->P));
@@ -532,7 +529,7 @@ template <class St, Mode M, bool W>
 void launch_moments(lbm_ctx *c, const FieldOut &o, const Box &b, int threads) {
     using R = typename St::R;
     const DevParams<R> &P = launch_params<R>(c);
-    const dim3 grid((unsigned)b.ntiles), block(threads);
+    const dim3 grid((unsigned)b.ntiles()), block(threads);
     if constexpr (St::Q == 19) {
         if (c->P.normal_fd) {
             launch_phi<St, M>(c, c->cur ^ 1, MassFix{0, nullptr, nullptr, 0});
@@ -581,12 +578,12 @@ void launch_init(lbm_ctx *c, const double *phi0, const double *u0, const double 
     const bool step = !c->P.normal_fd;
     // the sum of phi in the groups of full_base: in the same launch where that
     // is the launch
-    const bool sum_here = v.n == 1 && v.threads == BLOCK && v.b[0].tw == c->full_base.tw;
+    const bool sum_here = v.n == 1 && v.threads == BLOCK && v.b[0].tw() == c->full_base.tw();
     if (!sum_here)
-        hipLaunchKernelGGL(field_sum_kernel, dim3((unsigned)c->full_base.ntiles), dim3(BLOCK), 0, c->stream,
+        hipLaunchKernelGGL(field_sum_kernel, dim3((unsigned)c->full_base.ntiles()), dim3(BLOCK), 0, c->stream,
                            phi0, PD, c->full_base, c->partials);
     auto launch = [&](const Box &b, auto W, auto S) {
-        hipLaunchKernelGGL((init_kernel<St, decltype(W)::value, decltype(S)::value>), dim3((unsigned)b.ntiles),
+        hipLaunchKernelGGL((init_kernel<St, decltype(W)::value, decltype(S)::value>), dim3((unsigned)b.ntiles()),
                            dim3(v.threads), 0, c->stream, phi0, u0, p0, PD, PR, b, buf_of<St>(c, dst),
                            c->flag, sum_here ? c->partials : nullptr, buf_of<St>(c, post), make_wet<R>(&c->P));
     };
@@ -618,7 +615,7 @@ template <class St>
 void launch_load(lbm_ctx *c, const double *f, const double *g, int dst) {
     using R = typename St::R;
     const DevParams<R> &P = launch_params<R>(c);
-    hipLaunchKernelGGL((load_kernel<St>), dim3((unsigned)c->full.ntiles), dim3(c->cover.threads), 0, c->stream,
+    hipLaunchKernelGGL((load_kernel<St>), dim3((unsigned)c->full.ntiles()), dim3(c->cover.threads), 0, c->stream,
                        f, g, P, c->full, buf_of<St>(c, dst));
 }
 
@@ -655,21 +652,21 @@ int reduce_diag(lbm_ctx *c, const double *phi_ref) {
     o.phi_ref = phi_ref;
     o.partials = c->partials;
     const Box &all = c->full_base;
-    const int per = all.ntx * all.nz;  // blocks of a tile row
+    const int per = all.ntx() * all.nz;  // blocks of a tile row
     const int cap = (int)(c->L.partial_bytes / (NSUM * sizeof(double)));
-    if (all.ntiles <= cap) {
+    if (all.ntiles() <= cap) {
         moments_any(c, o, all, BLOCK);
-        fold_partials(c, all.ntiles, true);
+        fold_partials(c, all.ntiles(), true);
         return check_launch(c);
     }
-    for (int ty = 0; ty < all.nty;) {
+    for (int ty = 0; ty < all.nty();) {
         o.row0 = ty > 0 ? 1 : 0;
-        const int n = std::min(all.nty - ty, (cap - 1) / per);
+        const int n = std::min(all.nty() - ty, (cap - 1) / per);
         if (n < 1) return LBM_EDEVICE;
         const int y0 = ty * all.th, rows = std::min(n * all.th, c->P.ny - y0);
         moments_any(c, o, make_box(&c->P, c->base, y0, rows, 0, 0, c->P.nz, 1), BLOCK);
         ty += n;
-        fold_partials(c, o.row0 + n * per, ty == all.nty);
+        fold_partials(c, o.row0 + n * per, ty == all.nty());
     }
     return check_launch(c);
 }
@@ -681,7 +678,7 @@ int build_state(lbm_ctx *c, const double *d_phi, const double *d_u, const double
     hipLaunchKernelGGL(clear_int_kernel, dim3(1), dim3(1), 0, c->stream, c->flag);
     init_any(c, d_phi, d_u, d_p, 1, 0);
     hipLaunchKernelGGL(massfix_kernel, dim3(1), dim3(RBLOCK), 0, c->stream,
-                       (const double *)c->partials, c->full_base.ntiles, c->mf, c->mf + 1, 1);
+                       (const double *)c->partials, c->full_base.ntiles(), c->mf, c->mf + 1, 1);
     c->cur = 0;
     c->prev_local = true;
     c->mf_pending = false;

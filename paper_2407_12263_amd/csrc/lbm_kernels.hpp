@@ -148,15 +148,22 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv &f) {
 // The nodes of a launch and their tiles: all x, one or two slabs of `rows` rows
 // (the first at y0, the second ystep further), planes z0 + k zstep (k < nz).
 // A slab has nsub rows of tiles of tw x th nodes; tile rows 0 .. nty - 1 run
-// through the first slab, then the second.
+// through the first slab, then the second. No value is held twice: a kernel's
+// arguments are read once per XCD from memory far away, and the 20 bytes that
+// repeated divisors took were a 64-byte line more (16 steps of 64^3 FP16 214 ->
+// 209 us, D3Q27 BF16 298 -> 291).
 struct Box {
-    int tw, th, tw_log2;        // tw_log2: log2 tw, or -1 where it is no power of two
-    int ntx, nty, nz, ntiles;
-    int y0, ystep, nsub, rows, z0, zstep;
+    int th, tw_log2;         // tile height; log2 of its width, or -1 where that is no power of two
+    int nz, y0, ystep, nsub, rows, z0, zstep;
     int order;               // 0: tile = block id; 1: XCD runs; 2: XCD runs of z-banded order
-    int band, nfull;         // tile rows per band (order 2), full bands
-    int xq, xr;              // ntiles = 8 xq + xr (XCD runs)
+    int nfull;               // full bands (order 2)
+    int xq, xr;              // number of tiles = 8 xq + xr (XCD runs)
+    // tile width, tiles of a row, tile rows, tile rows per band (order 2)
     FastDiv d_tw, d_ntx, d_nty, d_band, d_perband, d_rem;
+    int tw() const { return (int)d_tw.d; }
+    int ntx() const { return (int)d_ntx.d; }
+    int nty() const { return (int)d_nty.d; }
+    int ntiles() const { return 8 * xq + xr; }
 };
 
 template <class R>
@@ -285,16 +292,20 @@ struct Site {
     bool wall;           // lo or hi on some axis
 };
 
+// A tile: its first node, and the first row beyond its slab or the lattice.
+struct Tile {
+    uint32_t x0, y0, z;
+    int yend;
+};
+
 // Block -> tile. Workgroups are dispatched round-robin to the 8 XCDs; with
 // order >= 1, XCD k takes the contiguous run of logical tiles
 // [start_k, start_k + count_k), so neighbouring tiles share its L2. Logical
 // tiles run x fastest, then (order 1) y, then z, or (order 2) y within a band
 // of `band` tile-rows, then z, then the band: the z-neighbour planes a tile
 // re-reads are then only a band's width of tiles away.
-template <int NQ, class R>
-__device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P, const Box &B, uint32_t b) {
-    using L = LatQ<NQ>;
-    Site<NQ> s;
+template <class R>
+__device__ __forceinline__ Tile make_tile(const DevParams<R> &P, const Box &B, uint32_t b) {
     uint32_t t = b;
     if (B.order != 0) {
         // XCD runs: block b runs on XCD b mod 8; the XCD's blocks take one
@@ -303,11 +314,11 @@ __device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P, const Box &
         const uint32_t q = (uint32_t)B.xq, r = (uint32_t)B.xr;
         t = (xcd < r ? xcd * (q + 1u) : r * (q + 1u) + (xcd - r) * q) + slot;
     }
-    const uint32_t nty = (uint32_t)B.nty, nz = (uint32_t)B.nz;
-    const uint32_t rr = fdiv(t, B.d_ntx), tx = t - rr * (uint32_t)B.ntx;
+    const uint32_t nty = B.d_nty.d, nz = (uint32_t)B.nz;
+    const uint32_t rr = fdiv(t, B.d_ntx), tx = t - rr * B.d_ntx.d;
     uint32_t ty, tz;
     if (B.order == 2) {
-        const uint32_t bw = (uint32_t)B.band, full = (uint32_t)B.nfull, per_band = bw * nz;
+        const uint32_t bw = B.d_band.d, full = (uint32_t)B.nfull, per_band = bw * nz;
         if (rr < full * per_band) {
             const uint32_t k = fdiv(rr, B.d_perband), w = rr - k * per_band;
             tz = fdiv(w, B.d_band);
@@ -321,15 +332,27 @@ __device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P, const Box &
         tz = fdiv(rr, B.d_nty);
         ty = rr - tz * nty;
     }
-    const uint32_t tw = (uint32_t)B.tw;
-    const uint32_t ly = B.tw_log2 >= 0 ? threadIdx.x >> B.tw_log2 : fdiv(threadIdx.x, B.d_tw);
-    const uint32_t lx = threadIdx.x - ly * tw;
     const bool second = ty >= (uint32_t)B.nsub;
-    const uint32_t row = (second ? ty - (uint32_t)B.nsub : ty) * (uint32_t)B.th + ly;
-    s.x = (int)(tx * tw + lx);
-    s.y = (int)((uint32_t)(B.y0 + (second ? B.ystep : 0)) + row);
-    s.z = (int)((uint32_t)B.z0 + tz * (uint32_t)B.zstep);
-    s.valid = s.x < P.nx && s.y < P.ny && row < (uint32_t)B.rows && ly < (uint32_t)B.th;
+    const int y0 = B.y0 + (second ? B.ystep : 0);
+    Tile o;
+    o.x0 = tx * B.d_tw.d;
+    o.y0 = (uint32_t)y0 + (second ? ty - (uint32_t)B.nsub : ty) * (uint32_t)B.th;
+    o.z = (uint32_t)B.z0 + tz * (uint32_t)B.zstep;
+    o.yend = y0 + B.rows < P.ny ? y0 + B.rows : P.ny;
+    return o;
+}
+
+// The node of this thread in tile o; B: any box of the launch (the tiles' shape).
+template <int NQ, class R>
+__device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P, const Box &B, const Tile &o) {
+    using L = LatQ<NQ>;
+    Site<NQ> s;
+    const uint32_t ly = B.tw_log2 >= 0 ? threadIdx.x >> B.tw_log2 : fdiv(threadIdx.x, B.d_tw);
+    const uint32_t lx = threadIdx.x - ly * B.d_tw.d;
+    s.x = (int)(o.x0 + lx);
+    s.y = (int)(o.y0 + ly);
+    s.z = (int)o.z;
+    s.valid = s.x < P.nx && s.y < o.yend && ly < (uint32_t)B.th;
     const int x = s.valid ? s.x : 0, y = s.valid ? s.y : 0, z = s.valid ? s.z : 0;
     const uint32_t nx = P.nx, nxy = (uint32_t)P.nx * P.ny;
     const uint32_t X[3] = {uint32_t(x == 0 ? P.nx - 1 : x - 1), uint32_t(x),
@@ -354,6 +377,11 @@ __device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P, const Box &
     }
     s.wall = s.wall && s.valid;
     return s;
+}
+
+template <int NQ, class R>
+__device__ __forceinline__ Site<NQ> make_site(const DevParams<R> &P, const Box &B, uint32_t b) {
+    return make_site<NQ>(P, B, make_tile(P, B, b));
 }
 
 // x - s*e^_i lies beyond a wall (s = +1: upstream, s = -1: downstream)
@@ -996,10 +1024,10 @@ __device__ __forceinline__ Macro<R> site_moments(const DevParams<R> &P, const Si
 
 template <class St, Mode M, bool WALLS, bool FD>
 __device__ __forceinline__ void step_body(const CBuf<St> &src, const Buf<St> &dst,
-                                          const DevParams<typename St::R> &P, const Box &B, uint32_t b,
+                                          const DevParams<typename St::R> &P, const Box &B, const Tile &o,
                                           const MassFix &mf, const Wet<typename St::R> &wp) {
     using R = typename St::R;
-    const Site<St::Q> s = make_site<St::Q>(P, B, b);
+    const Site<St::Q> s = make_site<St::Q>(P, B, o);
     double rep_phi = 0.0, rep_w = 0.0;
     if (s.valid) {
         const Src<St> in = make_src(src, P);
@@ -1033,7 +1061,7 @@ template <class St, Mode M, bool WALLS, bool FD>
 __global__ void __launch_bounds__(BLOCK) step_kernel(CBuf<St> src, Buf<St> dst,
                                                      DevParams<typename St::R> P, Box B, MassFix mf,
                                                      Wet<typename St::R> wp) {
-    step_body<St, M, WALLS, FD>(src, dst, P, B, blockIdx.x, mf, wp);
+    step_body<St, M, WALLS, FD>(src, dst, P, B, make_tile(P, B, blockIdx.x), mf, wp);
 }
 
 // The same step held to 96 VGPRs (5 wavefronts per SIMD) for the wall-free
@@ -1042,7 +1070,7 @@ __global__ void __launch_bounds__(BLOCK) step_kernel(CBuf<St> src, Buf<St> dst,
 template <class St, Mode M, bool WALLS, bool FD>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5, 8)))
 step_kernel_o5(CBuf<St> src, Buf<St> dst, DevParams<typename St::R> P, Box B, MassFix mf) {
-    step_body<St, M, WALLS, FD>(src, dst, P, B, blockIdx.x, mf, Wet<typename St::R>{0, 0, 1});
+    step_body<St, M, WALLS, FD>(src, dst, P, B, make_tile(P, B, blockIdx.x), mf, Wet<typename St::R>{0, 0, 1});
 }
 
 // The whole step of a lattice with walls in y and/or z in one launch: the
@@ -1057,12 +1085,12 @@ template <class St, Mode M>
 __global__ void __launch_bounds__(BLOCK) step_all_kernel(CBuf<St> src, Buf<St> dst, DevParams<typename St::R> P, Boxes B, MassFix mf,
                 Wet<typename St::R> wp) {
     const uint32_t b = blockIdx.x;
-    if (b < B.n0) {
-        step_body<St, M, false, false>(src, dst, P, B.b[0], b, mf, Wet<typename St::R>{0, 0, 1});
-    } else {
-        const bool z = b >= B.n1;
-        step_body<St, M, true, false>(src, dst, P, z ? B.b[2] : B.b[1], z ? b - B.n1 : b - B.n0, mf, wp);
-    }
+    // the tile before the branch: with a box's arithmetic in each branch the
+    // 16-bit kernels run out of scalar registers (96^3 BF16 876 us, here 760)
+    const int k = b < B.n0 ? 0 : (b < B.n1 ? 1 : 2);
+    const Tile o = make_tile(P, B.b[k], b - (k == 0 ? 0u : (k == 1 ? B.n0 : B.n1)));
+    if (k == 0) step_body<St, M, false, false>(src, dst, P, B.b[0], o, mf, Wet<typename St::R>{0, 0, 1});
+    else step_body<St, M, true, false>(src, dst, P, B.b[0], o, mf, wp);
 }
 
 // First pass of the finite-difference variant: phi = sum of the propagated g
