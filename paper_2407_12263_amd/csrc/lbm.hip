@@ -76,11 +76,15 @@ int tile_override(const lbm_params *P) {
 
 // base: a power of two that spans whole x-rows up to 128 nodes (a row's
 // periodic wrap stays inside the tile; 128 measured best among 32, 64 and 128
-// on the 128 x 512 x 128 Rayleigh-Taylor lattice). Otherwise the row itself
-// where that takes fewer tiles or spares a row's second, partial one (16
-// steps: 75 x 61 x 43 FP32 374 -> 311 us, 133 x 110 x 90 FP16 1484 -> 1187,
-// 150^3 FP64 12670 -> 10401; even shares of a row, 50 of 100, are 20% slower
-// than the row for their unaligned segments). Rows beyond a block's threads
+// on the 128 x 512 x 128 Rayleigh-Taylor lattice). Otherwise the row itself:
+// - up to 128 nodes where its fewer tiles are fewer rounds of 256 CUs (16
+//   steps: 75 x 61 x 43 FP32 374 -> 311 us, 6 rounds -> 4, 50^3 FP64 420 -> 337,
+//   3 -> 2; with the same two rounds 20 x 70 x 50 D3Q27 FP32 203 -> 217);
+// - up to 224 where it spares a row's second, partial tile (133 x 110 x 90
+//   FP16 1484 -> 1187, 150^3 FP64 12670 -> 10401, 210 x 60 x 60 FP32 1.10 times;
+//   230 x 60 x 60 D3Q27 FP16 0.98, 250 x 50 x 30 0.97 times).
+// Even shares of a row, 50 of 100, are 20% slower than the row for their
+// unaligned segments. Rows beyond a block's threads
 // take 64 where that leaves fewer lanes idle and the state is small (300 x 200
 // FP64 248 -> 161 us, 300 x 90 x 30 FP16 887 -> 749; but D3Q27 FP32 1962 ->
 // 2036).
@@ -93,10 +97,10 @@ TileCfg tile_cfg(const lbm_params *P, int threads, bool base) {
     t.w = 1 << l;
     const size_t idle = ((size_t)(nx + 127) / 128 * 128 - (nx + 63) / 64 * 64) / 64;
     const size_t bytes = (size_t)P->nx * P->ny * P->nz * elem_bytes(P->precision) * 2 * num_pop(P);
+    auto rounds = [&](int w) { return (plane_tiles(P, w, threads / w) * P->nz + 255) / 256; };
     if (lx >= 0 && threads == BLOCK) t.w = 1 << lx;
     else if (base) ;
-    else if (nx <= threads && (plane_tiles(P, nx, threads / nx) < plane_tiles(P, t.w, threads / t.w) ||
-                               (nx > t.w && nx < BLOCK)))
+    else if (nx <= threads && (rounds(nx) < rounds(t.w) || (nx > t.w && nx <= 224)))
         t.w = nx;
     else if (nx > threads && t.w == 128 && idle && bytes < (size_t)100 << 20) t.w = 64;
     t.th = threads / t.w;
@@ -106,8 +110,13 @@ TileCfg tile_cfg(const lbm_params *P, int threads, bool base) {
     const int dflt_order = 2;
     t.order = env_int("LBM_TILE_ORDER", dflt_order);
     if (t.order < 0 || t.order > 2) t.order = dflt_order;
-    t.band = env_int("LBM_TILE_BAND", 32);
-    if (t.band < 1) t.band = 32;
+    // a band of whole-row tiles is at most 64 rows of nodes, as that of tiles
+    // of two: with 32 tiles of three or more rows the planes of some lattices
+    // fall on each other in the caches (16 steps: 80^3 FP64 1533 -> 1278 us, D3Q27
+    // 2237 -> 1859, 20 x 160 x 160 FP64 1532 -> 1279; 75 x 61 x 43 the same)
+    const int dflt_band = !base && t.w == nx && (nx & (nx - 1)) ? std::max(1, std::min(32, 64 / t.th)) : 32;
+    t.band = env_int("LBM_TILE_BAND", dflt_band);
+    if (t.band < 1) t.band = dflt_band;
     return t;
 }
 

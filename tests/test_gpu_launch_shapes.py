@@ -94,3 +94,13 @@ def test_tile_override_stays_in_the_workspace(nx, ny, nz, wall, width, precision
     eps = 2.0 ** (-11 if precision == "fp16" else -52)
     assert abs(out[0][0] - out[1][0]) <= phi.numel() * eps
     assert float((out[0][1] - out[1][1]).abs().max()) <= 64 * eps
+
+
+# whole-row tiles where they are fewer rounds of the CUs and not where they are
+# as many; bands of 64 rows of nodes with and without a remainder; rows of 224
+# and 225 nodes
+@pytest.mark.parametrize("nx,ny,nz,wall", [(50, 50, 50, (0, 0, 0)), (20, 70, 50, (0, 0, 0)), (80, 200, 24, (0, 0, 0)),
+                                           (20, 170, 90, (0, 1, 0)), (40, 100, 60, (0, 0, 1)), (224, 9, 30, (0, 1, 0)),
+                                           (225, 9, 30, (0, 0, 0)), (80, 80, 12, (1, 1, 1))])
+def test_row_tiles_and_bands_match_the_oracle(nx, ny, nz, wall):
+    test_step_matches_the_oracle(nx, ny, nz, wall)
