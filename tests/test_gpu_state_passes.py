@@ -171,3 +171,25 @@ def test_fields_stored_twice(prec, dtype, walls):
     torch.cuda.synchronize()
     for w, x, y, z in zip(want, a, b, c):
         assert torch.equal(w, x) and torch.equal(w, y) and torch.equal(w, z)
+
+
+# the same with every bit, also where a wall-free interior and wall slabs run
+# instances of their own (walls in y with 40 rows, in z, in both)
+@pytest.mark.parametrize("precision,lattice", [("fp64", 19), ("fp32", 19), ("fp32", 27), ("fp64", 27)])
+@pytest.mark.parametrize("shape,wall,over", [((20, 40, 9), (0, 1, 0), {}), ((20, 13, 9), (0, 0, 1), {}),
+                                             ((70, 30, 12), (0, 1, 1), dict(wetting=1, cos_theta=0.5)),
+                                             ((20, 13, 9), (0, 1, 0), dict(wetting=1, cos_theta=-0.3)),
+                                             ((33, 9, 5), (1, 1, 1), {})])
+def test_first_collision_equals_a_step_bit_for_bit(precision, lattice, shape, wall, over):
+    say(f"[state] first collision {precision} Q{lattice} {shape} walls {wall} {over}")
+    nx, ny, nz = shape
+    w = inputs.static_droplet(n=nx, ny=ny, nz=nz, R=3.0)
+    u0 = 0.02 * np.random.default_rng(3).standard_normal(w.u0.shape)
+    prm = dict(w.params(), precision=precision, lattice=lattice, rho2=0.4, G=(0.0, -1e-5, 0.0), wall=wall,
+               mass_fix_every=0, **over)
+    a, b = (lbm.Solver(prm, w.phi0, u0, 1e-3 * w.phi0) for _ in range(2))
+    b.set_pdfs(*a.get_pdfs())
+    for s in (a, b):
+        s.step(3)
+    for x, y in zip(gpu_fields(a), gpu_fields(b)):
+        assert np.isfinite(x).all() and np.array_equal(x, y)
