@@ -43,7 +43,10 @@ time of the transfer operations of a surrogate cycle (snapshot, base copy,
 checks, level-set push with the solver rebuild) beside the coupling
 oracle's round at the same 256^3 / 128^3 size.
 
-Prints ONE JSON line (see the keys below).
+Prints ONE JSON line on stdout: the contract's keys, the roofline figure and the
+main rates (``summary``, under 2000 characters). The whole record, with
+everything described above, goes to stderr as one JSON line after
+"[bench] record", and to a file with --record.
 """
 from __future__ import annotations
 
@@ -91,6 +94,34 @@ def measured_traffic(launch_bytes_alg: float):
         return float(kv["hbm_bytes_per_step"])
     except (KeyError, ValueError):
         return None
+
+
+def summary(rec: dict) -> dict:
+    """The stdout line of a whole record: every scalar of the contract and, of
+    the rest, the figures that a reader looks for first."""
+    keys = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+            "scaling", "vs_baseline", "dtype", "data", "config")
+    out = {k: rec[k] for k in keys}
+    roof = ("bound", "achieved", "peak", "unit", "frac", "traffic", "algorithmic_bytes_per_step", "copy_gbs",
+            "frac_of_copy")
+    out["roofline"] = {k: rec["roofline"][k] for k in roof}
+    out["secondary_mlups"] = {m: r["mlups"] for m, r in rec["secondary"].items()}
+    out["finite"] = all(c["finite"] for c in rec["checks"].values())
+    if "workloads" in rec:
+        out["workloads_mlups"] = {m: r["mlups"] for m, r in rec["workloads"].items()}
+    if "cpu_baseline" in rec:
+        out["cpu_baseline"] = {k: rec["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")}
+    sur = rec.get("surrogate", {})
+    if "error" in sur:
+        out["surrogate"] = {"error": sur["error"][:200]}
+    elif sur:
+        low, net = sur.get("lowest_error_schedule") or {}, sur.get("unet_roofline") or {}
+        out["surrogate"] = {"speedup_at_err_1e-2": sur.get("speedup_at_err_1e-2"),
+                            "lowest_phi_l2_error": low.get("phi_l2_error"), "lowest_speedup": low.get("speedup"),
+                            "unet_forward_ms": net.get("forward_ms"), "unet_mfma_frac": net.get("frac"),
+                            "train_step_ms": net.get("train_step_ms")}
+        out["surrogate"] = {k: round(v, 5) if isinstance(v, float) else v for k, v in out["surrogate"].items()}
+    return out
 
 
 def time_solver(sol, steps: int, warmup: int):
@@ -253,6 +284,7 @@ def main():
                     help="skip the droplet, rising-bubble and Taylor-Green rates")
     ap.add_argument("--no-horizons", action="store_true",
                     help="skip the runs of the 3D test problems over their horizons")
+    ap.add_argument("--record", help="also write the whole record to this file (JSON)")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py runs on one GPU only: the library has no multi-GPU path "
@@ -384,7 +416,12 @@ def main():
                                    "kind": "oracle",
                                    "sample": "coarsen, features, checks and level-set "
                                              "prolongation at 256^3 / 128^3 in FP64, once"}
-    print(json.dumps(line), flush=True)
+    record = json.dumps(line)
+    if args.record:
+        with open(args.record, "w") as f:
+            f.write(record + "\n")
+    print("[bench] record " + record, file=sys.stderr, flush=True)
+    print(json.dumps(summary(line)), flush=True)
 
 
 if __name__ == "__main__":
