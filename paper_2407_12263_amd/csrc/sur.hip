@@ -2939,18 +2939,21 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
     const int nwv = conv_waves(cin, cout, nx, ny, nz, cus,
                                xc ? ConvCall::cat : (flip || y_pool ? ConvCall::other : ConvCall::plain));
     const long tiles = P / (kTX * kTY * nwv);
-    // three output tiles per eight-wavefront block where that makes fewer
-    // columns of blocks (3, 5, 6, 7, ... tiles): the halo is staged and its
-    // fragments read once for three tiles, and no column has half the work
-    // of another. Not where the weights of all chunks fit the LDS beside the
-    // halo for two tiles but not for three. Two tiles -> three, forward, data
-    // gradient with a mask, us: 128^3 16 -> 48 142 -> 91, 172 -> 131; 48 -> 48
-    // 322 -> 232, 348 -> 265; 80 -> 48 680 -> 520, 723 -> 564; 64^3 48 -> 80
-    // 73 -> 58, 88 -> 66; 64 -> 48 at 128^3, left out, 428 -> 426, 450 -> 454.
+    // three output tiles per eight-wavefront block where that makes enough
+    // fewer columns of blocks (3, 5, 6, 9, 11, 12, ... tiles): the halo is staged
+    // and its fragments read once for three tiles, but a column of three takes
+    // 1.3 to 1.4 times one of two. Not where the weights of all chunks fit the
+    // LDS beside the halo for two tiles but not for three. Two tiles -> three,
+    // forward, data gradient with a mask, us: 128^3 16 -> 48 142 -> 91, 172 ->
+    // 131; 48 -> 48 322 -> 232, 348 -> 265; 80 -> 48 680 -> 520, 723 -> 564; 64^3
+    // 48 -> 80 73 -> 58, 88 -> 66; 48 -> 144 103 -> 92, 125 -> 116; left out 64^3
+    // 48 -> 112 (four columns or three) 73 -> 90, 81 -> 110, 80 -> 128 155 -> 220,
+    // 167 -> 247, 128 x 128 x 64 16 -> 160 (five or four) 185 -> 154, 261 -> 283;
+    // 64 -> 48 at 128^3 428 -> 426, 450 -> 454.
     // (SUR_CONV_NT3=0 keeps two; for comparisons only, both give the same bits)
     const char *n3 = std::getenv("SUR_CONV_NT3");
     const int no = cout / 16;
-    if (nwv == 8 && !xc && (up || !y_pool) && (no + 2) / 3 < (no + 1) / 2 &&
+    if (nwv == 8 && !xc && (up || !y_pool) && 7 * ((no + 2) / 3) < 5 * ((no + 1) / 2) &&
         (conv_tiled_lds(3, 8, cin / 16) <= 160 * 1024 || conv_tiled_lds(kNT, 8, cin / 16) > 160 * 1024) &&
         !(n3 && *n3 == '0')) {
         nt = 3;

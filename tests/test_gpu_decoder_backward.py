@@ -234,3 +234,11 @@ def test_unet_in_place_decoder_equals_the_written_concat(sur, grid, channels, mo
                                         ((48, 64, 48), 16, 16)])
 def test_wavefront_rule_bits_of_four(sur, grid, cc, fc, monkeypatch):
     test_eight_wavefronts_bits_of_four(sur, grid, cc, fc, monkeypatch)
+
+
+# three output tiles per block with whole columns (9 tiles) and a last one of a
+# single tile (19), and the counts that keep two (7, 8, 10)
+@pytest.mark.parametrize("grid,cin,cout", [((64, 64, 64), 48, 144), ((64, 64, 64), 16, 304), ((64, 64, 64), 48, 128),
+                                           ((48, 64, 256), 16, 160)])
+def test_three_output_tiles_by_columns(sur, grid, cin, cout, monkeypatch):
+    test_three_output_tiles_bits_of_two(sur, grid, cin, cout, monkeypatch)
