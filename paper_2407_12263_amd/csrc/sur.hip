@@ -2889,8 +2889,8 @@ int device_cus() {
     return cus;
 }
 
-// What a convolution's launch is: a forward one, one of the concat form, one
-// that pools or a data gradient.
+// What a convolution's launch is: one with neither pooling nor mask, one of the
+// concat form, one that pools or a data gradient with a mask.
 enum class ConvCall { plain, cat, other };
 
 // Wavefronts per block of conv3d_tiled_kernel: eight on 16 x 4 x 8 tiles
@@ -2937,7 +2937,7 @@ void conv_tiled_launch(const void *x, int cin, const void *xc, int cc, const voi
     long ncb = (cout + 16 * nt - 1) / (16 * nt);
     const int cus = device_cus();
     const int nwv = conv_waves(cin, cout, nx, ny, nz, cus,
-                               xc ? ConvCall::cat : (flip || y_pool ? ConvCall::other : ConvCall::plain));
+                               xc ? ConvCall::cat : ((flip && mask) || y_pool ? ConvCall::other : ConvCall::plain));
     const long tiles = P / (kTX * kTY * nwv);
     // three output tiles per eight-wavefront block where that makes enough
     // fewer columns of blocks (3, 5, 6, 9, 11, 12, ... tiles): the halo is staged
