@@ -2618,7 +2618,7 @@ __global__ void features_kernel(float *__restrict__ s, int nx, int ny, int nz) {
 // instead of a logarithm and two hyperbolic tangents, without their
 // cancellation (no change where d = 0).
 // A block takes tiles of 2^ltx x 4 x (512 >> ltx) fine nodes, eight a thread.
-// The coarse cells around a tile (at most 34 x 4 x 6) are differenced once
+// The coarse cells around a tile (34 x 4 x 6 or 6 x 4 x 34 at most) are differenced once
 // into LDS, their psi included; per node that took sixteen logarithms and 40
 // reads of 64-byte rows. The sums of phi and of max(phi (1 - phi), 0) before
 // and after the update, which the mass restoration needs, come from the same
@@ -3679,9 +3679,10 @@ int sur_prolong_update(const float *s0, const float *s1, int32_t cnx, int32_t cn
     hipStream_t st = (hipStream_t)stream;
     const long N = 8L * cnx * cny * cnz;
     const long nb = grid1(N).x;
-    // tile width: the x size, 16 to 64 nodes; the blocks' sums fill at most
-    // the scratch of 2 doubles per 256 nodes (one block writes sums itself)
-    const int ltx = 2 * cnx > 32 ? 6 : (2 * cnx > 16 ? 5 : 4), tz = 512 >> ltx;
+    // tile width: the x size, 8 to 64 nodes (8 for 1 x 64 x 64 cells: 26 us,
+    // 42 at 16 wide); the blocks' sums fill at most the scratch of 2 doubles per
+    // 256 nodes (one block writes sums itself)
+    const int ltx = 2 * cnx > 32 ? 6 : (2 * cnx > 16 ? 5 : (2 * cnx > 8 ? 4 : 3)), tz = 512 >> ltx;
     const int ntx = (2 * cnx + (1 << ltx) - 1) >> ltx, nty = (2 * cny + 3) / 4;
     const long ntiles = (long)ntx * nty * ((2 * cnz + tz - 1) / tz);
     const long nblk = std::max(1L, std::min(ntiles, nb / 2));

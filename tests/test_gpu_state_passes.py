@@ -193,3 +193,9 @@ def test_first_collision_equals_a_step_bit_for_bit(precision, lattice, shape, wa
         s.step(3)
     for x, y in zip(gpu_fields(a), gpu_fields(b)):
         assert np.isfinite(x).all() and np.array_equal(x, y)
+
+
+# tiles eight nodes wide: remainders in each axis, more tiles than scratch rows
+@pytest.mark.parametrize("cg", [(2, 3, 40), (4, 5, 33), (1, 64, 64), (3, 1, 1), (1, 70, 1), (5, 2, 3)])
+def test_level_set_update_narrow_tiles(sur, cg):
+    test_level_set_update_tile_edges(sur, cg)
