@@ -1085,12 +1085,23 @@ template <class St, Mode M>
 __global__ void __launch_bounds__(BLOCK) step_all_kernel(CBuf<St> src, Buf<St> dst, DevParams<typename St::R> P, Boxes B, MassFix mf,
                 Wet<typename St::R> wp) {
     const uint32_t b = blockIdx.x;
-    // the tile before the branch: with a box's arithmetic in each branch the
-    // 16-bit kernels run out of scalar registers (96^3 BF16 876 us, here 760)
+    // A few blocks run per CU on a small lattice, and each XCD reads these
+    // arguments from memory once per step: a line asked for only once the
+    // branch is taken is a second wait in a row. Both ends of each box are
+    // therefore held here, before the branch (an empty instruction, whose
+    // loads the compiler places and waits for), and each branch finds its own
+    // tile. 16 steps with walls in y against the tile found before the branch
+    // (which spills scalar registers in the 16-bit kernels):
+    // 26x24x28 FP32 D3Q19 130 -> 114 us, FP16 136 -> 117, 75x61x43 FP16 D3Q27
+    // 354 -> 344; 96^3 within 0.5% either way in every storage. Without the
+    // held words 96^3 BF16 took 876 us, here 755.
+    asm volatile("" ::"s"(B.b[0].th), "s"(B.b[0].d_rem.d), "s"(B.b[1].th),
+                 "s"(B.b[1].d_rem.d), "s"(B.b[2].th), "s"(B.b[2].d_rem.d));
     const int k = b < B.n0 ? 0 : (b < B.n1 ? 1 : 2);
-    const Tile o = make_tile(P, B.b[k], b - (k == 0 ? 0u : (k == 1 ? B.n0 : B.n1)));
-    if (k == 0) step_body<St, M, false, false>(src, dst, P, B.b[0], o, mf, Wet<typename St::R>{0, 0, 1});
-    else step_body<St, M, true, false>(src, dst, P, B.b[0], o, mf, wp);
+    const uint32_t first = k == 0 ? 0u : (k == 1 ? B.n0 : B.n1);
+    const Wet<typename St::R> none{0, 0, 1};
+    if (k == 0) step_body<St, M, false, false>(src, dst, P, B.b[0], make_tile(P, B.b[0], b), mf, none);
+    else step_body<St, M, true, false>(src, dst, P, B.b[0], make_tile(P, B.b[k], b - first), mf, wp);
 }
 
 // First pass of the finite-difference variant: phi = sum of the propagated g
