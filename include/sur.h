@@ -94,8 +94,9 @@ int sur_conv3d_wgrad(const void *x, int32_t cin, const void *dy, int32_t cout, i
                      float *dbias, void *stream);
 
 /* The same with the sums in an order that stays as it is over versions of this
- * library, for training runs that have to repeat; slower where the sizes are no
- * multiples of 16 x 4 x 4 and on large grids with several input chunks. */
+ * library, for training runs that have to repeat; slower on most grids of
+ * 512 points or more whose sizes are no multiples of 16 x 4 x 4, and on large
+ * grids with several groups of 16 input channels. */
 int sur_conv3d_wgrad_ordered(const void *x, int32_t cin, const void *dy, int32_t cout, int32_t nx,
                              int32_t ny, int32_t nz, float *scratch, size_t scratch_floats, float *dw,
                              float *dbias, void *stream);

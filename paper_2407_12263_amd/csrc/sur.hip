@@ -3223,7 +3223,8 @@ size_t sur_wgrad_scratch_floats(int32_t cin, int32_t cout, int32_t nx, int32_t n
     const long parts = std::max(wgrad_chunks(P), wgrad_tiled_blocks(cin, P));
     // bias partials: one per 1024 points, or one per tiled block
     const long bparts = std::max((long)grid1(P, 1024).x, wgrad_tiled_blocks(cin, P));
-    // the rows of the first reduction pass (weights, then bias)
+    // and kSumSeg rows of each that callers' buffers hold beyond the partials:
+    // the reduction keeps its segments in LDS and leaves them unused
     return (size_t)(parts * 27L * cin * cout + bparts * (long)cout + kSumSeg * 27L * cin * cout +
                     kSumSeg * (long)cout);
 }
